@@ -116,22 +116,19 @@ int wcl_set_compression(wcl_ctx *ctx, int enable);
  * storage, FP32 arithmetic).  in_dev / out_dev: complex128
  * [nrhs][V][4][3] device buffers owned by the caller; they must not
  * overlap.  WCL_ESTATE before wcl_set_params; WCL_EINVAL for nrhs < 1, an
- * unknown prec or a null pointer; WCL_ENOMEM when the context's workspace
- * cannot grow (it is allocated on first use and kept). */
+ * unknown prec or a null pointer.  Runs as one launch and
+ * needs no workspace. */
 int wcl_apply(wcl_ctx *ctx, const double *in_dev, double *out_dev, int nrhs, int dagger, int prec);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): wcl_apply
  * without any allocation.  Same arguments, layouts, ownership, results and
- * errors as wcl_apply (the same kernels run in the same order), but its
- * temporaries live in a fixed scratch array of 64 MiB per GPU that the
- * library holds until the process ends, and it records no profiling events:
- * lattices of at most 174762 sites (e.g. 8^4, 16^3x32) -- larger ones fail
- * with WCL_EINVAL; right-hand sides are processed one after another.  Every
- * call on one GPU uses that GPU's one scratch array, so calls that overlap on
- * one GPU (other streams or host threads) race and must be serialised by
- * the caller.  The context's resident fields come from wcl_set_gauge and
- * wcl_set_params, which do allocate. */
+ * errors as wcl_apply (the same kernels run in the same order), and it
+ * records no profiling events.  Its limit is lattices of at most 174762
+ * sites (e.g. 8^4, 16^3x32): larger ones fail with WCL_EINVAL.  Calls on
+ * different contexts, streams or host threads are independent.  The
+ * context's resident fields come from wcl_set_gauge and wcl_set_params,
+ * which do allocate. */
 int wcl_apply_noalloc(wcl_ctx *ctx, const double *in_dev, double *out_dev, int nrhs, int dagger, int prec);
 
 /* One step of the hot path on canonical FP64 vectors, for per-step checks of

@@ -22,14 +22,10 @@
 
 using namespace wcl;
 
-// Fixed device scratch of wcl_apply_noalloc (for callers that cannot
-// allocate): every GPU the library runs on holds its own copy until the
-// process ends.  In host code `scratch` names a host-side stand-in, not the
-// device array: host code uses only the per-device address that
-// hipGetSymbolAddress returns (g_scratch below).
+// wcl_apply_noalloc takes lattices whose FP64 input and output fields fit
+// 64 MiB (the limit of its contract; it needs no scratch).
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(64) << 20;
 constexpr size_t NOALLOC_BYTES_PER_HALF_SITE = 768;   // FP64 in + out e/o fields, both parities
-static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 namespace {
 
@@ -437,25 +433,6 @@ int reconstruct64(wcl_ctx *c, const void *b, void *x, void *tmp_o, int nrhs = 1)
     return WCL_OK;
 }
 
-// Device address of `scratch` per device, taken once per device with that
-// device current (wcl_create).
-constexpr int MAX_DEVICES = 64;
-std::mutex g_scratch_mu;
-void *g_scratch[MAX_DEVICES] = {};
-
-int scratch_init(int device)
-{
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (device < 0 || device >= MAX_DEVICES) return fail(WCL_EINVAL, "device index beyond the scratch table");
-    if (g_scratch[device]) return WCL_OK;
-    void *ptr = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !ptr)
-        return fail(WCL_EHIP, std::string("hipGetSymbolAddress(scratch): ") + hipGetErrorString(e));
-    g_scratch[device] = ptr;
-    return WCL_OK;
-}
-
 int check_prec(int prec) { return (prec == 64 || prec == 32 || prec == 16) ? WCL_OK : fail(WCL_EINVAL, "prec must be 64, 32 or 16"); }
 
 // Scalar and partial buffers for n right-hand sides: outer scalars at
@@ -661,7 +638,7 @@ int wcl_create(const int dims[4], int t_bc, const int tile[4], void *hip_stream,
         return fail(WCL_EHIP, "no HIP device");
     }
     int rc = WCL_OK;
-    if ((rc = scratch_init(c->device)) != WCL_OK || (rc = alloc((void **)&c->info, sizeof(int))) != WCL_OK ||
+    if ((rc = alloc((void **)&c->info, sizeof(int))) != WCL_OK ||
         (rc = ensure_batch(c, 1)) != WCL_OK) {
         wcl_destroy(c);
         return rc;
@@ -807,6 +784,42 @@ int wcl_set_ras_cores(wcl_ctx *c, const int cores[4])
     return rc;
 }
 
+// D, D^dag, H, T or T^-1 on canonical spinors (one launch for all
+// right-hand sides); its profiling record is that of the two parities' work.
+static int run_canon(wcl_ctx *c, int op, const double *in, double *out, int nrhs, int prec)
+{
+    CanonLaunch L{};
+    L.g = &c->g;
+    L.link_prec = eff_lprec(c, prec);
+    L.mode = op == WCL_OP_HOP ? HOP : (op == WCL_OP_CLOVER || op == WCL_OP_CLOVER_INV) ? CLOV_H : CLOVX;
+    L.dagger = op == WCL_OP_DDAG;
+    L.in = in;
+    L.out = out;
+    L.links = links_for(c, L.link_prec);
+    L.clov = op == WCL_OP_CLOVER_INV ? clovinv_for(c, prec) : clov_for(c, prec);
+    L.coef = -c->kappa;
+    L.nrhs = nrhs;
+    L.xcd = c->hop_xcd;
+    const bool hop = L.mode != CLOV_H;
+    double b = 0, f = 0;
+    if (c->prof && hop) {
+        HopLaunch W = hop_base(c, prec, prec);
+        W.mode = L.mode;
+        W.nrhs = nrhs;
+        hop_work(W, &b, &f);
+        b *= 2.0;
+        f *= 2.0;
+    } else if (c->prof) {
+        b = 2.0 * c->Vh * (2.0 * spinor_bytes(prec_bytes(prec), 1) * nrhs + 0.5 * clover_bytes(prec_bytes(prec), 1));
+        f = 2.0 * c->Vh * nrhs * 504.0;
+    }
+    return profiled_ev(c, hop ? WCL_K_HOP : WCL_K_CLOVER, b, f, [&](const LaunchEvents &ev) {
+        CanonLaunch T = L;
+        T.ev = ev;
+        return launch_canon(T, c->st);
+    });
+}
+
 int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, int prec)
 {
     if (!c || !in || !out) return fail(WCL_EINVAL, "null argument");
@@ -815,90 +828,69 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
     if (nrhs < 1) return fail(WCL_EINVAL, "nrhs must be >= 1");
     if (op < 0 || op > WCL_OP_DDAG) return fail(WCL_EINVAL, "unknown op");
     if (op == WCL_OP_RAS && prec == 64) return fail(WCL_EINVAL, "RAS runs in FP32 arithmetic: prec 32 or 16");
+    if (op == WCL_OP_SCHUR_RHS && prec != 64) return fail(WCL_EINVAL, "SCHUR_RHS is an FP64 step");
+    const bool canon = op != WCL_OP_SCHUR && op != WCL_OP_SCHUR_RHS && op != WCL_OP_RAS;
     const size_t Vh = c->Vh;
     const int lp = prec;
     const int sp = (op == WCL_OP_RAS) ? P32 : prec;  // RAS vectors are FP32 in both tiers
-    void *a64, *b64, *t64e, *t64o, *a, *b;
-    CHK(wsget(c, S_IN64, spinor_bytes(8, Vh) * 2, &a64));
-    CHK(wsget(c, S_OUT64, spinor_bytes(8, Vh) * 2, &b64));
-    CHK(wsget(c, S_TMP64E, spinor_bytes(8, Vh), &t64e));
-    CHK(wsget(c, S_TMP64O, spinor_bytes(8, Vh), &t64o));
-    if (sp != P64) {
-        CHK(wsget(c, S_IN32, spinor_bytes(prec_bytes(sp), Vh) * 2, &a));
-        CHK(wsget(c, S_OUT32, spinor_bytes(prec_bytes(sp), Vh) * 2 + spinor_bytes(prec_bytes(sp), Vh), &b));
-    } else {
-        a = a64;
-        b = b64;
-    }
-    for (int k = 0; k < nrhs; k++) {
+    // right-hand sides per set of launches: the links of a launch serve all of
+    // them; at most 16, and a workspace of at most 1 GiB a field
+    const size_t hb = half_bytes(sp, Vh);
+    const int step = canon ? std::min(nrhs, 4096)
+                           : (int)std::max<size_t>(1, std::min<size_t>({(size_t)nrhs, 16, ((size_t)1 << 30) / (2 * hb)}));
+    for (int k = 0; k < nrhs; k += step) {
+        const int n = std::min(step, nrhs - k);
         const double *ink = in + (size_t)k * c->V * 24;
         double *outk = out + (size_t)k * c->V * 24;
-        HIPCHK(launch_pack_spinor(c->g, ink, a64, c->st));
-        if (sp != P64) HIPCHK(launch_convert(P64, sp, 2 * Vh, Vh, Vh, a64, a, nullptr, 0, 1.0, c->st));
-        switch (op) {
-        case WCL_OP_HOP:
-            for (int p = 0; p < 2; p++) {
-                HopLaunch L = hop_base(c, lp, sp);
-                L.mode = HOP;
-                L.p = p;
-                L.in = par(a, sp, Vh, 1 - p);
-                L.out = par(b, sp, Vh, p);
-                CHK(run_hop(c, L));
-            }
-            break;
-        case WCL_OP_CLOVER:
-        case WCL_OP_CLOVER_INV:
-            for (int p = 0; p < 2; p++)
-                CHK(run_clover(c, lp, sp, p, op == WCL_OP_CLOVER ? clov_for(c, lp) : clovinv_for(c, lp),
-                               par(a, sp, Vh, p), par(b, sp, Vh, p)));
-            break;
-        case WCL_OP_SCHUR:
-            CHK(schur(c, lp, sp, par(a, sp, Vh, 0), par(b, sp, Vh, 0), sp == P64 ? t64o : par(b, sp, Vh, 2), nullptr));
-            HIPCHK(launch_zero(P64, 12 * Vh, par(b64, P64, Vh, 1), c->st));
-            break;
-        case WCL_OP_SCHUR_RHS:
-            if (sp != P64) return fail(WCL_EINVAL, "SCHUR_RHS is an FP64 step");
-            CHK(schur_rhs64(c, a64, par(b64, P64, Vh, 0), t64o, t64e));
-            HIPCHK(launch_zero(P64, 12 * Vh, par(b64, P64, Vh, 1), c->st));
-            break;
-        case WCL_OP_RAS: {
+        if (canon) {
+            CHK(run_canon(c, op, ink, outk, n, prec));
+            continue;
+        }
+        void *a, *b, *t;
+        if (op == WCL_OP_SCHUR_RHS) {
+            void *te;
+            CHK(wsget(c, S_IN64, 2 * hb * step, &a));
+            CHK(wsget(c, S_OUT64, hb * step, &b));
+            CHK(wsget(c, S_TMP64E, hb * step, &te));
+            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            HIPCHK(launch_pack(c->g, P64, false, ink, a, 2 * hb, n, c->st));
+            CHK(schur_rhs64(c, a, b, t, te, n));
+            HIPCHK(launch_unpack(c->g, P64, true, b, hb, outk, n, c->st));
+            continue;
+        }
+        CHK(wsget(c, S_IN32, hb * step, &a));
+        CHK(wsget(c, S_OUT32, hb * step, &b));
+        HIPCHK(launch_pack(c->g, sp, true, ink, a, hb, n, c->st));
+        if (op == WCL_OP_SCHUR) {
+            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            CHK(schur(c, lp, sp, a, b, t, nullptr, n));
+        } else {
             RasLaunch R{};
             R.g = &c->g;
             R.overlap = c->ras_overlap;
             R.iters = c->ras_iters;
             R.jacobi = c->ras_solver == WCL_RAS_JACOBI;
             R.link_prec = eff_lprec(c, lp);
-            R.in = par(a, sp, Vh, 0);
-            R.out = par(b, sp, Vh, 0);
+            R.in = a;
+            R.out = b;
             R.links = links_for(c, R.link_prec);
             R.links_site = c->U32s;
             R.clov_inv = clovinv_for(c, lp);
             R.kappa2 = (float)(c->kappa * c->kappa);
             R.sc = nullptr;
-            R.nrhs = 1;
-            R.stride = 0;
+            R.nrhs = n;
+            R.stride = hb;
             if (c->ras_mult) {
                 void *rt, *tt, *to;
-                CHK(wsget(c, S_SAPR, half_bytes(sp, Vh), &rt));
-                CHK(wsget(c, S_SAPT, half_bytes(sp, Vh), &tt));
-                CHK(wsget(c, S_SAPO, half_bytes(sp, Vh), &to));
-                CHK(run_sap(c, R, lp, sp, R.in, R.out, rt, tt, to));
+                CHK(wsget(c, S_SAPR, hb * step, &rt));
+                CHK(wsget(c, S_SAPT, hb * step, &tt));
+                CHK(wsget(c, S_SAPO, hb * step, &to));
+                CHK(run_sap(c, R, lp, sp, a, b, rt, tt, to));
             } else {
                 CHK(run_ras(c, R));
             }
-            HIPCHK(launch_zero(P64, 12 * Vh, par(b64, P64, Vh, 1), c->st));
-            break;
         }
-        case WCL_OP_D:
-        case WCL_OP_DDAG:
-            CHK(full_D(c, lp, sp, a, b, op == WCL_OP_DDAG));
-            break;
-        }
-        if (sp != P64) {
-            const bool even_only = (op == WCL_OP_SCHUR || op == WCL_OP_RAS);
-            HIPCHK(launch_convert(sp, P64, (even_only ? 1 : 2) * Vh, Vh, Vh, b, b64, nullptr, 0, 1.0, c->st));
-        }
-        HIPCHK(launch_unpack_spinor(c->g, b64, outk, c->st));
+        HIPCHK(launch_unpack(c->g, sp, true, b, hb, outk, n, c->st));
     }
     return WCL_OK;
 }
@@ -908,23 +900,15 @@ int wcl_apply(wcl_ctx *c, const double *in, double *out, int nrhs, int dagger, i
     return wcl_apply_op(c, dagger ? WCL_OP_DDAG : WCL_OP_D, in, out, nrhs, prec);
 }
 
-// wcl_apply without allocation: the same kernels in the same order as
-// wcl_apply (pack, precision cast, the two parity launches of D, cast back,
-// unpack), with every temporary in this device's fixed scratch instead of
-// the context's workspace, and no profiling events.  Layout of the scratch
-// per call: [0, 384 Vh) the FP64 e/o input (both parities), then either the
-// FP64 e/o output or, for prec 32/16, the cast input and output (192 Vh
-// each at most); the cast-back output reuses the FP64 input region.
+// wcl_apply needs no temporaries, so this is wcl_apply without its profiling
+// records; the lattice limit of the entry point stands.
 int wcl_apply_noalloc(wcl_ctx *c, const double *in, double *out, int nrhs, int dagger, int prec)
 {
     if (!c || !in || !out) return fail(WCL_EINVAL, "null argument");
     if (!c->have_params) return fail(WCL_ESTATE, "operator used before wcl_set_gauge and wcl_set_params");
     CHK(check_prec(prec));
     if (nrhs < 1) return fail(WCL_EINVAL, "nrhs must be >= 1");
-    if (c->device < 0 || c->device >= MAX_DEVICES || !g_scratch[c->device])
-        return fail(WCL_ESTATE, "no scratch address for the context's device");
-    const size_t Vh = c->Vh;
-    const size_t need = NOALLOC_BYTES_PER_HALF_SITE * Vh;
+    const size_t need = NOALLOC_BYTES_PER_HALF_SITE * c->Vh;
     if (need > NOALLOC_SCRATCH_BYTES) {
         char msg[200];
         snprintf(msg, sizeof msg,
@@ -933,43 +917,11 @@ int wcl_apply_noalloc(wcl_ctx *c, const double *in, double *out, int nrhs, int d
                  need, NOALLOC_SCRATCH_BYTES, 2 * (NOALLOC_SCRATCH_BYTES / NOALLOC_BYTES_PER_HALF_SITE));
         return fail(WCL_EINVAL, msg);
     }
-    char *base = (char *)g_scratch[c->device];
-    const int sp = prec;
-    void *a64 = base;                                   // 2 x spinor_bytes(8, Vh) = 384 Vh
-    void *b = base + 2 * spinor_bytes(8, Vh);           // FP64 output, or the cast input ...
-    void *a = b;
-    void *bs = (char *)b + 2 * spinor_bytes(prec_bytes(sp), Vh);   // ... and the cast output
-    if (sp == P64) bs = b;
-    for (int k = 0; k < nrhs; k++) {
-        const double *ink = in + (size_t)k * c->V * 24;
-        double *outk = out + (size_t)k * c->V * 24;
-        HIPCHK(launch_pack_spinor(c->g, ink, a64, c->st));
-        const void *src = a64;
-        if (sp != P64) {
-            HIPCHK(launch_convert(P64, sp, 2 * Vh, Vh, Vh, a64, a, nullptr, 0, 1.0, c->st));
-            src = a;
-        }
-        for (int p = 0; p < 2; p++) {
-            HopLaunch L = hop_base(c, prec, sp);
-            L.mode = CLOVX;
-            L.dagger = dagger ? 1 : 0;
-            L.p = p;
-            L.in = par(src, sp, Vh, 1 - p);
-            L.x = par(src, sp, Vh, p);
-            L.out = par(bs, sp, Vh, p);
-            L.clov = clov_for(c, prec);
-            L.coef = -c->kappa;
-            L.in_stride = L.out_stride = L.x_stride = full_bytes(sp, Vh);
-            HIPCHK(launch_hop(L, c->st));
-        }
-        if (sp != P64) {
-            HIPCHK(launch_convert(sp, P64, 2 * Vh, Vh, Vh, bs, a64, nullptr, 0, 1.0, c->st));
-            HIPCHK(launch_unpack_spinor(c->g, a64, outk, c->st));
-        } else {
-            HIPCHK(launch_unpack_spinor(c->g, bs, outk, c->st));
-        }
-    }
-    return WCL_OK;
+    const bool prof = c->prof;
+    c->prof = false;
+    const int rc = wcl_apply(c, in, out, nrhs, dagger, prec);
+    c->prof = prof;
+    return rc;
 }
 
 void wcl_default_opts(wcl_solve_opts *o)
@@ -1622,15 +1574,13 @@ extern "C" int wcl_solve(wcl_ctx *c, const double *b, double *x, int nrhs, const
     HIPCHK(hipStreamSynchronize(c->st));
     const auto t0 = std::chrono::steady_clock::now();
     const size_t fb = full_bytes(P64, c->Vh);
-    for (int k = 0; k < n; k++)
-        HIPCHK(launch_pack_spinor(c->g, b + (size_t)k * c->V * 24, (char *)w.b + k * fb, c->st));
+    HIPCHK(launch_pack(c->g, P64, false, b, w.b, fb, n, c->st));
     if (o.adjoint) HIPCHK(launch_gamma5(2 * (size_t)n, c->Vh, w.b, c->st));  // D^dag = g5 D g5
     // initial guess (may alias x): the solve of D x' = g5 b starts from g5 x0
     // when adjoint
     const bool warm = o.x0_dev != nullptr;
     if (warm) {
-        for (int k = 0; k < n; k++)
-            HIPCHK(launch_pack_spinor(c->g, o.x0_dev + (size_t)k * c->V * 24, (char *)w.x + k * fb, c->st));
+        HIPCHK(launch_pack(c->g, P64, false, o.x0_dev, w.x, fb, n, c->st));
         if (o.adjoint) HIPCHK(launch_gamma5(2 * (size_t)n, c->Vh, w.x, c->st));
     }
     std::vector<double> bnorm2(n);
@@ -1675,8 +1625,7 @@ extern "C" int wcl_solve(wcl_ctx *c, const double *b, double *x, int nrhs, const
         else if (info[k].status == WCL_OK && rel[k] > o.tol) info[k].status = WCL_ENOCONV;
     }
     if (o.adjoint) HIPCHK(launch_gamma5(2 * (size_t)n, c->Vh, w.x, c->st));
-    for (int k = 0; k < n; k++)
-        HIPCHK(launch_unpack_spinor(c->g, (char *)w.x + k * fb, x + (size_t)k * c->V * 24, c->st));
+    HIPCHK(launch_unpack(c->g, P64, false, w.x, fb, x, n, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     int worst = WCL_OK;
@@ -1824,8 +1773,8 @@ extern "C" int wcl_grad(wcl_ctx *c, const double *x, const double *y, double *gU
     CHK(wsget(c, S_GG, link_bytes(8, Vh), &G));
     CHK(wsget(c, S_GHX, f64, &HX));
     CHK(wsget(c, S_GCX, f64, &CX));
-    HIPCHK(launch_pack_spinor(c->g, x, X, c->st));
-    HIPCHK(launch_pack_spinor(c->g, y, Y, c->st));
+    HIPCHK(launch_pack(c->g, P64, false, x, X, 0, 1, c->st));
+    HIPCHK(launch_pack(c->g, P64, false, y, Y, 0, 1, c->st));
     HIPCHK(launch_grad(c->g, c->U64, X, Y, K, c->kappa, c->csw, G, c->st));
     HIPCHK(launch_export_links(c->g, G, gU, c->st));
     // dL/dkappa = Re<y, H x> + c_sw Re<y, C x>

@@ -35,52 +35,6 @@ WCL_D int coords_to_h(const Geom &g, const int x[4])
 }
 
 // ---------------------------------------------------------------------------
-// Canonical <-> e/o FP64 spinors.
-__global__ void k_pack_spinor(Geom g, const double2 *__restrict__ canon, double2 *__restrict__ eo)
-{
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int V = 2 * g.Vh;
-    if (n >= V) return;
-    int x[4];
-    canon_coords(g, n, x);
-    const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
-    const size_t h = coords_to_h(g, x);
-    double2 *dst = eo + (size_t)p * 12 * g.Vh;
-    const double2 *src = canon + (size_t)n * 12;
-#pragma unroll
-    for (int i = 0; i < 12; i++) dst[i * (size_t)g.Vh + h] = src[i];
-}
-
-__global__ void k_unpack_spinor(Geom g, const double2 *__restrict__ eo, double2 *__restrict__ canon)
-{
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int V = 2 * g.Vh;
-    if (n >= V) return;
-    int x[4];
-    canon_coords(g, n, x);
-    const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
-    const size_t h = coords_to_h(g, x);
-    const double2 *src = eo + (size_t)p * 12 * g.Vh;
-    double2 *dst = canon + (size_t)n * 12;
-#pragma unroll
-    for (int i = 0; i < 12; i++) dst[i] = src[i * (size_t)g.Vh + h];
-}
-
-hipError_t launch_pack_spinor(const Geom &g, const double *canon, void *eo, hipStream_t st)
-{
-    const int V = 2 * g.Vh;
-    k_pack_spinor<<<(V + 255) / 256, 256, 0, st>>>(g, (const double2 *)canon, (double2 *)eo);
-    return hipGetLastError();
-}
-
-hipError_t launch_unpack_spinor(const Geom &g, const void *eo, double *canon, hipStream_t st)
-{
-    const int V = 2 * g.Vh;
-    k_unpack_spinor<<<(V + 255) / 256, 256, 0, st>>>(g, (const double2 *)eo, (double2 *)canon);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 // Gauge ingest: canonical U[V][4][3][3] complex128 -> internal link fields.
 __global__ void k_ingest_gauge(Geom g, const double2 *__restrict__ canon, void *u64, void *u32, void *u16)
 {

@@ -92,9 +92,27 @@ hipError_t launch_clover(const Geom &g, int link_prec, int spin_prec, int p, con
                          const void *in, void *out, hipStream_t st, int nrhs = 1, size_t in_stride = 0,
                          size_t out_stride = 0, LaunchEvents ev = {});
 
-// Canonical complex128 [V][4][3] <-> e/o FP64 field [2][12][Vh] double2.
-hipError_t launch_pack_spinor(const Geom &g, const double *canon, void *eo, hipStream_t st);
-hipError_t launch_unpack_spinor(const Geom &g, const void *eo, double *canon, hipStream_t st);
+// nrhs canonical complex128 [V][4][3] spinors <-> e/o fields (storage prec:
+// P64, P32, P16), eo_stride bytes apart.  even_only: the even half field
+// alone; odd_zero: the canonical odd sites are written as zero.
+hipError_t launch_pack(const Geom &g, int prec, bool even_only, const double *canon, void *eo, size_t eo_stride, int nrhs,
+                       hipStream_t st);
+hipError_t launch_unpack(const Geom &g, int prec, bool odd_zero, const void *eo, size_t eo_stride, double *canon, int nrhs,
+                         hipStream_t st);
+// out = H in (mode HOP), A in (CLOV_H), A in + coef H in (CLOVX; dagger:
+// projectors swapped) on nrhs canonical spinors, both parities, spinors
+// rounded to the storage of link_prec.
+struct CanonLaunch {
+    const Geom *g;
+    int link_prec, mode, dagger;
+    const double *in;
+    double *out;
+    const void *links, *clov;
+    double coef;
+    int nrhs, xcd;
+    LaunchEvents ev;
+};
+hipError_t launch_canon(const CanonLaunch &L, hipStream_t st);
 // Canonical U [V][4][3][3] -> internal link fields (any null pointer skipped).
 hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16,
                                hipStream_t st);
