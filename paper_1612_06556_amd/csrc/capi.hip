@@ -502,7 +502,7 @@ enum Slot {
     // plain FP64 full-field vectors
     S_PR, S_PRT, S_PP, S_PV, S_PS, S_PT, S_PX,
     // gradient
-    S_GX, S_GY, S_GK, S_GG, S_GHX, S_GCX,
+    S_GX, S_GY, S_GK,
     // SU(3) check partials
     S_SU3,
     // multiplicative Schwarz: residual, Dhat z, Schur odd temporary
@@ -1766,40 +1766,18 @@ extern "C" int wcl_grad(wcl_ctx *c, const double *x, const double *y, double *gU
     if (!c->have_params) return fail(WCL_ESTATE, "wcl_grad before wcl_set_gauge and wcl_set_params");
     const size_t Vh = c->Vh;
     const size_t f64 = 2 * spinor_bytes(8, Vh);
-    void *X, *Y, *K, *G, *HX, *CX;
+    void *X, *Y, *K;
     CHK(wsget(c, S_GX, f64, &X));
     CHK(wsget(c, S_GY, f64, &Y));
-    CHK(wsget(c, S_GK, 2 * 6 * 9 * 16 * Vh, &K));
-    CHK(wsget(c, S_GG, link_bytes(8, Vh), &G));
-    CHK(wsget(c, S_GHX, f64, &HX));
-    CHK(wsget(c, S_GCX, f64, &CX));
+    CHK(wsget(c, S_GK, 2 * 54 * sizeof(double) * Vh, &K));
     HIPCHK(launch_pack(c->g, P64, false, x, X, 0, 1, c->st));
     HIPCHK(launch_pack(c->g, P64, false, y, Y, 0, 1, c->st));
-    HIPCHK(launch_grad(c->g, c->U64, X, Y, K, c->kappa, c->csw, G, c->st));
-    HIPCHK(launch_export_links(c->g, G, gU, c->st));
-    // dL/dkappa = Re<y, H x> + c_sw Re<y, C x>
-    for (int p = 0; p < 2; p++) {
-        HopLaunch L = hop_base(c, P64, P64);
-        L.mode = HOP;
-        L.p = p;
-        L.in = par(X, P64, Vh, 1 - p);
-        L.out = par(HX, P64, Vh, p);
-        CHK(run_hop(c, L));
-    }
-    HIPCHK(launch_sigmaF(c->g, c->U64, X, CX, c->st));
-    const void *a[2] = {Y, Y}, *b[2] = {HX, CX};
-    HIPCHK(launch_dots(P64, 24 * Vh, 2, a, b, c->partials, nullptr, c->st, 1, 0, c->pstride));
-    double part[2][RED_BLOCKS];   // the real parts of <y, Hx> and <y, Cx> (terms 0 and 2)
-    HIPCHK(hipMemcpyAsync(part[0], c->partials, sizeof(part[0]), hipMemcpyDeviceToHost, c->st));
-    HIPCHK(hipMemcpyAsync(part[1], c->partials + 2 * (size_t)c->pstride, sizeof(part[1]), hipMemcpyDeviceToHost,
-                          c->st));
-    HIPCHK(hipStreamSynchronize(c->st));
-    double yhx = 0.0, ycx = 0.0;
-    for (int j = 0; j < RED_BLOCKS; j++) {
-        yhx += part[0][j];
-        ycx += part[1][j];
-    }
-    *gk = yhx + c->csw * ycx;
+    // the partial sums of dL/dkappa: one per 32 half-sites, the buffer holds
+    // 6 pstride >= 6 Vh / 64 of them
+    HIPCHK(launch_grad(c->g, c->U64, X, Y, (double *)K, c->kappa, c->csw, gU, c->partials, c->st));
+    HIPCHK(launch_finalize(NORM_ONLY, 1, c->partials, SF(c), c->st, 1, nullptr, 6 * c->pstride, grad_parts(c->g)));
+    CHK(read_sc(c, HF(c), SF(c), 1));   // synchronises the stream
+    *gk = HF(c)[0].t[0];
     return WCL_OK;
 }
 

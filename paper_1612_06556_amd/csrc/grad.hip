@@ -3,18 +3,22 @@
 //
 // With dL = -Re<y, dD x> and D = T - kappa H, T = 1 - c_sw kappa C,
 // C = sum_{mu<nu} sigma_{mu nu} F_{mu nu}:
-//   link gradient G (dL = Re sum conj(G_ab) dU_ab, PyTorch's convention)
-//     hopping:  kappa s sum_spin [ ((1 - g_mu) y(x)) x(x+mu)^dag + x(x) ((1 + g_mu) y(x+mu))^dag ]
-//     clover :  every plaquette loop E0 E1 E2 E3 (corners c0..c3, c_j at the
-//               start of edge E_j) enters Q at each of its corners, so
-//               dL = sum_plaquettes sum_j Re[z tr(rot_j(E0 E1 E2 E3) K(c_j))],
-//               z = -i c_sw kappa / 8, K = M' + M'^dag, M' the traceless part
-//               of M_ab = sum_{s,t} sigma_st x_t,a conj(y_s,b).  For the edge at
-//               position i the derivative is X_i = sum_j (loop from edge i+1
-//               round to edge i-1 with K(c_j) inserted at corner j), and
-//               G += conj(z) X_i^dag (edge U) or z X_i (edge U^dag).
-//   kappa:  dL/dkappa = Re<y, H x> + c_sw Re<y, C x>.
-// The kernel gathers, for each link, the 6 plaquettes that contain it.
+//   link gradient G = kappa (W + V) (dL = Re sum conj(G_ab) dU_ab, PyTorch's
+//   convention), for the link U_mu(x):
+//     hopping:  W = s sum_spin [ ((1 - g_mu) y(x)) x(x+mu)^dag + x(x) ((1 + g_mu) y(x+mu))^dag ];
+//               a projected spinor's lower half repeats its upper half up to
+//               units, so each spin sum is a sum over two half spinors;
+//     clover:   every closed loop E0 E1 E2 E3 from E0 = U_mu(x) round a plaquette
+//               (corners c0 = x, c1 = x + mu, c2, c3 at the start of each edge)
+//               enters Q at each corner, so dL = kappa Re[-i t tr(dU X)],
+//               t = +-c_sw / 8 (+ for the orientation mu nu, mu < nu),
+//               X = (K1 E1 + E1 K2) E2 E3 + E1 E2 (K3 E3 + E3 K0)
+//               with K = M' + M'^dag, M' the traceless part of
+//               M_ab = sum_{s,t} sigma_st x_t,a conj(y_s,b), and V += i t X^dag.
+//   kappa:  dL/dkappa = Re<y, H x> + c_sw Re<y, C x>.  H is linear and C
+//           homogeneous of degree 4 in the links, so it is the sum over links
+//           of Re tr(W^dag U) + Re tr(V^dag U) / 4: no further operator pass.
+// A thread gathers, for one link, the 6 plaquettes that contain it.
 #include "wcl_launch.h"
 
 namespace wcl {
@@ -23,6 +27,17 @@ namespace wcl {
 struct Mat {
     cplx<double> a[9];
 };
+struct Herm {   // d: diagonal; o: entries (0,1), (0,2), (1,2)
+    double d[3];
+    cplx<double> o[3];
+};
+
+WCL_D cplx<double> mentry(const Mat &A, const Mat &B, int i, int j)   // (A B)_ij
+{
+    cplx<double> s = A.a[i * 3] * B.a[j];
+    s = cfma(A.a[i * 3 + 1], B.a[3 + j], s);
+    return cfma(A.a[i * 3 + 2], B.a[6 + j], s);
+}
 
 WCL_D Mat mmul(const Mat &A, const Mat &B)
 {
@@ -30,12 +45,7 @@ WCL_D Mat mmul(const Mat &A, const Mat &B)
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
-        for (int j = 0; j < 3; j++) {
-            cplx<double> s = A.a[i * 3] * B.a[j];
-            s = cfma(A.a[i * 3 + 1], B.a[3 + j], s);
-            s = cfma(A.a[i * 3 + 2], B.a[6 + j], s);
-            C.a[i * 3 + j] = s;
-        }
+        for (int j = 0; j < 3; j++) C.a[i * 3 + j] = mentry(A, B, i, j);
     return C;
 }
 
@@ -49,57 +59,46 @@ WCL_D Mat mdag(const Mat &A)
     return C;
 }
 
-WCL_D Mat madd(const Mat &A, const Mat &B)
+// P E + E Q
+WCL_D Mat edge_insert(const Herm &P, const Mat &E, const Herm &Q)
 {
     Mat C;
 #pragma unroll
-    for (int k = 0; k < 9; k++) C.a[k] = A.a[k] + B.a[k];
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const double d = P.d[i] + Q.d[j];
+            cplx<double> s = {d * E.a[i * 3 + j].re, d * E.a[i * 3 + j].im};
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                if (k > i) s = cfma(P.o[i + k - 1], E.a[k * 3 + j], s);
+                if (k < i) s = cjfma(P.o[i + k - 1], E.a[k * 3 + j], s);
+                if (k < j) s = cfma(Q.o[j + k - 1], E.a[i * 3 + k], s);
+                if (k > j) s = cjfma(Q.o[j + k - 1], E.a[i * 3 + k], s);
+            }
+            C.a[i * 3 + j] = s;
+        }
     return C;
 }
 
-WCL_D int gcoords_to_h(const Geom &g, const int x[4])
+// K field: double [2 p][6 planes][9][Vh], the 3 diagonal entries and Re, Im of
+// (0,1), (0,2), (1,2)
+WCL_D Herm K_at(const double *K, int p, uint32_t h, uint32_t Vh, int plane)
 {
-    int blk = 0, lin = 0;
+    const uint32_t base = ((uint32_t)(p * 6 + plane) * 9 * Vh + h) * 8u;
+    Herm m;
 #pragma unroll
-    for (int mu = 0; mu < 4; mu++) {
-        const int b = x[mu] / g.B[mu];
-        blk += b * g.sb[mu];
-        lin += (x[mu] - b * g.B[mu]) * g.sl[mu];
+    for (uint32_t k = 0; k < 3; k++) {
+        m.d[k] = ldf<double>(K, base + k * Vh * 8u);
+        m.o[k] = {ldf<double>(K, base + (3 + 2 * k) * Vh * 8u), ldf<double>(K, base + (4 + 2 * k) * Vh * 8u)};
     }
-    return blk * g.Hb + (lin >> 1);
-}
-
-// site x + d (periodic), its parity and half index
-WCL_D void shifted(const Geom &g, const int x[4], const int d[4], int &p, int &h)
-{
-    int y[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) y[k] = (x[k] + d[k] + 2 * g.L[k]) % g.L[k];
-    p = (y[0] + y[1] + y[2] + y[3]) & 1;
-    h = gcoords_to_h(g, y);
-}
-
-WCL_D Mat link_at_d(const Geom &g, const void *u64, const int x[4], const int d[4], int mu)
-{
-    int p, h;
-    shifted(g, x, d, p, h);
-    Mat m;
-    load_link<double, double>(u64, mu, p, h, g.Vh, m.a);
     return m;
 }
 
-// K field: double2 [2 p][6 planes][9][Vh]
-WCL_D Mat K_at(const Geom &g, const double2 *K, const int x[4], const int d[4], int plane)
+WCL_D Mat link64(const void *u64, int mu, int p, uint32_t h, uint32_t Vh)
 {
-    int p, h;
-    shifted(g, x, d, p, h);
     Mat m;
-    const size_t base = ((size_t)p * 6 + plane) * 9;
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        const double2 v = K[(base + k) * g.Vh + h];
-        m.a[k] = {v.x, v.y};
-    }
+    load_link<double, double>(u64, mu, p, h, Vh, m.a);
     return m;
 }
 
@@ -108,23 +107,53 @@ WCL_D Mat K_at(const Geom &g, const double2 *K, const int x[4], const int d[4], 
 // plane order: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
 __host__ __device__ constexpr int plane_pauli(int p) { return p == 0 ? 3 : p == 1 ? 2 : p == 2 ? 1 : p == 3 ? 1 : p == 4 ? 2 : 3; }
 __host__ __device__ constexpr double plane_up(int p) { return (p == 0 || p == 3) ? -1.0 : 1.0; }
-__host__ __device__ constexpr double plane_lo(int p) { return (p == 2 || p == 4 || p == 5) ? -1.0 : (p == 0 || p == 3 ? -1.0 : 1.0); }
+__host__ __device__ constexpr double plane_lo(int p) { return p == 1 ? 1.0 : -1.0; }
 
-// Pauli matrix entries (s, t)
-WCL_D cplx<double> pauli(int m, int s, int t)
+// M_ab for one plane: sum over chirality blocks and s, t of
+// e sigma_st x_t,a conj(y_s,b), sigma a Pauli matrix.
+template <int PL>
+WCL_D cplx<double> plane_m(const cplx<double> x[12], const cplx<double> y[12], int a, int b)
 {
-    if (m == 1) return (s != t) ? cplx<double>{1.0, 0.0} : cplx<double>{0.0, 0.0};
-    if (m == 2) {
-        if (s == 0 && t == 1) return {0.0, -1.0};
-        if (s == 1 && t == 0) return {0.0, 1.0};
-        return {0.0, 0.0};
+    constexpr int m = plane_pauli(PL);
+    cplx<double> r = {0.0, 0.0};
+#pragma unroll
+    for (int blk = 0; blk < 2; blk++) {
+        const double e = blk == 0 ? plane_up(PL) : plane_lo(PL);
+        const cplx<double> x0 = x[6 * blk + a], x1 = x[6 * blk + 3 + a], y0 = y[6 * blk + b], y1 = y[6 * blk + 3 + b];
+        cplx<double> q;
+        if constexpr (m == 1) {
+            q = cjfma(y0, x1, conjm(y1, x0));                    // s=0,t=1 and s=1,t=0
+        } else if constexpr (m == 2) {
+            const cplx<double> d = cjfma(y0, x1, -conjm(y1, x0));  // -i (01) + i (10)
+            q = {d.im, -d.re};
+        } else {
+            q = cjfma(y0, x0, -conjm(y1, x1));
+        }
+        r = {fma(e, q.re, r.re), fma(e, q.im, r.im)};
     }
-    if (s != t) return {0.0, 0.0};
-    return {s == 0 ? 1.0 : -1.0, 0.0};
+    return r;
 }
 
-// K_plane(x) for all 6 planes at one site.
-__global__ void __launch_bounds__(128) k_grad_K(Geom g, const double2 *X, const double2 *Y, double2 *K)
+template <int PL>
+WCL_D void plane_K(const cplx<double> x[12], const cplx<double> y[12], double *K, uint32_t Vh)
+{
+    double d[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) d[a] = 2.0 * plane_m<PL>(x, y, a, a).re;
+    const double tr = (d[0] + d[1] + d[2]) / 3.0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) K[(size_t)(PL * 9 + a) * Vh] = d[a] - tr;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int a = k == 2 ? 1 : 0, b = k == 0 ? 1 : 2;
+        const cplx<double> u = plane_m<PL>(x, y, a, b), v = plane_m<PL>(x, y, b, a);
+        K[(size_t)(PL * 9 + 3 + 2 * k) * Vh] = u.re + v.re;
+        K[(size_t)(PL * 9 + 4 + 2 * k) * Vh] = u.im - v.im;
+    }
+}
+
+// K of all 6 planes at one site (streaming: two spinors in, 432 bytes out).
+__global__ void __launch_bounds__(128) k_grad_K(Geom g, const double2 *X, const double2 *Y, double *K)
 {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= 2 * g.Vh) return;
@@ -133,225 +162,180 @@ __global__ void __launch_bounds__(128) k_grad_K(Geom g, const double2 *X, const 
     cplx<double> xs[12], ys[12];
     load_spinor<double, double>(X + (size_t)p * 12 * g.Vh, h, g.Vh, xs);
     load_spinor<double, double>(Y + (size_t)p * 12 * g.Vh, h, g.Vh, ys);
-    for (int pl = 0; pl < 6; pl++) {
-        const int m = plane_pauli(pl);
-        cplx<double> M[9];
-#pragma unroll
-        for (int k = 0; k < 9; k++) M[k] = {0.0, 0.0};
-        for (int blk = 0; blk < 2; blk++) {
-            const double e = blk == 0 ? plane_up(pl) : plane_lo(pl);
-            for (int s = 0; s < 2; s++)
-                for (int t = 0; t < 2; t++) {
-                    const cplx<double> sg = e * pauli(m, s, t);
-                    if (sg.re == 0.0 && sg.im == 0.0) continue;
-                    // M_ab += sigma_st x_t,a conj(y_s,b)
-                    for (int a = 0; a < 3; a++)
-                        for (int b = 0; b < 3; b++) {
-                            const cplx<double> xy = {xs[(2 * blk + t) * 3 + a].re, xs[(2 * blk + t) * 3 + a].im};
-                            const cplx<double> yc = {ys[(2 * blk + s) * 3 + b].re, -ys[(2 * blk + s) * 3 + b].im};
-                            M[a * 3 + b] = M[a * 3 + b] + sg * (xy * yc);
-                        }
-                }
-        }
-        cplx<double> tr = {(M[0].re + M[4].re + M[8].re) / 3.0, (M[0].im + M[4].im + M[8].im) / 3.0};
-        M[0] = M[0] - tr; M[4] = M[4] - tr; M[8] = M[8] - tr;
-        const size_t base = ((size_t)p * 6 + pl) * 9;
-        for (int a = 0; a < 3; a++)
-            for (int b = 0; b < 3; b++) {
-                const cplx<double> v = {M[a * 3 + b].re + M[b * 3 + a].re, M[a * 3 + b].im - M[b * 3 + a].im};
-                K[(base + a * 3 + b) * g.Vh + h] = make_double2(v.re, v.im);
-            }
-    }
+    double *k = K + (size_t)p * 54 * g.Vh + h;
+    plane_K<0>(xs, ys, k, g.Vh);
+    plane_K<1>(xs, ys, k, g.Vh);
+    plane_K<2>(xs, ys, k, g.Vh);
+    plane_K<3>(xs, ys, k, g.Vh);
+    plane_K<4>(xs, ys, k, g.Vh);
+    plane_K<5>(xs, ys, k, g.Vh);
 }
 
-WCL_D int plane_index(int a, int b)
+// Change of the in-tile and tile index of a step in one direction; steps in
+// different directions add up.
+struct Step {
+    int lin, blk;
+};
+WCL_D Step step_of(const Geom &g, const Site &s, int mu, int dir)
 {
-    // a < b
-    return a == 0 ? (b - 1) : a == 1 ? (b + 1) : 5;
+    int l = 0, b = 0, B = 1, NB = 1, sl = 0, sb = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        if (k == mu) { l = s.l[k]; b = s.b[k]; B = g.B[k]; NB = g.NB[k]; sl = g.sl[k]; sb = g.sb[k]; }
+    const int lc = l + dir;
+    if (lc >= 0 && lc < B) return {dir * sl, 0};
+    const int nb = b + dir;
+    return {-dir * (B - 1) * sl, (nb < 0 ? NB - 1 : nb >= NB ? 1 - NB : dir) * sb};
+}
+WCL_D uint32_t at(const Geom &g, const Site &s, Step a, Step b = {0, 0})
+{
+    return (uint32_t)((s.blk + a.blk + b.blk) * g.Hb + ((s.lin + a.lin + b.lin) >> 1));
 }
 
-// Link gradient at (parity p, h, direction mu): hopping + clover.
-__global__ void __launch_bounds__(64) k_grad_link(Geom g, const void *u64, const double2 *X, const double2 *Y,
-                                                  const double2 *K, double kappa, double csw, void *G)
+// V += i t X^dag for one plaquette.  LOWER: the one on the -nu side, whose
+// edges run U_nu(x+mu-nu)^dag, U_mu(x-nu)^dag, U_nu(x-nu).
+template <bool LOWER>
+WCL_D void clover_plaquette(const Geom &g, const void *u64, const double *K, const Site &s, int p, uint32_t h, int mu,
+                            int nu, int plane, Step sm, double t, const Herm &K0, const Herm &K1, Mat &V)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 8 * g.Vh) return;
-    const int mu = idx / (2 * g.Vh);
-    const int rem = idx - mu * 2 * g.Vh;
-    const int p = rem / g.Vh;
-    const int h = rem - p * g.Vh;
-    const Site s = decompose(g, h, p);
-    const int *x = s.x;
-    Mat Gm;
-#pragma unroll
-    for (int k = 0; k < 9; k++) Gm.a[k] = {0.0, 0.0};
-
-    // hopping part
+    const uint32_t Vh = g.Vh;
+    const Step sn = step_of(g, s, nu, LOWER ? -1 : 1);
+    const uint32_t hm = at(g, s, sm), hn = at(g, s, sn), hmn = at(g, s, sm, sn);
+    const int q = 1 - p;
+    Mat E1 = LOWER ? link64(u64, nu, p, hmn, Vh) : link64(u64, nu, q, hm, Vh);
+    const Mat E2 = mdag(link64(u64, mu, q, hn, Vh));
+    Mat E3 = LOWER ? link64(u64, nu, q, hn, Vh) : link64(u64, nu, p, h, Vh);
+    if (LOWER) E1 = mdag(E1);
+    else E3 = mdag(E3);
     {
-        int d[4] = {0, 0, 0, 0};
-        d[mu] = 1;
-        int pf, hf;
-        shifted(g, x, d, pf, hf);
-        cplx<double> xn[12], yn[12], xf[12], yf[12];
-        load_spinor<double, double>(X + (size_t)p * 12 * g.Vh, h, g.Vh, xn);
-        load_spinor<double, double>(Y + (size_t)p * 12 * g.Vh, h, g.Vh, yn);
-        load_spinor<double, double>(X + (size_t)pf * 12 * g.Vh, hf, g.Vh, xf);
-        load_spinor<double, double>(Y + (size_t)pf * 12 * g.Vh, hf, g.Vh, yf);
-        cplx<double> w[12], v[12], hh[6];
+        const Mat A = edge_insert(K1, E1, K_at(K, p, hmn, Vh, plane));
+        const Mat B = mmul(E2, E3);
 #pragma unroll
-        for (int k = 0; k < 12; k++) { w[k] = {0.0, 0.0}; v[k] = {0.0, 0.0}; }
-        switch (mu) {
-        case 0: project<0, -1, double>(yn, hh); accumulate<0, -1, double>(w, hh);
-                project<0, 1, double>(yf, hh); accumulate<0, 1, double>(v, hh); break;
-        case 1: project<1, -1, double>(yn, hh); accumulate<1, -1, double>(w, hh);
-                project<1, 1, double>(yf, hh); accumulate<1, 1, double>(v, hh); break;
-        case 2: project<2, -1, double>(yn, hh); accumulate<2, -1, double>(w, hh);
-                project<2, 1, double>(yf, hh); accumulate<2, 1, double>(v, hh); break;
-        default: project<3, -1, double>(yn, hh); accumulate<3, -1, double>(w, hh);
-                 project<3, 1, double>(yf, hh); accumulate<3, 1, double>(v, hh); break;
-        }
-        const double sgn = (mu == 3 && g.tbc < 0 && x[3] == g.L[3] - 1) ? -1.0 : 1.0;
-        const double c = kappa * sgn;
-        for (int a = 0; a < 3; a++)
-            for (int b = 0; b < 3; b++) {
-                cplx<double> acc = {0.0, 0.0};
-                for (int sp = 0; sp < 4; sp++) {
-                    acc = cjfma(xf[sp * 3 + b], w[sp * 3 + a], acc);   // w_a conj(x'_b)
-                    acc = cjfma(v[sp * 3 + b], xn[sp * 3 + a], acc);   // x_a conj(v_b)
-                }
-                Gm.a[a * 3 + b] = Gm.a[a * 3 + b] + c * acc;
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const cplx<double> x = mentry(A, B, i, j);
+                V.a[j * 3 + i] = {fma(t, x.im, V.a[j * 3 + i].re), fma(t, x.re, V.a[j * 3 + i].im)};
             }
     }
-
-    // clover part: the 6 plaquettes containing U_mu(x)
-    const cplx<double> z = {0.0, -csw * kappa / 8.0};
-    for (int nu = 0; nu < 4; nu++) {
-        if (nu == mu) continue;
-        const int a = mu < nu ? mu : nu, b = mu < nu ? nu : mu;
-        const int pl = plane_index(a, b);
-        for (int which = 0; which < 2; which++) {
-            // lower-left corner c0 and the position i of U_mu(x) in E0 E1 E2 E3
-            int c0[4] = {x[0], x[1], x[2], x[3]};
-            int pos;
-            if (mu == a) {
-                pos = which == 0 ? 0 : 2;
-                if (which == 1) c0[nu] -= 1;
-            } else {
-                pos = which == 0 ? 1 : 3;
-                if (which == 0) c0[nu] -= 1;
-            }
-            int da[4] = {0, 0, 0, 0}, db[4] = {0, 0, 0, 0}, dab[4] = {0, 0, 0, 0}, o[4] = {0, 0, 0, 0};
-            da[a] = 1; db[b] = 1; dab[a] = 1; dab[b] = 1;
-            Mat E[4], Kc[4];
-            E[0] = link_at_d(g, u64, c0, o, a);
-            E[1] = link_at_d(g, u64, c0, da, b);
-            E[2] = mdag(link_at_d(g, u64, c0, db, a));
-            E[3] = mdag(link_at_d(g, u64, c0, o, b));
-            Kc[0] = K_at(g, K, c0, o, pl);
-            Kc[1] = K_at(g, K, c0, da, pl);
-            Kc[2] = K_at(g, K, c0, dab, pl);
-            Kc[3] = K_at(g, K, c0, db, pl);
-            // X_i = sum_j (E_{i+1} .. with K_j inserted at corner j)
-            const int i1 = (pos + 1) & 3, i2 = (pos + 2) & 3, i3 = (pos + 3) & 3;
-            Mat X = mmul(mmul(Kc[i1], E[i1]), mmul(E[i2], E[i3]));
-            X = madd(X, mmul(mmul(E[i1], Kc[i2]), mmul(E[i2], E[i3])));
-            X = madd(X, mmul(mmul(E[i1], E[i2]), mmul(Kc[i3], E[i3])));
-            X = madd(X, mmul(mmul(E[i1], E[i2]), mmul(E[i3], Kc[pos])));
-            const bool daggered = (pos >= 2);
-            if (!daggered) {
-                const Mat Xd = mdag(X);
-                const cplx<double> zc = {z.re, -z.im};
+    {
+        const Mat A = mmul(E1, E2);
+        const Mat B = edge_insert(K_at(K, q, hn, Vh, plane), E3, K0);
 #pragma unroll
-                for (int k = 0; k < 9; k++) Gm.a[k] = Gm.a[k] + zc * Xd.a[k];
-            } else {
+        for (int i = 0; i < 3; i++)
 #pragma unroll
-                for (int k = 0; k < 9; k++) Gm.a[k] = Gm.a[k] + z * X.a[k];
+            for (int j = 0; j < 3; j++) {
+                const cplx<double> x = mentry(A, B, i, j);
+                V.a[j * 3 + i] = {fma(t, x.im, V.a[j * 3 + i].re), fma(t, x.re, V.a[j * 3 + i].im)};
             }
-        }
     }
-    store_link<double, double>(G, mu, p, h, g.Vh, Gm.a);
 }
 
-// C x = sum_{mu<nu} sigma_{mu nu} F_{mu nu} x on one parity, from the links.
-WCL_D Mat fs_from_links(const Geom &g, const void *u64, const int x[4], int mu, int nu)
+// W_ab of direction MU from the half spinors of y(x), x(x+mu) and x(x), y(x+mu).
+template <int MU>
+WCL_D void hop_outer(const cplx<double> xn[12], const cplx<double> yn[12], const cplx<double> xf[12],
+                     const cplx<double> yf[12], double sgn, Mat &W)
 {
-    int o[4] = {0, 0, 0, 0};
-    int pm[4] = {0, 0, 0, 0}, pn[4] = {0, 0, 0, 0}, mm[4] = {0, 0, 0, 0}, mn[4] = {0, 0, 0, 0};
-    int mmpn[4] = {0, 0, 0, 0}, mmmn[4] = {0, 0, 0, 0}, pmmn[4] = {0, 0, 0, 0};
-    pm[mu] = 1; pn[nu] = 1; mm[mu] = -1; mn[nu] = -1;
-    mmpn[mu] = -1; mmpn[nu] = 1;
-    mmmn[mu] = -1; mmmn[nu] = -1;
-    pmmn[mu] = 1; pmmn[nu] = -1;
-    const Mat Umu = link_at_d(g, u64, x, o, mu), Unu = link_at_d(g, u64, x, o, nu);
-    Mat Q = mmul(mmul(Umu, link_at_d(g, u64, x, pm, nu)), mmul(mdag(link_at_d(g, u64, x, pn, mu)), mdag(Unu)));
-    Q = madd(Q, mmul(mmul(Unu, mdag(link_at_d(g, u64, x, mmpn, mu))),
-                     mmul(mdag(link_at_d(g, u64, x, mm, nu)), link_at_d(g, u64, x, mm, mu))));
-    Q = madd(Q, mmul(mmul(mdag(link_at_d(g, u64, x, mm, mu)), mdag(link_at_d(g, u64, x, mmmn, nu))),
-                     mmul(link_at_d(g, u64, x, mmmn, mu), link_at_d(g, u64, x, mn, nu))));
-    Q = madd(Q, mmul(mmul(mdag(link_at_d(g, u64, x, mn, nu)), link_at_d(g, u64, x, mn, mu)),
-                     mmul(link_at_d(g, u64, x, pmmn, nu), mdag(Umu))));
-    Mat F;
+    cplx<double> a[6], b[6], c[6], d[6];
+    project<MU, -1, double>(yn, a);
+    project<MU, -1, double>(xf, b);
+    project<MU, 1, double>(xn, c);
+    project<MU, 1, double>(yf, d);
+#pragma unroll
     for (int i = 0; i < 3; i++)
-        for (int j = 0; j < 3; j++) {
-            const double wr = Q.a[i * 3 + j].re - Q.a[j * 3 + i].re;
-            const double wi = Q.a[i * 3 + j].im + Q.a[j * 3 + i].im;
-            F.a[i * 3 + j] = {wi * 0.125, -wr * 0.125};
-        }
-    const double tr = (F.a[0].re + F.a[4].re + F.a[8].re) / 3.0;
-    F.a[0].re -= tr; F.a[4].re -= tr; F.a[8].re -= tr;
-    F.a[0].im = F.a[4].im = F.a[8].im = 0.0;
-    return F;
-}
-
-__global__ void __launch_bounds__(64) k_sigmaF(Geom g, const void *u64, const double2 *X, double2 *out)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 2 * g.Vh) return;
-    const int p = idx / g.Vh;
-    const int h = idx - p * g.Vh;
-    const Site s = decompose(g, h, p);
-    cplx<double> xs[12], o[12];
-    load_spinor<double, double>(X + (size_t)p * 12 * g.Vh, h, g.Vh, xs);
 #pragma unroll
-    for (int k = 0; k < 12; k++) o[k] = {0.0, 0.0};
-    const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {1, 2, 3, 2, 3, 3};
-    for (int pl = 0; pl < 6; pl++) {
-        const Mat F = fs_from_links(g, u64, s.x, pa[pl], pb[pl]);
-        const int m = plane_pauli(pl);
-        for (int blk = 0; blk < 2; blk++) {
-            const double e = blk == 0 ? plane_up(pl) : plane_lo(pl);
-            for (int sp = 0; sp < 2; sp++)
-                for (int t = 0; t < 2; t++) {
-                    const cplx<double> sg = e * pauli(m, sp, t);
-                    if (sg.re == 0.0 && sg.im == 0.0) continue;
-                    for (int a = 0; a < 3; a++) {
-                        cplx<double> acc = {0.0, 0.0};
-                        for (int b = 0; b < 3; b++) acc = cfma(F.a[a * 3 + b], xs[(2 * blk + t) * 3 + b], acc);
-                        o[(2 * blk + sp) * 3 + a] = o[(2 * blk + sp) * 3 + a] + sg * acc;
-                    }
-                }
+        for (int j = 0; j < 3; j++) {
+            cplx<double> w = conjm(b[j], a[i]);
+            w = cjfma(b[3 + j], a[3 + i], w);
+            w = cjfma(d[j], c[i], w);
+            w = cjfma(d[3 + j], c[3 + i], w);
+            W.a[i * 3 + j] = {sgn * w.re, sgn * w.im};
         }
-    }
-    store_spinor<double, double>(out + (size_t)p * 12 * g.Vh, h, g.Vh, o);
 }
 
-// Internal link field -> canonical [V][4][3][3] complex128.
-__global__ void k_export_links(Geom g, const void *G, double2 *canon)
+WCL_D double re_trace_dag(const Mat &A, const Mat &U)   // Re tr(A^dag U)
 {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= 2 * g.Vh) return;
-    int x[4];
-    int r = n;
-    x[0] = r % g.L[0]; r /= g.L[0];
-    x[1] = r % g.L[1]; r /= g.L[1];
-    x[2] = r % g.L[2];
-    x[3] = r / g.L[2];
-    const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
-    const int h = gcoords_to_h(g, x);
-    for (int mu = 0; mu < 4; mu++) {
-        cplx<double> u[9];
-        load_link<double, double>(G, mu, p, h, g.Vh, u);
-        for (int k = 0; k < 9; k++) canon[((size_t)n * 4 + mu) * 9 + k] = make_double2(u[k].re, u[k].im);
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < 9; k++) t = fma(A.a[k].re, U.a[k].re, fma(A.a[k].im, U.a[k].im, t));
+    return t;
+}
+
+// A workgroup takes 32 pairs of x-neighbours (64 sites, both parities), each
+// wave one direction, so the four links of a site meet in LDS and the gradient
+// leaves in the caller's canonical order (1152-byte runs).  One plaquette is
+// one straight piece of code run six times with run-time directions: the
+// matrices stay in registers (an earlier form indexed them at run time: 1.2 KB
+// of scratch a thread) and the code in the instruction cache.
+// Bound by the neighbour matrices' way through L2 (4.8 KB a link) at one wave
+// per SIMD: 222 us at 16^3x32 (11.3 TB/s of those reads; 1559 us, then 50 for
+// the canonical copy, 261 for C x and 43 for H x, before).  Holding one row of
+// a product at a time, or fencing the plaquettes apart, measured 4 to 8% slower.
+__global__ void __launch_bounds__(256) k_grad_link(Geom g, const void *u64, const double2 *X, const double2 *Y,
+                                                   const double *K, double kappa, double csw, double2 *gU,
+                                                   double *partial)
+{
+    constexpr int ROW = 64 * 9 + 1;   // 16-byte units of one direction
+    __shared__ double2 lds[4 * ROW];
+    __shared__ uint32_t base[32];     // canonical index of the x-even site | its parity << 31
+    __shared__ double red[4];
+    const int lane = threadIdx.x & 63;
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int p = lane >> 5;
+    const uint32_t Vh = g.Vh, h0 = (uint32_t)xcd_block(blockIdx.x, gridDim.x) * 32u;
+    const uint32_t np = min(32u, Vh - h0), h = h0 + (lane & 31);
+    double gk = 0.0;
+    if ((uint32_t)(lane & 31) < np) {
+        const Site s = decompose(g, (int)h, p);
+        if (mu == 0 && p == 0) {
+            const uint32_t odd = (uint32_t)(s.x[1] + s.x[2] + s.x[3]) & 1u;
+            base[lane] = (uint32_t)((s.x[0] & ~1) + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3]))) | (odd << 31);
+        }
+        const Step sm = step_of(g, s, mu, 1);
+        const uint32_t hm = at(g, s, sm);
+        const Mat U = link64(u64, mu, p, h, Vh);
+        Mat G;
+#pragma unroll
+        for (int k = 0; k < 9; k++) G.a[k] = {0.0, 0.0};
+        for (int k = 1; k < 4; k++) {
+            const int nu = (mu + k) & 3;
+            const int a = min(mu, nu), b = max(mu, nu);
+            const int plane = a == 0 ? b - 1 : a + b;
+            const double t = (mu < nu ? 0.125 : -0.125) * csw;
+            const Herm K0 = K_at(K, p, h, Vh, plane), K1 = K_at(K, 1 - p, hm, Vh, plane);
+            clover_plaquette<false>(g, u64, K, s, p, h, mu, nu, plane, sm, t, K0, K1, G);
+            clover_plaquette<true>(g, u64, K, s, p, h, mu, nu, plane, sm, -t, K0, K1, G);
+        }
+        gk = 0.25 * re_trace_dag(G, U);
+        Mat W;
+        {
+            cplx<double> xn[12], yn[12], xf[12], yf[12];
+            const double2 *X1 = X + (size_t)p * 12 * Vh, *Y1 = Y + (size_t)p * 12 * Vh;
+            const double2 *X2 = X + (size_t)(1 - p) * 12 * Vh, *Y2 = Y + (size_t)(1 - p) * 12 * Vh;
+            load_spinor<double, double>(X1, h, Vh, xn);
+            load_spinor<double, double>(Y1, h, Vh, yn);
+            load_spinor<double, double>(X2, hm, Vh, xf);
+            load_spinor<double, double>(Y2, hm, Vh, yf);
+            const double sgn = (mu == 3 && g.tbc < 0 && s.x[3] == g.L[3] - 1) ? -1.0 : 1.0;
+            if (mu == 0) hop_outer<0>(xn, yn, xf, yf, sgn, W);
+            else if (mu == 1) hop_outer<1>(xn, yn, xf, yf, sgn, W);
+            else if (mu == 2) hop_outer<2>(xn, yn, xf, yf, sgn, W);
+            else hop_outer<3>(xn, yn, xf, yf, sgn, W);
+        }
+        gk += re_trace_dag(W, U);
+#pragma unroll
+        for (int k = 0; k < 9; k++)
+            lds[mu * ROW + lane * 9 + k] = make_double2(kappa * (G.a[k].re + W.a[k].re), kappa * (G.a[k].im + W.a[k].im));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) gk += __shfl_xor(gk, o, 64);
+    if (lane == 0) red[mu] = gk;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    for (uint32_t i = threadIdx.x; i < np * 72u; i += 256u) {
+        const uint32_t pr = i / 72u, r = i - pr * 72u, xo = r / 36u, e = r - xo * 36u;
+        const uint32_t b = base[pr], q = (xo + (b >> 31)) & 1u;
+        gU[(size_t)(b & 0x7fffffffu) * 36 + r] = lds[(e / 9u) * ROW + (q * 32u + pr) * 9u + e % 9u];
     }
 }
 
@@ -369,30 +353,17 @@ __global__ void k_gamma5(size_t nsec, size_t Vh, double2 *f)
     }
 }
 
-hipError_t launch_grad(const Geom &g, const void *u64, const void *X, const void *Y, void *K, double kappa,
-                       double csw, void *G, hipStream_t st)
+int grad_parts(const Geom &g) { return (g.Vh + 31) / 32; }
+
+hipError_t launch_grad(const Geom &g, const void *u64, const void *X, const void *Y, double *K, double kappa,
+                       double csw, double *gU, double *partial, hipStream_t st)
 {
     const int n2 = 2 * g.Vh;
-    k_grad_K<<<(n2 + 127) / 128, 128, 0, st>>>(g, (const double2 *)X, (const double2 *)Y, (double2 *)K);
+    k_grad_K<<<(n2 + 127) / 128, 128, 0, st>>>(g, (const double2 *)X, (const double2 *)Y, K);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int n8 = 8 * g.Vh;
-    k_grad_link<<<(n8 + 63) / 64, 64, 0, st>>>(g, u64, (const double2 *)X, (const double2 *)Y, (const double2 *)K,
-                                               kappa, csw, G);
-    return hipGetLastError();
-}
-
-hipError_t launch_sigmaF(const Geom &g, const void *u64, const void *X, void *out, hipStream_t st)
-{
-    const int n2 = 2 * g.Vh;
-    k_sigmaF<<<(n2 + 63) / 64, 64, 0, st>>>(g, u64, (const double2 *)X, (double2 *)out);
-    return hipGetLastError();
-}
-
-hipError_t launch_export_links(const Geom &g, const void *G, double *canon, hipStream_t st)
-{
-    const int n = 2 * g.Vh;
-    k_export_links<<<(n + 127) / 128, 128, 0, st>>>(g, G, (double2 *)canon);
+    k_grad_link<<<grad_parts(g), 256, 0, st>>>(g, u64, (const double2 *)X, (const double2 *)Y, K, kappa, csw,
+                                               (double2 *)gU, partial);
     return hipGetLastError();
 }
 

@@ -110,3 +110,23 @@ def test_backward_16x32_timed():
     gU_o, gk_o = orc.grad(to_host(x.detach()), y)
     assert rel(to_host(tU.grad), gU_o) <= 1e-10
     assert abs(float(tk.grad) - gk_o) <= 1e-10 * abs(gk_o)
+
+
+@pytest.mark.parametrize("dims,tile,kappa", [
+    ((6, 6, 6, 6), None, 0.11),            # 648 pairs: 20 workgroups of 32 and one of 8
+    ((4, 6, 8, 4), None, 0.12),            # 2^4 tiles, 384 pairs
+    ((8, 8, 8, 16), (8, 4, 8, 4), 0.125),  # tiles spanning whole x-rows
+    ((4, 4, 4, 4), None, 0.0),             # dL/dkappa without the kappa of the link gradient
+])
+def test_grad_shapes(dims, tile, kappa):
+    """Link and kappa gradient against the oracle's formula on lattices whose
+    last workgroup is ragged and on other tiles."""
+    lat, orc, _ = setup(dims, -1, kappa, 1.3, 91, tile)
+    x, y = synth.gaussian_spinor(dims, 92), synth.gaussian_spinor(dims, 93)
+    gU, gk = lat.grad(to_gpu(x), to_gpu(y))
+    rU, rk = orc.grad(x, y)
+    scale = abs(rk) + float(np.linalg.norm(x) * np.linalg.norm(y))
+    print(dims, np.linalg.norm(to_host(gU) - rU), abs(gk - rk) / scale, flush=True)
+    assert np.linalg.norm(to_host(gU) - rU) <= 1e-10 * max(np.linalg.norm(rU), 1e-300) or kappa == 0.0
+    assert kappa != 0.0 or not to_host(gU).any()
+    assert abs(gk - rk) <= 1e-10 * scale
