@@ -27,14 +27,6 @@ struct PairLds {
     uint32_t base[NP];   // canonical index of the pair's x-even site | its parity << 31
 };
 
-WCL_D uint32_t pair_base(const Geom &g, int h)
-{
-    const Site s = decompose(g, h, 0);
-    const uint32_t odd = (uint32_t)(s.x[1] + s.x[2] + s.x[3]) & 1u;
-    const uint32_t n = (uint32_t)((s.x[0] & ~1) + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3])));
-    return n | (odd << 31);
-}
-
 // One complex number in the storage of a tier: rounded as the tier's fields
 // are (FP16 from the FP32 value).
 template <typename SS>

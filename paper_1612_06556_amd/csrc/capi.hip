@@ -55,6 +55,14 @@ struct Buf {
     size_t bytes = 0;
 };
 
+// What the setup kernels report: zero unless a check failed, and cleared by the
+// call that reads a failure, so a call that succeeds writes nothing.
+struct Flags {
+    unsigned long long defect;   // bits of the largest SU(3) defect above the tolerance
+    int bad_blocks;              // clover blocks that are not positive definite
+    int pad;
+};
+
 }  // namespace
 
 struct wcl_ctx {
@@ -67,7 +75,7 @@ struct wcl_ctx {
     void *U32s = nullptr;                   // per-site copy of U32c (the fused Schwarz kernel's)
     int compress = 0;                       // FP32/FP16 tiers read the two-row links
     void *T64 = nullptr, *Ti64 = nullptr, *T32 = nullptr, *Ti32 = nullptr, *T16 = nullptr, *Ti16 = nullptr;
-    int *info = nullptr;
+    Flags *flags = nullptr, *flags_host = nullptr;   // device, pinned host
     double kappa = 0, csw = 0;
     bool have_gauge = false, have_params = false;
     int ras_overlap = 1, ras_iters = 4, ras_solver = WCL_RAS_MR;
@@ -108,6 +116,24 @@ int alloc(void **p, size_t bytes)
         (void)hipGetLastError();
         return fail(WCL_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
     }
+    return WCL_OK;
+}
+
+int alloc_host(void **p, size_t bytes)
+{
+    if (hipHostMalloc(p, bytes, hipHostMallocDefault) != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+        return fail(WCL_ENOMEM, "hipHostMalloc failed");
+    }
+    return WCL_OK;
+}
+
+int clear_flags(wcl_ctx *c)
+{
+    *c->flags_host = Flags{};
+    HIPCHK(hipMemcpyAsync(c->flags, c->flags_host, sizeof(Flags), hipMemcpyHostToDevice, c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
     return WCL_OK;
 }
 
@@ -550,15 +576,28 @@ int ensure_gras(wcl_ctx *c)
 // own rounding is 6e-8).
 constexpr double SU3_TOL = 1e-7;
 
-// Check that the FP64 links are SU(3) (two-row storage rebuilds row 2 as
-// conj(row0 x row1)), then write the FP32 and FP16 two-row copies.
-int build_compressed(wcl_ctx *c)
+int su3_failure(double m)
+{
+    char msg[160];
+    snprintf(msg, sizeof msg, "two-row link storage needs SU(3) links: largest defect %.3e > %.1e", m, SU3_TOL);
+    return fail(WCL_EINVAL, msg);
+}
+
+int alloc_compressed(wcl_ctx *c)
 {
     const size_t Vh = c->Vh;
     // each copy on its own: a failed allocation leaves the others for the next call
     if (!c->U32c) CHK(alloc(&c->U32c, link_bytes_c(P32C, Vh)));
     if (!c->U16c) CHK(alloc(&c->U16c, link_bytes_c(P16C, Vh)));
     if (!c->U32s) CHK(alloc(&c->U32s, link_bytes_c(P32C, Vh)));
+    return WCL_OK;
+}
+
+// Check that the FP64 links are SU(3) (two-row storage rebuilds row 2 as
+// conj(row0 x row1)), then write the FP32 and FP16 two-row copies.
+int build_compressed(wcl_ctx *c)
+{
+    CHK(alloc_compressed(c));
     const int nb = 256;
     void *part;
     CHK(wsget(c, S_SU3, nb * sizeof(double), &part));
@@ -569,11 +608,7 @@ int build_compressed(wcl_ctx *c)
     double m = 0.0;
     for (double d : h)
         if (d > m || d != d) m = d;
-    if (!(m <= SU3_TOL)) {
-        char msg[160];
-        snprintf(msg, sizeof msg, "two-row link storage needs SU(3) links: largest defect %.3e > %.1e", m, SU3_TOL);
-        return fail(WCL_EINVAL, msg);
-    }
+    if (!(m <= SU3_TOL)) return su3_failure(m);
     HIPCHK(launch_compress_links(c->g, c->U64, c->U32c, c->U16c, c->U32s, c->st));
     return WCL_OK;
 }
@@ -638,7 +673,8 @@ int wcl_create(const int dims[4], int t_bc, const int tile[4], void *hip_stream,
         return fail(WCL_EHIP, "no HIP device");
     }
     int rc = WCL_OK;
-    if ((rc = alloc((void **)&c->info, sizeof(int))) != WCL_OK ||
+    if ((rc = alloc((void **)&c->flags, sizeof(Flags))) != WCL_OK || (rc = alloc_host((void **)&c->flags_host, sizeof(Flags))) != WCL_OK ||
+        (rc = clear_flags(c)) != WCL_OK ||
         (rc = ensure_batch(c, 1)) != WCL_OK) {
         wcl_destroy(c);
         return rc;
@@ -658,13 +694,14 @@ int wcl_destroy(wcl_ctx *c)
 {
     if (!c) return WCL_OK;
     (void)hipStreamSynchronize(c->st);
-    void *ptrs[] = {c->U64, c->U32, c->U16, c->U32c, c->U16c, c->U32s, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16, c->info,
+    void *ptrs[] = {c->U64, c->U32, c->U16, c->U32c, c->U16c, c->U32s, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16, c->flags,
                     c->partials, c->sc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (Buf &b : c->ws)
         if (b.p) (void)hipFree(b.p);
     if (c->sc_host) (void)hipHostFree(c->sc_host);
+    if (c->flags_host) (void)hipHostFree(c->flags_host);
     for (auto &r : c->recs) {
         (void)hipEventDestroy(r.e0);
         (void)hipEventDestroy(r.e1);
@@ -683,10 +720,21 @@ int wcl_set_gauge(wcl_ctx *c, const double *U)
     if (!c->U64) CHK(alloc(&c->U64, link_bytes(8, Vh)));
     if (!c->U32) CHK(alloc(&c->U32, link_bytes(4, Vh)));
     if (!c->U16) CHK(alloc(&c->U16, link_bytes(2, Vh)));
-    HIPCHK(launch_ingest_gauge(c->g, U, c->U64, c->U32, c->U16, c->st));
     c->have_gauge = false;
     c->have_params = false;
-    if (c->compress) CHK(build_compressed(c));
+    if (c->compress) CHK(alloc_compressed(c));
+    HIPCHK(launch_ingest_gauge(c->g, U, c->U64, c->U32, c->U16, c->compress ? c->U32c : nullptr, c->U16c, c->U32s, SU3_TOL,
+                               &c->flags->defect, c->st));
+    if (c->compress) {
+        HIPCHK(hipMemcpyAsync(c->flags_host, c->flags, sizeof(Flags), hipMemcpyDeviceToHost, c->st));
+        HIPCHK(hipStreamSynchronize(c->st));
+        if (c->flags_host->defect) {
+            double m;
+            memcpy(&m, &c->flags_host->defect, sizeof m);
+            CHK(clear_flags(c));
+            return su3_failure(m);
+        }
+    }
     c->have_gauge = true;
     return WCL_OK;
 }
@@ -719,15 +767,16 @@ int wcl_set_params(wcl_ctx *c, double kappa, double csw)
         if (!*cl[i]) CHK(alloc(cl[i], clover_bytes(cl_bytes[i], Vh)));
     c->kappa = kappa;
     c->csw = csw;
-    int zero = 0, bad = 0;
-    HIPCHK(hipMemcpyAsync(c->info, &zero, sizeof(int), hipMemcpyHostToDevice, c->st));
     void *fbuf;
     CHK(wsget(c, S_CLOVF, (size_t)6 * 9 * 2 * c->Vh * sizeof(double), &fbuf));
     HIPCHK(launch_clover_build(c->g, c->U64, csw * kappa, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16,
-                               c->info, (double *)fbuf, c->st));
-    HIPCHK(hipMemcpyAsync(&bad, c->info, sizeof(int), hipMemcpyDeviceToHost, c->st));
+                               &c->flags->bad_blocks, (double *)fbuf, c->st));
+    HIPCHK(hipMemcpyAsync(c->flags_host, c->flags, sizeof(Flags), hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
-    if (bad) return fail(WCL_ENAN, std::to_string(bad) + " clover blocks are not positive definite");
+    if (const int bad = c->flags_host->bad_blocks) {
+        CHK(clear_flags(c));
+        return fail(WCL_ENAN, std::to_string(bad) + " clover blocks are not positive definite");
+    }
     c->have_params = true;
     return WCL_OK;
 }

@@ -171,27 +171,6 @@ __global__ void __launch_bounds__(128) k_grad_K(Geom g, const double2 *X, const 
     plane_K<5>(xs, ys, k, g.Vh);
 }
 
-// Change of the in-tile and tile index of a step in one direction; steps in
-// different directions add up.
-struct Step {
-    int lin, blk;
-};
-WCL_D Step step_of(const Geom &g, const Site &s, int mu, int dir)
-{
-    int l = 0, b = 0, B = 1, NB = 1, sl = 0, sb = 0;
-#pragma unroll
-    for (int k = 0; k < 4; k++)
-        if (k == mu) { l = s.l[k]; b = s.b[k]; B = g.B[k]; NB = g.NB[k]; sl = g.sl[k]; sb = g.sb[k]; }
-    const int lc = l + dir;
-    if (lc >= 0 && lc < B) return {dir * sl, 0};
-    const int nb = b + dir;
-    return {-dir * (B - 1) * sl, (nb < 0 ? NB - 1 : nb >= NB ? 1 - NB : dir) * sb};
-}
-WCL_D uint32_t at(const Geom &g, const Site &s, Step a, Step b = {0, 0})
-{
-    return (uint32_t)((s.blk + a.blk + b.blk) * g.Hb + ((s.lin + a.lin + b.lin) >> 1));
-}
-
 // V += i t X^dag for one plaquette.  LOWER: the one on the -nu side, whose
 // edges run U_nu(x+mu-nu)^dag, U_mu(x-nu)^dag, U_nu(x-nu).
 template <bool LOWER>
@@ -287,10 +266,7 @@ __global__ void __launch_bounds__(256) k_grad_link(Geom g, const void *u64, cons
     double gk = 0.0;
     if ((uint32_t)(lane & 31) < np) {
         const Site s = decompose(g, (int)h, p);
-        if (mu == 0 && p == 0) {
-            const uint32_t odd = (uint32_t)(s.x[1] + s.x[2] + s.x[3]) & 1u;
-            base[lane] = (uint32_t)((s.x[0] & ~1) + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3]))) | (odd << 31);
-        }
+        if (mu == 0 && p == 0) base[lane] = pair_base(g, s);
         const Step sm = step_of(g, s, mu, 1);
         const uint32_t hm = at(g, s, sm);
         const Mat U = link64(u64, mu, p, h, Vh);

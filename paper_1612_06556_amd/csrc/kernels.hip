@@ -1,6 +1,6 @@
-// kernels.hip -- layout conversion, gauge ingest, clover build and inversion,
-// the even/odd hopping kernel with its fused epilogues, precision conversion
-// and the BLAS-1 / reduction kernels of the solvers.
+// kernels.hip -- the even/odd hopping kernel with its fused epilogues, the
+// clover apply, precision conversion and the BLAS-1 / reduction kernels of the
+// solvers.
 //
 // The operator (Wilson-Clover, paper Sec. 1 and Sec. 2):
 //   D = T - kappa H,  (H psi)(x) = sum_mu (1 - g_mu) U_mu(x) psi(x+mu)
@@ -11,425 +11,6 @@
 #include "hop_dev.h"
 
 namespace wcl {
-
-// ---------------------------------------------------------------------------
-// Geometry helpers for the setup kernels (divisions are fine there).
-WCL_D void canon_coords(const Geom &g, int n, int x[4])
-{
-    x[0] = n % g.L[0]; n /= g.L[0];
-    x[1] = n % g.L[1]; n /= g.L[1];
-    x[2] = n % g.L[2];
-    x[3] = n / g.L[2];
-}
-
-WCL_D int coords_to_h(const Geom &g, const int x[4])
-{
-    int blk = 0, lin = 0;
-#pragma unroll
-    for (int mu = 0; mu < 4; mu++) {
-        const int b = x[mu] / g.B[mu];
-        blk += b * g.sb[mu];
-        lin += (x[mu] - b * g.B[mu]) * g.sl[mu];
-    }
-    return blk * g.Hb + (lin >> 1);
-}
-
-// ---------------------------------------------------------------------------
-// Gauge ingest: canonical U[V][4][3][3] complex128 -> internal link fields.
-__global__ void k_ingest_gauge(Geom g, const double2 *__restrict__ canon, void *u64, void *u32, void *u16)
-{
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    const int V = 2 * g.Vh;
-    if (n >= V) return;
-    int x[4];
-    canon_coords(g, n, x);
-    const int p = (x[0] + x[1] + x[2] + x[3]) & 1;
-    const size_t h = coords_to_h(g, x);
-    for (int mu = 0; mu < 4; mu++) {
-        cplx<double> u[9];
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            const double2 d = canon[((size_t)n * 4 + mu) * 9 + k];
-            u[k] = {d.x, d.y};
-        }
-        if (u64) store_link<double, double>(u64, mu, p, h, g.Vh, u);
-        if (u32) store_link<float, double>(u32, mu, p, h, g.Vh, u);
-        if (u16) store_link<__half, double>(u16, mu, p, h, g.Vh, u);
-    }
-}
-
-// Two-row (12-real) FP32 and FP16 copies of the FP64 links.
-__global__ void k_compress_links(Geom g, const void *u64, void *u32c, void *u16c, void *u32s)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 8 * g.Vh) return;
-    const int mp = i / g.Vh, h = i - mp * g.Vh;
-    cplx<double> u[9];
-    load_link<double, double>(u64, mp >> 1, mp & 1, h, g.Vh, u);
-    store_link<R12f, double>(u32c, mp >> 1, mp & 1, h, g.Vh, u);
-    store_link<R12h, double>(u16c, mp >> 1, mp & 1, h, g.Vh, u);
-    store_link_site<double>(u32s, mp >> 1, mp & 1, h, g.Vh, u);
-}
-
-hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, void *u32s, hipStream_t st)
-{
-    k_compress_links<<<(8 * g.Vh + 255) / 256, 256, 0, st>>>(g, u64, u32c, u16c, u32s);
-    return hipGetLastError();
-}
-
-// Largest |row2 - conj(row0 x row1)| over the FP64 links (per-workgroup maxima).
-// max that keeps a NaN (fmax would drop it)
-WCL_D double nanmax(double m, double d) { return (d > m || d != d) ? d : m; }
-
-__global__ void __launch_bounds__(256) k_su3_check(Geom g, const void *u64, double *partial)
-{
-    __shared__ double red[256];
-    double m = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 8 * g.Vh; i += gridDim.x * blockDim.x) {
-        const int mp = i / g.Vh, h = i - mp * g.Vh;
-        cplx<double> u[9], r[9];
-        load_link<double, double>(u64, mp >> 1, mp & 1, h, g.Vh, u);
-#pragma unroll
-        for (int k = 0; k < 9; k++) r[k] = u[k];
-        su3_third_row(r);
-#pragma unroll
-        for (int k = 6; k < 9; k++) m = nanmax(m, fmax(fabs(r[k].re - u[k].re), fabs(r[k].im - u[k].im)));
-        cplx<double> ip = {0.0, 0.0};
-        double n0 = 0.0, n1 = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const cplx<double> a = u[c], b = u[3 + c];
-            n0 += a.re * a.re + a.im * a.im;
-            n1 += b.re * b.re + b.im * b.im;
-            ip.re += a.re * b.re + a.im * b.im;
-            ip.im += a.re * b.im - a.im * b.re;
-        }
-        m = nanmax(m, fabs(n0 - 1.0));
-        m = nanmax(m, fabs(n1 - 1.0));
-        m = nanmax(m, sqrt(ip.re * ip.re + ip.im * ip.im));
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] = nanmax(red[threadIdx.x], red[threadIdx.x + o]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-hipError_t launch_su3_check(const Geom &g, const void *u64, double *partial, int nblocks, hipStream_t st)
-{
-    k_su3_check<<<nblocks, 256, 0, st>>>(g, u64, partial);
-    return hipGetLastError();
-}
-
-hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16,
-                               hipStream_t st)
-{
-    const int V = 2 * g.Vh;
-    k_ingest_gauge<<<(V + 127) / 128, 128, 0, st>>>(g, (const double2 *)canon, u64, u32, u16);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Clover term.  For each site, F_{mu nu} = (Q - Q^dag)/(8i) made traceless,
-// Q the sum of the four plaquette leaves in the mu-nu plane.  In the chiral
-// basis sum_{mu<nu} sigma_{mu nu} F_{mu nu} is block diagonal:
-//   chirality +: sum_k s_k (x) (E_k - B_k),   chirality -: sum_k s_k (x) (-E_k - B_k)
-// with E_k = F_{k t} and B = (F_yz, F_zx, F_xy), and s_k (x) G written out as
-// [[G_3, G_1 - i G_2], [G_1 + i G_2, -G_3]].
-struct M3 {
-    cplx<double> a[9];
-};
-
-WCL_D M3 m3_mul(const M3 &A, const M3 &B)
-{
-    M3 C;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            cplx<double> s = A.a[i * 3] * B.a[j];
-            s = cfma(A.a[i * 3 + 1], B.a[3 + j], s);
-            s = cfma(A.a[i * 3 + 2], B.a[6 + j], s);
-            C.a[i * 3 + j] = s;
-        }
-    return C;
-}
-
-WCL_D M3 m3_dag(const M3 &A)
-{
-    M3 C;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) C.a[i * 3 + j] = {A.a[j * 3 + i].re, -A.a[j * 3 + i].im};
-    return C;
-}
-
-// link U_mu at global coordinates x + d (periodic wrap)
-WCL_D M3 link_at(const Geom &g, const void *u64, const int x[4], const int d[4], int mu)
-{
-    int y[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) y[k] = (x[k] + d[k] + g.L[k]) % g.L[k];
-    const int p = (y[0] + y[1] + y[2] + y[3]) & 1;
-    M3 m;
-    load_link<double, double>(u64, mu, p, coords_to_h(g, y), g.Vh, m.a);
-    return m;
-}
-
-// Inverse of a Hermitian positive definite 6x6 by Cholesky: A = L L^dag,
-// A^-1 = W^dag W with W = L^-1.  Returns false on a non-positive pivot.
-WCL_D bool hpd_inverse6(const cplx<double> A[36], cplx<double> Ai[36])
-{
-    cplx<double> L[36];
-#pragma unroll
-    for (int k = 0; k < 36; k++) L[k] = {0.0, 0.0};
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < 6; j++) {
-        double d = A[j * 6 + j].re;
-#pragma unroll
-        for (int k = 0; k < j; k++) d -= L[j * 6 + k].re * L[j * 6 + k].re + L[j * 6 + k].im * L[j * 6 + k].im;
-        if (!(d > 0.0)) { ok = false; d = 1.0; }
-        const double ljj = sqrt(d);
-        L[j * 6 + j] = {ljj, 0.0};
-        const double inv = 1.0 / ljj;
-#pragma unroll
-        for (int i = j + 1; i < 6; i++) {
-            cplx<double> s = A[i * 6 + j];
-#pragma unroll
-            for (int k = 0; k < j; k++) s = s - L[i * 6 + k] * cplx<double>{L[j * 6 + k].re, -L[j * 6 + k].im};
-            L[i * 6 + j] = inv * s;
-        }
-    }
-    // W = L^-1 (lower triangular), forward substitution column by column
-    cplx<double> W[36];
-#pragma unroll
-    for (int k = 0; k < 36; k++) W[k] = {0.0, 0.0};
-#pragma unroll
-    for (int j = 0; j < 6; j++) {
-        W[j * 6 + j] = {1.0 / L[j * 6 + j].re, 0.0};
-#pragma unroll
-        for (int i = j + 1; i < 6; i++) {
-            cplx<double> s = {0.0, 0.0};
-#pragma unroll
-            for (int k = j; k < i; k++) s = cfma(L[i * 6 + k], W[k * 6 + j], s);
-            W[i * 6 + j] = (-1.0 / L[i * 6 + i].re) * s;
-        }
-    }
-    // Ai = W^dag W
-#pragma unroll
-    for (int i = 0; i < 6; i++)
-#pragma unroll
-        for (int j = 0; j < 6; j++) {
-            cplx<double> s = {0.0, 0.0};
-            const int k0 = i > j ? i : j;
-#pragma unroll
-            for (int k = k0; k < 6; k++) s = cjfma(W[k * 6 + i], W[k * 6 + j], s);
-            Ai[i * 6 + j] = s;
-        }
-    return ok;
-}
-
-WCL_D void pack_block(const cplx<double> A[36], double *out36)
-{
-#pragma unroll
-    for (int i = 0; i < 6; i++) out36[i] = A[i * 6 + i].re;
-    int k = 0;
-#pragma unroll
-    for (int i = 0; i < 6; i++)
-#pragma unroll
-        for (int j = i + 1; j < 6; j++) {
-            out36[6 + 2 * k] = A[i * 6 + j].re;
-            out36[7 + 2 * k] = A[i * 6 + j].im;
-            k++;
-        }
-}
-
-// One clover leaf of plane (mu, nu) at x (leaf 0: x -> x+mu -> x+mu+nu ->
-// x+nu; 1: x -> x+nu -> x-mu+nu -> x-mu; 2: x -> x-mu -> x-mu-nu -> x-nu;
-// 3: x -> x-nu -> x+mu-nu -> x+mu; each back to x).
-WCL_D M3 clover_leaf(const Geom &g, const void *u64, const int x[4], int mu, int nu, int leaf)
-{
-    int o[4] = {0, 0, 0, 0};
-    int pm[4] = {0, 0, 0, 0}, pn[4] = {0, 0, 0, 0}, mm[4] = {0, 0, 0, 0}, mn[4] = {0, 0, 0, 0};
-    int mmpn[4] = {0, 0, 0, 0}, mmmn[4] = {0, 0, 0, 0}, pmmn[4] = {0, 0, 0, 0};
-    pm[mu] = 1; pn[nu] = 1; mm[mu] = -1; mn[nu] = -1;
-    mmpn[mu] = -1; mmpn[nu] = 1;
-    mmmn[mu] = -1; mmmn[nu] = -1;
-    pmmn[mu] = 1; pmmn[nu] = -1;
-    if (leaf == 0)
-        return m3_mul(m3_mul(link_at(g, u64, x, o, mu), link_at(g, u64, x, pm, nu)),
-                      m3_mul(m3_dag(link_at(g, u64, x, pn, mu)), m3_dag(link_at(g, u64, x, o, nu))));
-    if (leaf == 1)
-        return m3_mul(m3_mul(link_at(g, u64, x, o, nu), m3_dag(link_at(g, u64, x, mmpn, mu))),
-                      m3_mul(m3_dag(link_at(g, u64, x, mm, nu)), link_at(g, u64, x, mm, mu)));
-    if (leaf == 2)
-        return m3_mul(m3_mul(m3_dag(link_at(g, u64, x, mm, mu)), m3_dag(link_at(g, u64, x, mmmn, nu))),
-                      m3_mul(link_at(g, u64, x, mmmn, mu), link_at(g, u64, x, mn, nu)));
-    return m3_mul(m3_mul(m3_dag(link_at(g, u64, x, mn, nu)), link_at(g, u64, x, mn, mu)),
-                  m3_mul(link_at(g, u64, x, pmmn, nu), m3_dag(link_at(g, u64, x, o, mu))));
-}
-
-// Clover setup in two passes.  Pass 1: a workgroup takes 64 sites of one
-// plane, each wave one of the four leaves; the leaves meet in LDS and the
-// first wave forms the traceless Hermitian F_{mu nu} = (Q - Q^dag)/(8i) - tr
-// (Q = leaf 0 + 1 + 2 + 3) and stores its upper triangle (F00, F11, F22,
-// Re/Im F01, F02, F12: 9 reals) in F[plane][9][2 Vh].  Planes: E_k = F_{k t}
-// (0..2), B_x = F_yz, -B_y = F_xz, B_z = F_xy (3..5).
-__global__ void __launch_bounds__(256) k_clover_fs(Geom g, const void *u64, double *F)
-{
-    __shared__ double lq[4][18][64];
-    const int n = 2 * g.Vh;
-    const int lane = threadIdx.x & 63, leaf = threadIdx.x >> 6;
-    const int idx = blockIdx.x * 64 + lane;
-    const int plane = blockIdx.y;
-    // (mu, nu) of the planes: (0,3) (1,3) (2,3) (1,2) (0,2) (0,1)
-    const int mu = plane < 3 ? plane : (plane == 3 ? 1 : 0);
-    const int nu = plane < 3 ? 3 : (plane == 5 ? 1 : 2);
-    if (idx < n) {
-        const int p = idx / g.Vh;
-        const Site s = decompose(g, idx - p * g.Vh, p);
-        const M3 l = clover_leaf(g, u64, s.x, mu, nu, leaf);
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            lq[leaf][2 * k][lane] = l.a[k].re;
-            lq[leaf][2 * k + 1][lane] = l.a[k].im;
-        }
-    }
-    __syncthreads();
-    if (leaf != 0 || idx >= n) return;
-    M3 Q;
-#pragma unroll
-    for (int k = 0; k < 9; k++) Q.a[k] = {lq[0][2 * k][lane], lq[0][2 * k + 1][lane]};
-#pragma unroll
-    for (int q = 1; q < 4; q++)
-#pragma unroll
-        for (int k = 0; k < 9; k++) Q.a[k] = Q.a[k] + cplx<double>{lq[q][2 * k][lane], lq[q][2 * k + 1][lane]};
-    M3 f;
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            const double wr = Q.a[i * 3 + j].re - Q.a[j * 3 + i].re;
-            const double wi = Q.a[i * 3 + j].im + Q.a[j * 3 + i].im;
-            f.a[i * 3 + j] = {wi * 0.125, -wr * 0.125};
-        }
-    const double tr = (f.a[0].re + f.a[4].re + f.a[8].re) / 3.0;
-    double *o = F + (size_t)plane * 9 * n + idx;
-    o[0] = f.a[0].re - tr;
-    o[(size_t)n] = f.a[4].re - tr;
-    o[2 * (size_t)n] = f.a[8].re - tr;
-    o[3 * (size_t)n] = f.a[1].re;
-    o[4 * (size_t)n] = f.a[1].im;
-    o[5 * (size_t)n] = f.a[2].re;
-    o[6 * (size_t)n] = f.a[2].im;
-    o[7 * (size_t)n] = f.a[5].re;
-    o[8 * (size_t)n] = f.a[5].im;
-}
-
-// Entry (a, b) of plane `plane` of the stored F (the lower triangle by
-// Hermiticity).
-WCL_D cplx<double> f_entry(const double *F, size_t n, int idx, int plane, int a, int b)
-{
-    const double *q = F + (size_t)plane * 9 * n + idx;
-    if (a == b) return {q[(size_t)a * n], 0.0};
-    const int lo = a < b ? a : b, hi = a < b ? b : a;
-    const int k = lo == 0 ? (hi == 1 ? 3 : 5) : 7;
-    const double re = q[(size_t)k * n], im = q[(size_t)(k + 1) * n];
-    return a < b ? cplx<double>{re, im} : cplx<double>{re, -im};
-}
-
-// Half (chirality block chi) of a packed clover site in storage S: FP64 and
-// FP32 blocks fill whole 16-byte words; FP16 block 0 ends and block 1 starts
-// in word 4, whose other half is carried in `keep`.
-template <typename S>
-WCL_D void store_clover_block(void *base, int p, uint32_t h, uint32_t Vh, int chi, const double c[36], uint2 &keep)
-{
-    if constexpr (sizeof(S) == 8) {
-#pragma unroll
-        for (uint32_t k = 0; k < 18; k++)
-            stf(base, (((uint32_t)p * 36 + 18 * chi + k) * Vh + h) * 16u, make_double2(c[2 * k], c[2 * k + 1]));
-    } else if constexpr (sizeof(S) == 4) {
-#pragma unroll
-        for (uint32_t k = 0; k < 9; k++)
-            stf(base, (((uint32_t)p * 18 + 9 * chi + k) * Vh + h) * 16u,
-                make_float4((float)c[4 * k], (float)c[4 * k + 1], (float)c[4 * k + 2], (float)c[4 * k + 3]));
-    } else {
-        uint32_t w[18];
-#pragma unroll
-        for (int k = 0; k < 18; k++) w[k] = f22h((float)c[2 * k], (float)c[2 * k + 1]);
-        if (chi == 0) {
-#pragma unroll
-            for (uint32_t k = 0; k < 4; k++)
-                stf(base, (((uint32_t)p * 9 + k) * Vh + h) * 16u, make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]));
-            keep = make_uint2(w[16], w[17]);
-        } else {
-            stf(base, (((uint32_t)p * 9 + 4) * Vh + h) * 16u, make_uint4(keep.x, keep.y, w[0], w[1]));
-#pragma unroll
-            for (uint32_t k = 0; k < 4; k++)
-                stf(base, (((uint32_t)p * 9 + 5 + k) * Vh + h) * 16u,
-                    make_uint4(w[2 + 4 * k], w[3 + 4 * k], w[4 + 4 * k], w[5 + 4 * k]));
-        }
-    }
-}
-
-// Pass 2: one thread per site builds T = 1 - c_sw kappa sigma.F one
-// chirality block at a time from the stored F, inverts it (FP64 Cholesky)
-// and writes both into every requested storage.
-__global__ void __launch_bounds__(64) k_clover_inv(Geom g, const double *F, double ck, void *t64, void *ti64,
-                                                   void *t32, void *ti32, void *t16, void *ti16, int *info)
-{
-    const size_t n = 2 * (size_t)g.Vh;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int)n) return;
-    const int p = idx / g.Vh;
-    const int h = idx - p * g.Vh;
-    bool ok = true;
-    uint2 keepT = make_uint2(0u, 0u), keepTi = make_uint2(0u, 0u);
-    for (int chi = 0; chi < 2; chi++) {
-        const double se = chi == 0 ? 1.0 : -1.0;
-        // G_k = se * E_k - B_k
-        cplx<double> A[36];
-#pragma unroll
-        for (int a = 0; a < 3; a++)
-#pragma unroll
-            for (int b = 0; b < 3; b++) {
-                const cplx<double> G1 = se * f_entry(F, n, idx, 0, a, b) - f_entry(F, n, idx, 3, a, b);
-                const cplx<double> G2 = se * f_entry(F, n, idx, 1, a, b) + f_entry(F, n, idx, 4, a, b);
-                const cplx<double> G3 = se * f_entry(F, n, idx, 2, a, b) - f_entry(F, n, idx, 5, a, b);
-                const cplx<double> iG2 = {-G2.im, G2.re};
-                const double id = (a == b) ? 1.0 : 0.0;
-                A[a * 6 + b] = cplx<double>{id, 0.0} - ck * G3;
-                A[(3 + a) * 6 + 3 + b] = cplx<double>{id, 0.0} + ck * G3;
-                A[a * 6 + 3 + b] = -ck * (G1 - iG2);
-                A[(3 + a) * 6 + b] = -ck * (G1 + iG2);
-            }
-        double packed[36];
-        pack_block(A, packed);
-        if (t64) store_clover_block<double>(t64, p, h, g.Vh, chi, packed, keepT);
-        if (t32) store_clover_block<float>(t32, p, h, g.Vh, chi, packed, keepT);
-        if (t16) store_clover_block<__half>(t16, p, h, g.Vh, chi, packed, keepT);
-        cplx<double> Ai[36];
-        ok = hpd_inverse6(A, Ai) && ok;
-        pack_block(Ai, packed);
-        if (ti64) store_clover_block<double>(ti64, p, h, g.Vh, chi, packed, keepTi);
-        if (ti32) store_clover_block<float>(ti32, p, h, g.Vh, chi, packed, keepTi);
-        if (ti16) store_clover_block<__half>(ti16, p, h, g.Vh, chi, packed, keepTi);
-    }
-    if (!ok) atomicAdd(info, 1);
-}
-
-hipError_t launch_clover_build(const Geom &g, const void *u64, double ck, void *t64, void *ti64, void *t32,
-                               void *ti32, void *t16, void *ti16, int *info, double *fbuf, hipStream_t st)
-{
-    const int n = 2 * g.Vh;
-    k_clover_fs<<<dim3((n + 63) / 64, 6), 256, 0, st>>>(g, u64, fbuf);
-    k_clover_inv<<<(n + 63) / 64, 64, 0, st>>>(g, fbuf, ck, t64, ti64, t32, ti32, t16, ti16, info);
-    return hipGetLastError();
-}
 
 // NT: links and clover loaded non-temporally (a single right-hand side reads
 // them once per launch).  Off by default: repeated applications in a solver

@@ -128,6 +128,37 @@ WCL_D int neighbour(const Geom &g, const Site &s, int mu, int dir)
     return blk * g.Hb + (lin >> 1);
 }
 
+// Change of the in-tile and tile index of a step in one direction; steps in
+// different directions add up.
+struct Step {
+    int lin, blk;
+};
+WCL_D Step step_of(const Geom &g, const Site &s, int mu, int dir)
+{
+    int l = 0, b = 0, B = 1, NB = 1, sl = 0, sb = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        if (k == mu) { l = s.l[k]; b = s.b[k]; B = g.B[k]; NB = g.NB[k]; sl = g.sl[k]; sb = g.sb[k]; }
+    const int lc = l + dir;
+    if (lc >= 0 && lc < B) return {dir * sl, 0};
+    const int nb = b + dir;
+    return {-dir * (B - 1) * sl, (nb < 0 ? NB - 1 : nb >= NB ? 1 - NB : dir) * sb};
+}
+WCL_D uint32_t at(const Geom &g, const Site &s, Step a, Step b = {0, 0})
+{
+    return (uint32_t)((s.blk + a.blk + b.blk) * g.Hb + ((s.lin + a.lin + b.lin) >> 1));
+}
+
+// The half index enumerates pairs of x-neighbours: the sites of both parities
+// with one h are x = 2j and 2j + 1 of one row, contiguous in canonical order.
+// The canonical index of the x-even one, its parity in bit 31.
+WCL_D uint32_t pair_base(const Geom &g, const Site &s)
+{
+    const uint32_t odd = (uint32_t)(s.x[1] + s.x[2] + s.x[3]) & 1u;
+    return (uint32_t)((s.x[0] & ~1) + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3]))) | (odd << 31);
+}
+WCL_D uint32_t pair_base(const Geom &g, int h) { return pair_base(g, decompose(g, h, 0)); }
+
 // ---------------------------------------------------------------------------
 // Complex arithmetic.
 template <typename R>

@@ -113,9 +113,11 @@ struct CanonLaunch {
     LaunchEvents ev;
 };
 hipError_t launch_canon(const CanonLaunch &L, hipStream_t st);
-// Canonical U [V][4][3][3] -> internal link fields (any null pointer skipped).
-hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16,
-                               hipStream_t st);
+// Canonical U [V][4][3][3] -> internal link fields; with c32 (P32C), c16 (P16C)
+// and s32 (per site) also the two-row copies, and *defect = max of it and the
+// bits of the largest SU(3) defect (launch_su3_check) if above tol.
+hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16, void *c32, void *c16,
+                               void *s32, double tol, unsigned long long *defect, hipStream_t st);
 // FP64 links -> two-row FP32 (P32C) and FP16 (P16C) link fields, and the
 // per-site copy of the two-row FP32 links read by the fused Schwarz kernel.
 hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, void *u32s,
