@@ -303,8 +303,7 @@ __global__ void __launch_bounds__(256) k_grad_link(Geom g, const void *u64, cons
         for (int k = 0; k < 9; k++)
             lds[mu * ROW + lane * 9 + k] = make_double2(kappa * (G.a[k].re + W.a[k].re), kappa * (G.a[k].im + W.a[k].im));
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) gk += __shfl_xor(gk, o, 64);
+    gk = wave_sum(gk);
     if (lane == 0) red[mu] = gk;
     __syncthreads();
     if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);

@@ -24,8 +24,7 @@ __global__ void __launch_bounds__(256) k_hop_dot(HopArgs a, const void *dotw, do
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
     for (int k = 0; k < 3; k++) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) d[k] += __shfl_xor(d[k], o, 64);
+        d[k] = wave_sum(d[k]);
         if (lane == 0) red[k * 16 + wid] = d[k];
     }
     __syncthreads();

@@ -355,15 +355,7 @@ hipError_t launch_convert(int ip, int op, size_t nsites, size_t Vi, size_t Vo, c
 }
 
 // ---------------------------------------------------------------------------
-// Reductions: wavefront butterfly (DPP / ds_swizzle through __shfl_xor), then
-// one value per wave through LDS.
-WCL_D double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
+// Reductions: wave sums, then one value per wave through LDS.
 template <int NV>
 WCL_D void block_sum(double v[NV], double *lds /* [NV][16] */)
 {

@@ -179,29 +179,21 @@ WCL_D void ras_hop_finish(const void *links, const void *clov, int q, const RasS
     }
 }
 
+// Workgroup sums (at most 16 waves) in every thread: each wave's sum through
+// LDS, then every wave adds all of them in the same order (one barrier).  The
+// caller's next barrier but one comes before the next call.
 template <int NV>
 WCL_D void block_allreduce(double v[NV], double *red)
 {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
 #pragma unroll
     for (int k = 0; k < NV; k++) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+        v[k] = wave_sum(v[k]);
         if (lane == 0) red[k * 16 + wid] = v[k];
     }
     __syncthreads();
-    if (wid == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; k++) {
-            double t = lane < nw ? red[k * 16 + lane] : 0.0;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-            if (lane == 0) red[NV * 16 + k] = t;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; k++) v[k] = red[NV * 16 + k];
+    for (int k = 0; k < NV; k++) v[k] = row_sum((lane & 15) < nw ? red[k * 16 + (lane & 15)] : 0.0);
 }
 
 // JAC: block Jacobi steps (alpha = 1, no reductions) instead of minimal

@@ -786,6 +786,36 @@ WCL_D void su3_dag_mul(const cplx<R> u[9], const cplx<R> h[6], cplx<R> o[6])
         }
 }
 
+// Sum over the wave, in every lane: the xor butterfly 32, 16, 8, 4, 2, 1 on the
+// VALU (lane swaps, then rotations inside rows of 16, which are xor steps once
+// the lanes hold sums of that period), not through LDS.  All 64 lanes active.
+template <int CTRL>
+WCL_D double dpp_add(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false);
+    return v + __hiloint2double(hi, lo);
+}
+WCL_D double row_sum(double v)   // over the lane's row of 16
+{
+    v = dpp_add<0x128>(v);   // row_ror:8, 4, 2, 1
+    v = dpp_add<0x124>(v);
+    v = dpp_add<0x122>(v);
+    return dpp_add<0x121>(v);
+}
+WCL_D double wave_sum(double v)
+{
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
+    const uint32_t lo2 = (uint32_t)__double2loint(v), hi2 = (uint32_t)__double2hiint(v);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false);
+    const auto h16 = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
+    v = __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
+    return row_sum(v);
+}
+
 // The thread's index in its workgroup as a value the compiler cannot prove
 // loop-invariant: per-thread arithmetic of a code path that runs inside a
 // long kernel loop (the persistent solver's phases) stays in that path
