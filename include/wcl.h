@@ -98,10 +98,7 @@ int wcl_set_params(wcl_ctx *ctx, double kappa, double csw);
  * rows).  An SU(3) matrix is fixed by its first two rows (row 2 =
  * conj(row0 x row1)), so the hopping and Schwarz kernels read 48 (FP32) or
  * 24 (FP16) bytes per link instead of 72 / 36 and rebuild the third row in
- * registers; FP64 work always uses the full links.  The context then holds
- * the FP32 two-row links twice (field-major for the hopping kernels, per site
- * for the Schwarz block solves: 384 bytes a site each) and the FP16 ones
- * once.  Enabling
+ * registers; FP64 work always uses the full links.  Enabling
  * checks, on the current and every later wcl_set_gauge, that each link is
  * SU(3) to 1e-7 (row norms, row orthogonality, row 2 against the cross
  * product); otherwise the call fails with WCL_EINVAL and, in wcl_set_gauge,
@@ -158,7 +155,10 @@ int wcl_apply_op(wcl_ctx *ctx, int op, const double *in_dev, double *out_dev, in
  * the colours before it (the paper leaves the Schwarz variant open, Sec. 2).
  * The cores are the layout's tiles unless wcl_set_ras_cores set others.
  * Tile cores with MR or Jacobi and an extended block of at most 648 sites
- * per parity run as one fused kernel (block vectors in LDS); every other
+ * per parity run as one fused kernel (block vectors in LDS; the first
+ * application on a new gauge field, clover term or overlap parity copies the
+ * tier's links and clover inverse into the kernel's order, in the context's
+ * workspace: as many bytes as those fields); every other
  * setting runs the block solves with the block vectors in device memory
  * (the context allocates them here: 8 or 4 FP32 fields of the extended
  * blocks' size, with BiCGStab or not).  WCL_EINVAL when the extended block

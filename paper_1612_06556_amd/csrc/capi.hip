@@ -72,7 +72,8 @@ struct wcl_ctx {
     int device = 0;
     void *U64 = nullptr, *U32 = nullptr, *U16 = nullptr;
     void *U32c = nullptr, *U16c = nullptr;  // two-row links (built when compression is on)
-    void *U32s = nullptr;                   // per-site copy of U32c (the fused Schwarz kernel's)
+    int gauge_epoch = 0, params_epoch = 0;  // successful-or-not wcl_set_gauge / wcl_set_params calls
+    struct RasCopy { int o = -1, gauge = -1, params = -1; } ras_copy[4];   // see ensure_ras_copies
     int compress = 0;                       // FP32/FP16 tiers read the two-row links
     void *T64 = nullptr, *Ti64 = nullptr, *T32 = nullptr, *Ti32 = nullptr, *T16 = nullptr, *Ti16 = nullptr;
     Flags *flags = nullptr, *flags_host = nullptr;   // device, pinned host
@@ -276,8 +277,9 @@ bool ras_generic(const wcl_ctx *c)
 }
 
 int ensure_gras(wcl_ctx *c);
+int ensure_ras_copies(wcl_ctx *c, int lprec, const void **links, const void **clov_inv);
 
-int run_ras(wcl_ctx *c, const RasLaunch &R)
+int run_ras(wcl_ctx *c, RasLaunch R)
 {
     double b = 0, f = 0;
     if (ras_generic(c)) {
@@ -285,6 +287,7 @@ int run_ras(wcl_ctx *c, const RasLaunch &R)
         if (c->prof) gras_work(c->gras, R, c->ras_solver, &b, &f);
         return profiled(c, WCL_K_RAS, b, f, [&] { return launch_gras(c->gras, R, c->ras_solver, c->st); });
     }
+    CHK(ensure_ras_copies(c, R.link_prec, &R.links_ras, &R.clov_inv_ras));
     if (c->prof) ras_work(R, &b, &f);
     return profiled_ev(c, WCL_K_RAS, b, f, [&](const LaunchEvents &ev) {
         RasLaunch T = R;
@@ -539,8 +542,10 @@ enum Slot {
     S_CLOVF,
     // persistent inner solve: per-workgroup partial sums, barrier counters + time-out flag
     S_PPART, S_PBAR,
+    // operator copies of the fused Schwarz kernel: links and clover inverse of each tier
+    S_RASL, S_RASC = S_RASL + 4,
     // bench copies start here
-    S_BENCH = 64,
+    S_BENCH = 96,
 };
 
 // Tables and block fields of the global-memory Schwarz path for the current
@@ -572,6 +577,35 @@ int ensure_gras(wcl_ctx *c)
     return WCL_OK;
 }
 
+// The fused Schwarz kernel's copies of the links and clover inverse in its
+// block order, for the tier's storage code lprec: rebuilt (two launches) when
+// the gauge field, the clover term or the parity of the overlap changed since,
+// so the work is that of the first application on a new field.
+int ensure_ras_copies(wcl_ctx *c, int lprec, const void **links, const void **clov_inv)
+{
+    const int k = lprec == P32 ? 0 : lprec == P16 ? 1 : lprec == P32C ? 2 : 3, o = c->ras_overlap & 1;
+    const size_t Vh = c->Vh;
+    const size_t lb = lprec == P32 || lprec == P16 ? link_bytes(prec_bytes(lprec), Vh) : link_bytes_c(lprec, Vh);
+    void *l, *t;
+    CHK(wsget(c, S_RASL + k, lb, &l));
+    CHK(wsget(c, S_RASC + k, clover_bytes(prec_bytes(lprec), Vh), &t));
+    wcl_ctx::RasCopy &r = c->ras_copy[k];
+    if (r.o != o || r.gauge != c->gauge_epoch) {
+        r.gauge = -1;
+        HIPCHK(launch_ras_links(c->g, lprec, o, links_for(c, lprec), l, c->st));
+        r.gauge = c->gauge_epoch;
+    }
+    if (r.o != o || r.params != c->params_epoch) {
+        r.params = -1;
+        HIPCHK(launch_ras_clover(c->g, lprec, o, clovinv_for(c, lprec), t, c->st));
+        r.params = c->params_epoch;
+    }
+    r.o = o;
+    *links = l;
+    *clov_inv = t;
+    return WCL_OK;
+}
+
 // Largest SU(3) defect accepted for two-row link storage (the FP32 tier's
 // own rounding is 6e-8).
 constexpr double SU3_TOL = 1e-7;
@@ -589,7 +623,6 @@ int alloc_compressed(wcl_ctx *c)
     // each copy on its own: a failed allocation leaves the others for the next call
     if (!c->U32c) CHK(alloc(&c->U32c, link_bytes_c(P32C, Vh)));
     if (!c->U16c) CHK(alloc(&c->U16c, link_bytes_c(P16C, Vh)));
-    if (!c->U32s) CHK(alloc(&c->U32s, link_bytes_c(P32C, Vh)));
     return WCL_OK;
 }
 
@@ -609,7 +642,7 @@ int build_compressed(wcl_ctx *c)
     for (double d : h)
         if (d > m || d != d) m = d;
     if (!(m <= SU3_TOL)) return su3_failure(m);
-    HIPCHK(launch_compress_links(c->g, c->U64, c->U32c, c->U16c, c->U32s, c->st));
+    HIPCHK(launch_compress_links(c->g, c->U64, c->U32c, c->U16c, c->st));
     return WCL_OK;
 }
 
@@ -694,7 +727,7 @@ int wcl_destroy(wcl_ctx *c)
 {
     if (!c) return WCL_OK;
     (void)hipStreamSynchronize(c->st);
-    void *ptrs[] = {c->U64, c->U32, c->U16, c->U32c, c->U16c, c->U32s, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16, c->flags,
+    void *ptrs[] = {c->U64, c->U32, c->U16, c->U32c, c->U16c, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16, c->flags,
                     c->partials, c->sc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -722,8 +755,9 @@ int wcl_set_gauge(wcl_ctx *c, const double *U)
     if (!c->U16) CHK(alloc(&c->U16, link_bytes(2, Vh)));
     c->have_gauge = false;
     c->have_params = false;
+    c->gauge_epoch++;
     if (c->compress) CHK(alloc_compressed(c));
-    HIPCHK(launch_ingest_gauge(c->g, U, c->U64, c->U32, c->U16, c->compress ? c->U32c : nullptr, c->U16c, c->U32s, SU3_TOL,
+    HIPCHK(launch_ingest_gauge(c->g, U, c->U64, c->U32, c->U16, c->compress ? c->U32c : nullptr, c->U16c, SU3_TOL,
                                &c->flags->defect, c->st));
     if (c->compress) {
         HIPCHK(hipMemcpyAsync(c->flags_host, c->flags, sizeof(Flags), hipMemcpyDeviceToHost, c->st));
@@ -767,6 +801,7 @@ int wcl_set_params(wcl_ctx *c, double kappa, double csw)
         if (!*cl[i]) CHK(alloc(cl[i], clover_bytes(cl_bytes[i], Vh)));
     c->kappa = kappa;
     c->csw = csw;
+    c->params_epoch++;
     void *fbuf;
     CHK(wsget(c, S_CLOVF, (size_t)6 * 9 * 2 * c->Vh * sizeof(double), &fbuf));
     HIPCHK(launch_clover_build(c->g, c->U64, csw * kappa, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16,
@@ -923,7 +958,6 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             R.in = a;
             R.out = b;
             R.links = links_for(c, R.link_prec);
-            R.links_site = c->U32s;
             R.clov_inv = clovinv_for(c, lp);
             R.kappa2 = (float)(c->kappa * c->kappa);
             R.sc = nullptr;
@@ -1066,7 +1100,6 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
         R.jacobi = c->ras_solver == WCL_RAS_JACOBI;
         R.link_prec = eff_lprec(c, lp);
         R.links = links_for(c, R.link_prec);
-        R.links_site = c->U32s;
         R.clov_inv = clovinv_for(c, lp);
         R.kappa2 = (float)(c->kappa * c->kappa);
         R.sc = sc;
@@ -1155,10 +1188,10 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
         P.link_prec = eff_lprec(c, cfg.lprec);
         P.vec_prec = vp;
         P.links = links_for(c, P.link_prec);
-        P.links_site = c->U32s;
         P.clov_inv = clovinv_for(c, cfg.lprec);
         P.kappa2 = c->kappa * c->kappa;
         P.use_ras = cfg.ras ? 1 : 0;
+        if (cfg.ras) CHK(ensure_ras_copies(c, P.link_prec, &P.links_ras, &P.clov_inv_ras));
         P.overlap = c->ras_overlap;
         P.iters = c->ras_iters;
         P.jacobi = c->ras_solver == WCL_RAS_JACOBI;
@@ -1596,6 +1629,11 @@ extern "C" int wcl_solve(wcl_ctx *c, const double *b, double *x, int nrhs, const
     if (o.persistent && o.use_ras && (ras_generic(c) || c->ras_mult || c->ras_solver != WCL_RAS_MR))
         return fail(WCL_EINVAL, "the persistent inner solve runs the additive Schwarz with minimal-residual "
                                 "blocks of the fused kernel (tile cores, at most 648 sites per parity)");
+    if (o.use_ras && inner && !ras_generic(c)) {
+        // before the inner iteration may be captured
+        const void *l, *t;
+        CHK(ensure_ras_copies(c, eff_lprec(c, o.inner_prec), &l, &t));
+    }
     const int n = nrhs;
     CHK(ensure_batch(c, n));
     SolveWs w;

@@ -449,7 +449,7 @@ hipError_t launch_persist(const PersistLaunch &L, hipStream_t st)
             ne *= L.g->B[mu] + 2 * L.overlap;
         }
         if (ne / 2 > 648 || L.jacobi) return hipErrorInvalidValue;
-        if (L.link_prec == P32C && !L.links_site) return hipErrorInvalidValue;
+        if (!L.links_ras || !L.clov_inv_ras) return hipErrorInvalidValue;
         for (int half = 0; half < 2; half++) {
             RasArgs &r = a.ra[half];
             r.g = *L.g;
@@ -457,8 +457,8 @@ hipError_t launch_persist(const PersistLaunch &L, hipStream_t st)
             r.iters = L.iters;
             r.in = half ? L.s : L.p;
             r.out = half ? L.sh : L.ph;
-            r.links = L.link_prec == P32C ? L.links_site : L.links;
-            r.clov_inv = L.clov_inv;
+            r.links = L.links_ras;
+            r.clov_inv = L.clov_inv_ras;
             r.kappa2 = (float)L.kappa2;
             r.sc = nullptr;
             r.nrhs = L.nrhs;

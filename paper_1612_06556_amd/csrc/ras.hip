@@ -14,7 +14,8 @@
 // even half) live in LDS as FP32 (2 x 12 x 648 complex = 124 KB for a 4^4 core
 // with overlap 1); the iterate z, the residual and the operator output stay in
 // registers of the thread that owns the site; links and clover inverse stream
-// from L2 / the Infinity Cache on every iteration.
+// from L2 / the Infinity Cache on every iteration, from copies in the block
+// order (ras_dev.h), whose 128-byte lines the blocks use whole.
 #include "ras_dev.h"
 
 namespace wcl {
@@ -34,6 +35,79 @@ __global__ void __launch_bounds__(MAXNE == 648 ? 704 : 128) k_ras(RasArgs a)
     if (a.sc && a.sc[rhs].done) return;
     __shared__ RasLds<MAXNE> lds;
     ras_block<SL, MAXNE, JAC, SV>(a, blk, rhs, lds);
+}
+
+// Copies of the links and the clover inverse in the block order: thread = block
+// index of one parity, blockIdx.y = parity + 2 * (direction, or half of the
+// clover words).  Writes whole lines, reads the lines of the field order.
+WCL_D uint32_t ras_source(const Geom &g, int o, uint32_t i, int p)
+{
+    const uint32_t j = i & 7u;
+    uint32_t c = i >> 3;
+    const int b1 = j & 1, b2 = (j >> 1) & 1, b3 = (int)(j >> 2), b0 = (p + b1 + b2 + b3) & 1;
+    const int b[4] = {b0, b1, b2, b3};
+    int blk = 0, lin = 0;
+#pragma unroll
+    for (int mu = 0; mu < 4; mu++) {
+        const int Lh = g.L[mu] >> 1;
+        const int cc = (int)(c % Lh);
+        c /= Lh;
+        int x = 2 * cc + b[mu] - o;
+        if (x < 0) x += g.L[mu];
+        const int t = x / g.B[mu];
+        blk += t * g.sb[mu];
+        lin += (x - t * g.B[mu]) * g.sl[mu];
+    }
+    return (uint32_t)(blk * g.Hb + (lin >> 1));
+}
+
+template <typename SL>
+__global__ void __launch_bounds__(256) k_ras_links(Geom g, int o, const void *src, void *dst)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= (uint32_t)g.Vh) return;
+    const int p = blockIdx.y & 1, mu = blockIdx.y >> 1;
+    LinkRaw<SL> r;
+    load_link_raw<SL>(src, mu, p, ras_source(g, o, i, p), g.Vh, r);
+    store_link_raw<SL>(dst, mu, p, i, g.Vh, r);
+}
+
+template <int WORDS>
+__global__ void __launch_bounds__(256) k_ras_clover(Geom g, int o, const void *src, void *dst)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, Vh = g.Vh;
+    if (i >= Vh) return;
+    const uint32_t p = blockIdx.y & 1, k0 = (blockIdx.y >> 1) * 9;   // 9 words of 16 bytes a thread
+    const uint32_t h = ras_source(g, o, i, (int)p);
+    uint4 v[9];
+#pragma unroll
+    for (uint32_t k = 0; k < 9; k++) v[k] = ldf<uint4>(src, ((p * WORDS + k0 + k) * Vh + h) * 16u);
+#pragma unroll
+    for (uint32_t k = 0; k < 9; k++) stf(dst, ((p * WORDS + k0 + k) * Vh + i) * 16u, v[k]);
+}
+
+hipError_t launch_ras_links(const Geom &g, int prec, int overlap, const void *src, void *dst, hipStream_t st)
+{
+    const dim3 grid((g.Vh + 255) / 256, 8), block(256);
+    const int o = overlap & 1;
+    switch (prec) {
+    case P32: k_ras_links<float><<<grid, block, 0, st>>>(g, o, src, dst); break;
+    case P16: k_ras_links<__half><<<grid, block, 0, st>>>(g, o, src, dst); break;
+    case P32C: k_ras_links<R12f><<<grid, block, 0, st>>>(g, o, src, dst); break;
+    case P16C: k_ras_links<R12h><<<grid, block, 0, st>>>(g, o, src, dst); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_ras_clover(const Geom &g, int prec, int overlap, const void *src, void *dst, hipStream_t st)
+{
+    const int o = overlap & 1;
+    const unsigned n = (g.Vh + 255) / 256;
+    if (prec == P32 || prec == P32C) k_ras_clover<18><<<dim3(n, 4), 256, 0, st>>>(g, o, src, dst);
+    else if (prec == P16 || prec == P16C) k_ras_clover<9><<<dim3(n, 2), 256, 0, st>>>(g, o, src, dst);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 int ras_threads(const Geom &g, int overlap)
@@ -85,10 +159,9 @@ hipError_t launch_ras(const RasLaunch &L, hipStream_t st)
     a.iters = L.iters;
     a.in = L.in;
     a.out = L.out;
-    // the two-row FP32 links are read from their per-site copy
-    if (L.link_prec == P32C && !L.links_site) return hipErrorInvalidValue;
-    a.links = L.link_prec == P32C ? L.links_site : L.links;
-    a.clov_inv = L.clov_inv;
+    if (!L.links_ras || !L.clov_inv_ras) return hipErrorInvalidValue;
+    a.links = L.links_ras;
+    a.clov_inv = L.clov_inv_ras;
     a.kappa2 = L.kappa2;
     a.sc = L.sc;
     a.nrhs = L.nrhs;

@@ -6,7 +6,7 @@
 namespace wcl {
 
 // Two-row (12-real) FP32 and FP16 copies of the FP64 links.
-__global__ void k_compress_links(Geom g, const void *u64, void *u32c, void *u16c, void *u32s)
+__global__ void k_compress_links(Geom g, const void *u64, void *u32c, void *u16c)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 8 * g.Vh) return;
@@ -15,12 +15,11 @@ __global__ void k_compress_links(Geom g, const void *u64, void *u32c, void *u16c
     load_link<double, double>(u64, mp >> 1, mp & 1, h, g.Vh, u);
     store_link<R12f, double>(u32c, mp >> 1, mp & 1, h, g.Vh, u);
     store_link<R12h, double>(u16c, mp >> 1, mp & 1, h, g.Vh, u);
-    store_link_site<double>(u32s, mp >> 1, mp & 1, h, g.Vh, u);
 }
 
-hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, void *u32s, hipStream_t st)
+hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, hipStream_t st)
 {
-    k_compress_links<<<(8 * g.Vh + 255) / 256, 256, 0, st>>>(g, u64, u32c, u16c, u32s);
+    k_compress_links<<<(8 * g.Vh + 255) / 256, 256, 0, st>>>(g, u64, u32c, u16c);
     return hipGetLastError();
 }
 
@@ -81,14 +80,14 @@ hipError_t launch_su3_check(const Geom &g, const void *u64, double *partial, int
 // ---------------------------------------------------------------------------
 // Gauge ingest: canonical U[V][4][3][3] complex128 to every internal copy in
 // one pass.  A workgroup takes 32 pairs of x-neighbours (1152 contiguous bytes
-// a pair) through LDS, each wave one direction.  Two-row copies (c32, c16,
-// s32; may be null) come with the SU(3) check: *defect (0 before) receives the
+// a pair) through LDS, each wave one direction.  Two-row copies (c32, c16;
+// may be null) come with the SU(3) check: *defect (0 before) receives the
 // bits of the largest defect above `tol` (non-negative doubles, NaN above all,
 // order as their bits).  Bound by HBM: U once in, the copies out: 165 us at
 // 24^3x32 with two-row copies (913 MB, 5.5 TB/s; 362 us as three passes, the first
 // with 576-byte strides).
 __global__ void __launch_bounds__(256) k_ingest_gauge(Geom g, const double2 *__restrict__ canon, void *u64, void *u32,
-                                                      void *u16, void *c32, void *c16, void *s32, double tol,
+                                                      void *u16, void *c32, void *c16, double tol,
                                                       unsigned long long *defect)
 {
     constexpr int ROW = 64 * 9 + 1;   // 16-byte units of one direction
@@ -126,16 +125,15 @@ __global__ void __launch_bounds__(256) k_ingest_gauge(Geom g, const double2 *__r
             m = su3_defect(u);
             store_link<R12f, double>(c32, mu, p, h, Vh, u);
             store_link<R12h, double>(c16, mu, p, h, Vh, u);
-            store_link_site<double>(s32, mu, p, h, Vh, u);
         }
     }
     if (!(m <= tol)) atomicMax(defect, (unsigned long long)__double_as_longlong(m));
 }
 
 hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16, void *c32, void *c16,
-                               void *s32, double tol, unsigned long long *defect, hipStream_t st)
+                               double tol, unsigned long long *defect, hipStream_t st)
 {
-    k_ingest_gauge<<<(g.Vh + 31) / 32, 256, 0, st>>>(g, (const double2 *)canon, u64, u32, u16, c32, c16, s32, tol, defect);
+    k_ingest_gauge<<<(g.Vh + 31) / 32, 256, 0, st>>>(g, (const double2 *)canon, u64, u32, u16, c32, c16, tol, defect);
     return hipGetLastError();
 }
 

@@ -458,7 +458,6 @@ WCL_D T ldb(__amdgpu_buffer_rsrc_t rs, uint32_t off)
     return r;
 }
 
-// R12f: from the per-site copy (store_link_site).
 template <typename S>
 WCL_D void load_link_raw_or_zero(__amdgpu_buffer_rsrc_t rs, int mu, int p, uint32_t h, bool in, uint32_t Vh,
                                  LinkRaw<S> &r)
@@ -468,10 +467,8 @@ WCL_D void load_link_raw_or_zero(__amdgpu_buffer_rsrc_t rs, int mu, int p, uint3
     const uint32_t mp = (uint32_t)(mu * 2 + p);
     const uint32_t o16 = in ? h * 16u : OUT, o8 = in ? h * 8u : OUT, o4 = in ? h * 4u : OUT;
     if constexpr (std::is_same<S, R12f>::value) {
-        // the per-site copy (store_link_site)
-        const uint32_t o48 = in ? (mp * Vh + h) * 48u : OUT;
 #pragma unroll
-        for (uint32_t k = 0; k < 3; k++) r.v[k] = ldb<float4>(rs, o48 + k * 16u);
+        for (uint32_t k = 0; k < 3; k++) r.v[k] = ldb<float4>(rs, (mp * 3 + k) * Vh * 16u + o16);
     } else if constexpr (std::is_same<S, R12h>::value) {
         r.v = ldb<uint4>(rs, mp * Vh * 16u + o16);
         r.w = ldb<uint2>(rs, 8u * Vh * 16u + mp * Vh * 8u + o8);
@@ -486,18 +483,27 @@ WCL_D void load_link_raw_or_zero(__amdgpu_buffer_rsrc_t rs, int mu, int p, uint3
     }
 }
 
-// Per-site copy of the two-row FP32 links, [mu][parity][Vh][12 reals] (48
-// contiguous bytes a link): the fused Schwarz kernel gathers the links of
-// scattered block sites, and one link then spans one or two cache lines
-// instead of three partly used ones.
-template <typename R>
-WCL_D void store_link_site(void *base, int mu, int p, uint32_t h, uint32_t Vh, const cplx<R> u[9])
+// A link as loaded, written back to another place of the same layout.
+template <typename S>
+WCL_D void store_link_raw(void *base, int mu, int p, uint32_t h, uint32_t Vh, const LinkRaw<S> &r)
 {
     const uint32_t mp = (uint32_t)(mu * 2 + p);
+    if constexpr (std::is_same<S, R12f>::value) {
 #pragma unroll
-    for (uint32_t k = 0; k < 3; k++)
-        stf(base, (mp * Vh + h) * 48u + k * 16u,
-            make_float4((float)u[2 * k].re, (float)u[2 * k].im, (float)u[2 * k + 1].re, (float)u[2 * k + 1].im));
+        for (uint32_t k = 0; k < 3; k++) stf(base, ((mp * 3 + k) * Vh + h) * 16u, r.v[k]);
+    } else if constexpr (std::is_same<S, R12h>::value) {
+        stf(base, (mp * Vh + h) * 16u, r.v);
+        stf(base, 8u * Vh * 16u + (mp * Vh + h) * 8u, r.w);
+    } else if constexpr (sizeof(S) == 4) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) stf(base, ((mp * 4 + k) * Vh + h) * 16u, r.v[k]);
+        stf(base, 32u * Vh * 16u + (mp * Vh + h) * 8u, r.w);
+    } else {
+        static_assert(sizeof(S) == 2, "FP32 and FP16 links only");
+#pragma unroll
+        for (uint32_t k = 0; k < 2; k++) stf(base, ((mp * 2 + k) * Vh + h) * 16u, r.v[k]);
+        stf(base, 16u * Vh * 16u + (mp * Vh + h) * 4u, r.w);
+    }
 }
 
 template <typename S, typename R>

@@ -113,15 +113,13 @@ struct CanonLaunch {
     LaunchEvents ev;
 };
 hipError_t launch_canon(const CanonLaunch &L, hipStream_t st);
-// Canonical U [V][4][3][3] -> internal link fields; with c32 (P32C), c16 (P16C)
-// and s32 (per site) also the two-row copies, and *defect = max of it and the
-// bits of the largest SU(3) defect (launch_su3_check) if above tol.
+// Canonical U [V][4][3][3] -> internal link fields; with c32 (P32C) and c16
+// (P16C) also the two-row copies, and *defect = max of it and the bits of the
+// largest SU(3) defect (launch_su3_check) if above tol.
 hipError_t launch_ingest_gauge(const Geom &g, const double *canon, void *u64, void *u32, void *u16, void *c32, void *c16,
-                               void *s32, double tol, unsigned long long *defect, hipStream_t st);
-// FP64 links -> two-row FP32 (P32C) and FP16 (P16C) link fields, and the
-// per-site copy of the two-row FP32 links read by the fused Schwarz kernel.
-hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, void *u32s,
-                                 hipStream_t st);
+                               double tol, unsigned long long *defect, hipStream_t st);
+// FP64 links -> two-row FP32 (P32C) and FP16 (P16C) link fields.
+hipError_t launch_compress_links(const Geom &g, const void *u64, void *u32c, void *u16c, hipStream_t st);
 // Per-workgroup maxima of the SU(3) defect of the FP64 links (|row2 -
 // conj(row0 x row1)|, |row norm - 1|, |<row0, row1>|) into partial[nblocks].
 hipError_t launch_su3_check(const Geom &g, const void *u64, double *partial, int nblocks, hipStream_t st);
@@ -213,9 +211,8 @@ struct RasLaunch {
     int link_prec;
     const void *in;      // even field, FP32 (or FP16 when vec_prec == P16)
     void *out;           // even field, same storage
-    const void *links;
-    const void *links_site;   // two-row FP32 links per site (P32C, fused kernel), else unused
-    const void *clov_inv;
+    const void *links, *clov_inv;            // device-memory path: the context's fields
+    const void *links_ras, *clov_inv_ras;    // fused kernel: their copies in the block order
     float kappa2;
     const Scalars *sc;   // may be null; per right-hand side, skips when done
     int nrhs;            // right-hand sides, fields `stride` bytes apart
@@ -228,6 +225,11 @@ struct RasLaunch {
     LaunchEvents ev;     // timing events of the launch (null: untimed)
 };
 hipError_t launch_ras(const RasLaunch &a, hipStream_t st);
+// A link field (launch_ras_links) or clover field (launch_ras_clover) of
+// storage `prec` in the block order of the fused Schwarz kernel with this
+// overlap (see ras_dev.h; only the parity of the overlap matters).
+hipError_t launch_ras_links(const Geom &g, int prec, int overlap, const void *src, void *dst, hipStream_t st);
+hipError_t launch_ras_clover(const Geom &g, int prec, int overlap, const void *src, void *dst, hipStream_t st);
 
 // The inner single-precision BiCGStab (right preconditioned by the fused
 // additive RAS, minimal-residual blocks, or unpreconditioned) as one
@@ -242,7 +244,7 @@ struct PersistLaunch {
     const Geom *g;
     int link_prec, vec_prec;
     const void *links, *clov_inv;
-    const void *links_site;   // per-site two-row FP32 links of the Schwarz phases (P32C)
+    const void *links_ras, *clov_inv_ras;   // the Schwarz phases' copies in the block order
     double kappa2;
     int use_ras, overlap, iters;
     bool jacobi;
