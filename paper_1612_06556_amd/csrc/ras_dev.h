@@ -101,8 +101,9 @@ WCL_D void ras_load(const void *links, int q, const RasSite &S, uint32_t Vh, uin
     st.w = MU == 3 ? (FWD ? S.sf : S.sb) : 1.f;   // used on t hops only
 }
 
+// tb: whether the block holds a hop across the t boundary (uniform).
 template <typename SL, int K, int NE>
-WCL_D void ras_compute(const RasStage<SL> &st, const float2 *src, cplx<float> acc[12])
+WCL_D void ras_compute(const RasStage<SL> &st, const float2 *src, bool tb, cplx<float> acc[12])
 {
     constexpr int MU = K >> 1;
     constexpr bool FWD = (K & 1) == 0;
@@ -116,16 +117,18 @@ WCL_D void ras_compute(const RasStage<SL> &st, const float2 *src, cplx<float> ac
     project<MU, S, float>(psi, hh);
     // the weight carries the t boundary sign (a cut hop has a zero link)
     if constexpr (MU == 3) {
+        if (tb) {
 #pragma unroll
-        for (int k = 0; k < 6; k++) hh[k] = st.w * hh[k];
+            for (int k = 0; k < 6; k++) hh[k] = st.w * hh[k];
+        }
     }
     expand_link<SL, float>(st.u, u);
     if (FWD) su3_mul(u, hh, uh);
     else su3_dag_mul(u, hh, uh);
-    accumulate<MU, S, float>(acc, uh);
+    accumulate<MU, S, float, K == 0>(acc, uh);
 }
 
-// The first two link loads of a pass, then acc = 0.  The loads' fences take
+// The first two link loads of a pass (the first hop sets acc).  The loads' fences take
 // the previous pass's accumulator, so they wait for the work that consumed
 // it.  (The workgroup barriers wait for LDS operations only, so loads issued
 // before the barrier that ends the previous pass would stay in flight across
@@ -136,8 +139,6 @@ WCL_D void ras_hop_start(const void *links, int q, const RasSite &S, uint32_t Vh
 {
     ras_load<SL, 0>(links, q, S, Vh, t, gnb, A, acc);
     ras_load<SL, 1>(links, q, S, Vh, t, gnb, B, acc);
-#pragma unroll
-    for (int c = 0; c < 12; c++) acc[c] = {0.f, 0.f};
 }
 
 // acc = (block hop of the other parity, read from src) at this thread's
@@ -147,47 +148,51 @@ WCL_D void ras_hop_start(const void *links, int q, const RasSite &S, uint32_t Vh
 // hop is computed (with FP32 the extra registers spill).
 template <typename SL, int NE>
 WCL_D void ras_hop_finish(const void *links, const void *clov, int q, const RasSite &S, uint32_t Vh, uint32_t t,
-                          const int *gnb, const float2 *src, RasStage<SL> &A, RasStage<SL> &B, cplx<float> acc[12],
+                          const int *gnb, const float2 *src, bool tb, RasStage<SL> &A, RasStage<SL> &B, cplx<float> acc[12],
                           cplx<float> out[12])
 {
     using CS = typename ClovS<SL>::T;
-    ras_compute<SL, 0, NE>(A, src, acc);
+    ras_compute<SL, 0, NE>(A, src, tb, acc);
     ras_load<SL, 2>(links, q, S, Vh, t, gnb, A, acc);
-    ras_compute<SL, 1, NE>(B, src, acc);
+    ras_compute<SL, 1, NE>(B, src, tb, acc);
     ras_load<SL, 3>(links, q, S, Vh, t, gnb, B, acc);
-    ras_compute<SL, 2, NE>(A, src, acc);
+    ras_compute<SL, 2, NE>(A, src, tb, acc);
     ras_load<SL, 4>(links, q, S, Vh, t, gnb, A, acc);
-    ras_compute<SL, 3, NE>(B, src, acc);
+    ras_compute<SL, 3, NE>(B, src, tb, acc);
     ras_load<SL, 5>(links, q, S, Vh, t, gnb, B, acc);
-    ras_compute<SL, 4, NE>(A, src, acc);
+    ras_compute<SL, 4, NE>(A, src, tb, acc);
     ras_load<SL, 6>(links, q, S, Vh, t, gnb, A, acc);
-    ras_compute<SL, 5, NE>(B, src, acc);
+    ras_compute<SL, 5, NE>(B, src, tb, acc);
     ras_load<SL, 7>(links, q, S, Vh, t, gnb, B, acc);
-    ras_compute<SL, 6, NE>(A, src, acc);
+    ras_compute<SL, 6, NE>(A, src, tb, acc);
     if constexpr (sizeof(CS) == 2) {
         ClovHalfRaw<CS> c0;
         {
             uint32_t gc = S.g, dummy = 0;
             ras_fence(acc, gc, dummy);
-            load_clover_half_raw<CS>(clov, q, gc, Vh, 0, c0);
+            load_clover_half_raw<CS>(field_rsrc(clov), q, gc, Vh, 0, c0);
         }
-        ras_compute<SL, 7, NE>(B, src, acc);
+        ras_compute<SL, 7, NE>(B, src, tb, acc);
         float cl[36];
         expand_clover_half<CS, float>(c0, 0, cl);
         clover_mul_half(cl, acc, out);
     } else {
-        ras_compute<SL, 7, NE>(B, src, acc);
+        ras_compute<SL, 7, NE>(B, src, tb, acc);
         uint32_t gc = S.g, dummy = 0;
         ras_fence(acc, gc, dummy);
+        ClovHalfRaw<CS> c0;
+        load_clover_half_raw<CS>(field_rsrc(clov), q, gc, Vh, 0, c0);
         float cl[36];
-        load_clover_half<CS, float>(clov, q, gc, Vh, 0, cl);
+        expand_clover_half<CS, float>(c0, 0, cl);
         clover_mul_half(cl, acc, out);
     }
     {
         uint32_t gc = S.g, dummy = 0;
         ras_fence(acc, gc, dummy);
+        ClovHalfRaw<CS> c1;
+        load_clover_half_raw<CS>(field_rsrc(clov), q, gc, Vh, 1, c1);
         float cl[36];
-        load_clover_half<CS, float>(clov, q, gc, Vh, 1, cl);
+        expand_clover_half<CS, float>(c1, 1, cl);
         clover_mul_half(cl, acc + 6, out + 6);
     }
 }
@@ -333,6 +338,9 @@ WCL_D void ras_block(const RasArgs &a, int blk, int rhs, RasLds<MAXNE> &L)
         for (int c = 0; c < 12; c++) sE[c * MAXNE + t] = make_float2(r[c].re, r[c].im);
     }
 
+    // hops across the t boundary exist in blocks that reach it only
+    const int t0 = bc[3] * g.B[3] - d, t1 = t0 + ev[3];   // the block's t range
+    const bool tb = g.tbc < 0 && (t0 <= 0 || t1 >= g.L[3]);
     RasStage<SL> A, B;
     cplx<float> acc[12];
 #pragma unroll
@@ -343,7 +351,7 @@ WCL_D void ras_block(const RasArgs &a, int blk, int rhs, RasLds<MAXNE> &L)
         if (active) {
             cplx<float> y[12];
             ras_hop_start<SL>(a.links, 1, SO, Vh, t, gh, A, B, acc);
-            ras_hop_finish<SL, MAXNE>(a.links, a.clov_inv, 1, SO, Vh, t, gh, sE, A, B, acc, y);
+            ras_hop_finish<SL, MAXNE>(a.links, a.clov_inv, 1, SO, Vh, t, gh, sE, tb, A, B, acc, y);
 #pragma unroll
             for (int c = 0; c < 12; c++) sO[c * MAXNE + t] = make_float2(y[c].re, y[c].im);
         }
@@ -354,7 +362,7 @@ WCL_D void ras_block(const RasArgs &a, int blk, int rhs, RasLds<MAXNE> &L)
         if (active) {
             cplx<float> w[12];
             ras_hop_start<SL>(a.links, 0, SE, Vh, t, gh, A, B, acc);
-            ras_hop_finish<SL, MAXNE>(a.links, a.clov_inv, 0, SE, Vh, t, gh, sO, A, B, acc, w);
+            ras_hop_finish<SL, MAXNE>(a.links, a.clov_inv, 0, SE, Vh, t, gh, sO, tb, A, B, acc, w);
             float qr = 0.f, qi = 0.f, qq = 0.f;
 #pragma unroll
             for (int c = 0; c < 12; c++) {
@@ -367,9 +375,6 @@ WCL_D void ras_block(const RasArgs &a, int blk, int rhs, RasLds<MAXNE> &L)
                 }
             }
             dots[0] = qr; dots[1] = qi; dots[2] = qq;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 12; c++) qv[c] = {0.f, 0.f};
         }
         float ar = 1.f, ai = 0.f;
         if constexpr (!JAC) {
@@ -391,23 +396,27 @@ WCL_D void ras_block(const RasArgs &a, int blk, int rhs, RasLds<MAXNE> &L)
         }
         if (active) {
             // z += alpha r (kept only where it is written: the core), r -= alpha q
-            cplx<float> z[12];
             if (core) {
+                cplx<float> z[12];
                 if (it == 0 && !a.accumulate) {
 #pragma unroll
                     for (int c = 0; c < 12; c++) z[c] = {0.f, 0.f};
                 } else {
                     load_spinor<SV, float>(rout, hE, Vh, z);
                 }
+#pragma unroll
+                for (int c = 0; c < 12; c++) {
+                    const float2 r = sE[c * MAXNE + t];
+                    z[c] = {fmaf(ar, r.x, fmaf(-ai, r.y, z[c].re)), fmaf(ar, r.y, fmaf(ai, r.x, z[c].im))};
+                }
+                store_spinor<SV, float>(rout, hE, Vh, z);
             }
 #pragma unroll
             for (int c = 0; c < 12; c++) {
                 const float2 r = sE[c * MAXNE + t];
-                if (core) z[c] = {fmaf(ar, r.x, fmaf(-ai, r.y, z[c].re)), fmaf(ar, r.y, fmaf(ai, r.x, z[c].im))};
                 sE[c * MAXNE + t] = make_float2(fmaf(-ar, qv[c].re, fmaf(ai, qv[c].im, r.x)),
                                                 fmaf(-ar, qv[c].im, fmaf(-ai, qv[c].re, r.y)));
             }
-            if (core) store_spinor<SV, float>(rout, hE, Vh, z);
         }
     }
 }

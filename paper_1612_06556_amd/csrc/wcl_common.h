@@ -236,8 +236,8 @@ WCL_D void project(const cplx<R> psi[12], cplx<R> h[6])
 }
 
 // acc += (1 + S gamma_mu) applied to a projected, colour-rotated half spinor:
-// upper += uh, lower += S G^dag uh.
-template <int MU, int S, typename R>
+// upper += uh, lower += S G^dag uh.  SET: acc = that.
+template <int MU, int S, typename R, bool SET = false>
 WCL_D void accumulate(cplx<R> acc[12], const cplx<R> uh[6])
 {
 #pragma unroll
@@ -245,11 +245,11 @@ WCL_D void accumulate(cplx<R> acc[12], const cplx<R> uh[6])
         const int c0 = gcol(MU, r);  // G^dag has the same column pattern as G
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            acc[r * 3 + c] = acc[r * 3 + c] + uh[r * 3 + c];
             cplx<R> t;
             if (r == 0) t = mul_unit<gdcode(MU, 0) + (S < 0 ? 2 : 0)>(uh[c0 * 3 + c]);
             else t = mul_unit<gdcode(MU, 1) + (S < 0 ? 2 : 0)>(uh[c0 * 3 + c]);
-            acc[(2 + r) * 3 + c] = acc[(2 + r) * 3 + c] + t;
+            acc[r * 3 + c] = SET ? uh[r * 3 + c] : acc[r * 3 + c] + uh[r * 3 + c];
+            acc[(2 + r) * 3 + c] = SET ? t : acc[(2 + r) * 3 + c] + t;
         }
     }
 }
@@ -441,18 +441,19 @@ WCL_D __amdgpu_buffer_rsrc_t field_rsrc(const void *base)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)0x80000000u, 0x00020000);
 }
+// soff: a uniform part of the offset (added by the load unit, not per lane).
 template <typename T>
-WCL_D T ldb(__amdgpu_buffer_rsrc_t rs, uint32_t off)
+WCL_D T ldb(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t soff = 0)
 {
     T r;
     if constexpr (sizeof(T) == 16) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, soff, 0);
         __builtin_memcpy(&r, &v, 16);
     } else if constexpr (sizeof(T) == 8) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, soff, 0);
         __builtin_memcpy(&r, &v, 8);
     } else {
-        const unsigned int v = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+        const unsigned int v = __builtin_amdgcn_raw_buffer_load_b32(rs, off, soff, 0);
         __builtin_memcpy(&r, &v, 4);
     }
     return r;
@@ -468,18 +469,18 @@ WCL_D void load_link_raw_or_zero(__amdgpu_buffer_rsrc_t rs, int mu, int p, uint3
     const uint32_t o16 = in ? h * 16u : OUT, o8 = in ? h * 8u : OUT, o4 = in ? h * 4u : OUT;
     if constexpr (std::is_same<S, R12f>::value) {
 #pragma unroll
-        for (uint32_t k = 0; k < 3; k++) r.v[k] = ldb<float4>(rs, (mp * 3 + k) * Vh * 16u + o16);
+        for (uint32_t k = 0; k < 3; k++) r.v[k] = ldb<float4>(rs, o16, (mp * 3 + k) * Vh * 16u);
     } else if constexpr (std::is_same<S, R12h>::value) {
-        r.v = ldb<uint4>(rs, mp * Vh * 16u + o16);
-        r.w = ldb<uint2>(rs, 8u * Vh * 16u + mp * Vh * 8u + o8);
+        r.v = ldb<uint4>(rs, o16, mp * Vh * 16u);
+        r.w = ldb<uint2>(rs, o8, 8u * Vh * 16u + mp * Vh * 8u);
     } else if constexpr (sizeof(S) == 4) {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; k++) r.v[k] = ldb<float4>(rs, (mp * 4 + k) * Vh * 16u + o16);
-        r.w = ldb<float2>(rs, 32u * Vh * 16u + mp * Vh * 8u + o8);
+        for (uint32_t k = 0; k < 4; k++) r.v[k] = ldb<float4>(rs, o16, (mp * 4 + k) * Vh * 16u);
+        r.w = ldb<float2>(rs, o8, 32u * Vh * 16u + mp * Vh * 8u);
     } else {
 #pragma unroll
-        for (uint32_t k = 0; k < 2; k++) r.v[k] = ldb<uint4>(rs, (mp * 2 + k) * Vh * 16u + o16);
-        r.w = ldb<uint32_t>(rs, 16u * Vh * 16u + mp * Vh * 4u + o4);
+        for (uint32_t k = 0; k < 2; k++) r.v[k] = ldb<uint4>(rs, o16, (mp * 2 + k) * Vh * 16u);
+        r.w = ldb<uint32_t>(rs, o4, 16u * Vh * 16u + mp * Vh * 4u);
     }
 }
 
@@ -711,6 +712,20 @@ WCL_D void expand_clover_half(const ClovHalfRaw<S> &r, int half, R c[36])
         const int off = half ? 4 : 0;
 #pragma unroll
         for (int k = 0; k < 36; k++) c[k] = (R)t[off + k];
+    }
+}
+
+// The same through a buffer resource (FP32 and FP16 fields, below 2 GiB).
+template <typename S>
+WCL_D void load_clover_half_raw(__amdgpu_buffer_rsrc_t rs, int p, uint32_t h, uint32_t Vh, int half, ClovHalfRaw<S> &r)
+{
+    if constexpr (sizeof(S) == 4) {
+#pragma unroll
+        for (uint32_t k = 0; k < 9; k++) r.v[k] = ldb<float4>(rs, h * 16u, ((uint32_t)p * 18 + 9 * half + k) * Vh * 16u);
+    } else {
+        const uint32_t w0 = half ? 4u : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < 5; k++) r.v[k] = ldb<uint4>(rs, h * 16u, ((uint32_t)p * 9 + w0 + k) * Vh * 16u);
     }
 }
 
