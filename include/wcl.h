@@ -113,15 +113,15 @@ int wcl_set_compression(wcl_ctx *ctx, int enable);
  * storage, FP32 arithmetic).  in_dev / out_dev: complex128
  * [nrhs][V][4][3] device buffers owned by the caller; they must not
  * overlap.  WCL_ESTATE before wcl_set_params; WCL_EINVAL for nrhs < 1, an
- * unknown prec or a null pointer.  Runs as one launch and
- * needs no workspace. */
+ * unknown prec or a null pointer; WCL_ENOMEM when the context's workspace
+ * cannot grow (prec 16 on large lattices: allocated on first use and kept;
+ * the other calls need none). */
 int wcl_apply(wcl_ctx *ctx, const double *in_dev, double *out_dev, int nrhs, int dagger, int prec);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): wcl_apply
  * without any allocation.  Same arguments, layouts, ownership, results and
- * errors as wcl_apply (the same kernels run in the same order), and it
- * records no profiling events.  Its limit is lattices of at most 174762
+ * errors as wcl_apply, and it records no profiling events.  Its limit is lattices of at most 174762
  * sites (e.g. 8^4, 16^3x32): larger ones fail with WCL_EINVAL.  Calls on
  * different contexts, streams or host threads are independent.  The
  * context's resident fields come from wcl_set_gauge and wcl_set_params,

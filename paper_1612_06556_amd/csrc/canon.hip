@@ -14,7 +14,7 @@ namespace wcl {
 
 namespace {
 
-constexpr uint32_t CUT = 0x80000000u;   // beyond every buffer resource: reads zero
+constexpr uint32_t CUT = 0x80000000u;   // no LDS slot; beyond every buffer resource
 
 // NP pairs of canonical sites in the storage SS of a tier: component-major
 // 16-byte words, slot = parity * NP + pair.  The stride is odd in 16-byte
@@ -154,7 +154,10 @@ WCL_D void write_pairs(const PairLds<SS, NP> &L, uint32_t np, double2 *canon)
         const uint32_t xo = c >= 12u ? 1u : 0u, p = (xo + (b >> 31)) & 1u;
         double2 v = make_double2(0.0, 0.0);
         if (!ODD0 || p == 0) v = get_component<SS>(L.w, PairLds<SS, NP>::STRIDE, (int)(p * NP + pr), (int)(c - 12u * xo));
-        canon[(size_t)(b & 0x7fffffffu) * 12 + c] = v;
+        // written once and not read here again: kept out of the caches' way
+        u32x4 w;
+        __builtin_memcpy(&w, &v, 16);
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(canon + (size_t)(b & 0x7fffffffu) * 12 + c));
     }
 }
 
@@ -264,16 +267,18 @@ hipError_t launch_unpack(const Geom &g, int prec, bool odd_zero, const void *eo,
 // ---------------------------------------------------------------------------
 // D, D^dag, H, T or T^-1 from canonical spinor to canonical spinor in one
 // launch: the workgroup's own pairs come from LDS (rounded to the tier's
-// storage), a neighbour outside them straight from the canonical vector
-// through a buffer resource, where a lane whose neighbour is in LDS has an
-// out-of-range offset (zero, no memory traffic): every load is unconditional,
-// so the next hop's operands stay in flight while a hop is computed.  Per
-// site the arithmetic and its order are those of the even/odd hop.  Both
-// parities in one workgroup read each of its links from memory once.  Bound
-// by HBM on large lattices: D^dag in FP64 on 24^3x32 takes 164 us (4.1 TB/s of
-// the call's 679 MB; 325 us as pack, one launch per parity and unpack), D in
-// FP32 on 32^3x64 529 us (1158), D in two-row FP16 on 12 x 16^3x32 245 us
-// (756); by latency on 8^4, FP64: 9.7 us a call (31.8).
+// storage), a neighbour outside them straight from the canonical vector, by
+// the lanes that have one there (unconditional loads, reading zero in the
+// others, kept the texture units busy 95% of the time on large lattices).  Per site the
+// arithmetic and its order are those of the even/odd hop.  Both
+// parities in one workgroup read each of its links from memory once.  Output
+// and clover go past the caches (non-temporal: 8 to 10% of the time), which
+// leaves L2 to the faces that regions share.  Bound by the memory fabric on
+// large lattices: D^dag in FP64 on 24^3x32 takes 143 us (844 MB moved for the
+// call's 679 MB, 5.9 TB/s; 325 us as pack, one launch per parity and unpack),
+// D in FP32 on 32^3x64 485 us (2.8 GB for 2.0, 5.8 TB/s; 1158); by latency on
+// 8^4, FP64: 9.7 us a call (31.8).  Grouping right-hand sides by regions whose
+// operator fits L2 measured the same.
 struct CanonArgs {
     Geom g;
     const double2 *in;
@@ -291,7 +296,7 @@ struct CanonStage {
 };
 
 template <typename SL, int K, int NP, typename R>
-WCL_D void canon_load(const CanonArgs &a, __amdgpu_buffer_rsrc_t rs, const Site &s, uint32_t p, uint32_t h0, uint32_t h,
+WCL_D void canon_load(const CanonArgs &a, const double2 *in, const Site &s, uint32_t p, uint32_t h0, uint32_t h,
                       uint32_t n, CanonStage<SL> &st, cplx<R> acc[12])
 {
     constexpr int MU = K >> 1;
@@ -305,9 +310,16 @@ WCL_D void canon_load(const CanonArgs &a, __amdgpu_buffer_rsrc_t rs, const Site 
     const uint32_t l = hn - h0;
     const bool near = l < (uint32_t)NP;
     st.slot = near ? (1u - p) * NP + l : CUT;
-    const uint32_t off = near ? CUT : nn * 192u;
+    if constexpr (NP == 32) {
+        // few waves, each waiting for its own chain of loads: unconditional loads
+        // keep the wait counts exact (out of range, so zero, where the LDS serves)
+        const uint32_t off = near ? CUT : nn * 192u;
 #pragma unroll
-    for (uint32_t i = 0; i < 12; i++) st.far[i] = ldb<double2>(rs, off + i * 16u);
+        for (uint32_t i = 0; i < 12; i++) st.far[i] = ldb<double2>(field_rsrc(in), off + i * 16u);
+    } else if (!near) {
+#pragma unroll
+        for (uint32_t i = 0; i < 12; i++) st.far[i] = ldf<double2>(in, nn * 192u + i * 16u);
+    }
     if (FWD) load_link_raw<SL>(a.links, MU, (int)p, h, g.Vh, st.u);
     else load_link_raw<SL>(a.links, MU, 1 - (int)p, hn, g.Vh, st.u);
 }
@@ -346,13 +358,13 @@ WCL_D void canon_compute(const CanonArgs &a, const PairLds<SS, NP> &L, const Sit
 }
 
 template <typename SL, typename SS, int K, int SG, int NP, typename R>
-WCL_D void canon_hops(const CanonArgs &a, __amdgpu_buffer_rsrc_t rs, const PairLds<SS, NP> &L, const Site &s, uint32_t p,
+WCL_D void canon_hops(const CanonArgs &a, const double2 *in, const PairLds<SS, NP> &L, const Site &s, uint32_t p,
                       uint32_t h0, uint32_t h, uint32_t n, CanonStage<SL> st[2], cplx<R> acc[12])
 {
     if constexpr (K < 8) {
-        if constexpr (K + 1 < 8) canon_load<SL, K + 1, NP, R>(a, rs, s, p, h0, h, n, st[(K + 1) & 1], acc);
+        if constexpr (K + 1 < 8) canon_load<SL, K + 1, NP, R>(a, in, s, p, h0, h, n, st[(K + 1) & 1], acc);
         canon_compute<SL, SS, K, SG, NP, R>(a, L, s, st[K & 1], acc);
-        canon_hops<SL, SS, K + 1, SG, NP, R>(a, rs, L, s, p, h0, h, n, st, acc);
+        canon_hops<SL, SS, K + 1, SG, NP, R>(a, in, L, s, p, h0, h, n, st, acc);
     }
 }
 
@@ -378,10 +390,9 @@ __global__ void __launch_bounds__(2 * NP) k_canon(CanonArgs a)
         if constexpr (MODE != CLOV_H) {
             const Site s = decompose(g, (int)h, (int)p);
             const uint32_t n = (uint32_t)(s.x[0] + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3])));
-            const __amdgpu_buffer_rsrc_t rs = field_rsrc(in);
             CanonStage<SL> st[2];
-            canon_load<SL, 0, NP, R>(a, rs, s, p, h0, h, n, st[0], acc);
-            canon_hops<SL, SS, 0, DAG ? -1 : 1, NP, R>(a, rs, L, s, p, h0, h, n, st, acc);
+            canon_load<SL, 0, NP, R>(a, in, s, p, h0, h, n, st[0], acc);
+            canon_hops<SL, SS, 0, DAG ? -1 : 1, NP, R>(a, in, L, s, p, h0, h, n, st, acc);
         }
         if constexpr (MODE == HOP) {
 #pragma unroll
@@ -396,7 +407,9 @@ __global__ void __launch_bounds__(2 * NP) k_canon(CanonArgs a)
                 uint32_t hc = h, dummy = 0;
                 pipeline_fence(acc, hc, dummy);
                 R c[36];
-                load_clover_half<typename ClovS<SL>::T, R>(a.clov, (int)p, hc, Vh, half, c);
+                // non-temporal: L2 keeps what neighbouring workgroups share (FP16: 2% slower
+                // for 12 right-hand sides, which share it themselves)
+                load_clover_half<typename ClovS<SL>::T, R, sizeof(SS) != 2>(a.clov, (int)p, hc, Vh, half, c);
                 clover_mul_half(c, xv + 6 * half, o + 6 * half);
             }
             if constexpr (MODE == CLOVX) {
@@ -409,6 +422,91 @@ __global__ void __launch_bounds__(2 * NP) k_canon(CanonArgs a)
     if (i < np) put_spinor<SS, R>(L.w, PairLds<SS, NP>::STRIDE, (int)threadIdx.x, o);
     __syncthreads();
     write_pairs<SS, NP, false>(L, np, a.out + (size_t)rhs * 24 * Vh);
+}
+
+// The same from e/o fields in the tier's storage (parity-major, in_stride bytes
+// between right-hand sides) to canonical spinors: neighbours at 16-byte words
+// a lane instead of 192 bytes of the canonical vector.
+template <typename SL, int K, int SG, typename R, typename SS>
+WCL_D void eo_hops(const CanonArgs &a, const char *in, const Site &s, uint32_t p, uint32_t h, HopStage<SL, R> st[2],
+                   cplx<R> acc[12])
+{
+    // hop_load and hop_compute of the even/odd kernel, unstaged
+    if constexpr (K < 8) {
+        HopArgs q;
+        q.g = a.g;
+        q.links = a.links;
+        q.p = (int)p;
+        const LdsIn none{};
+        if constexpr (K + 1 < 8) hop_load<SL, SS, K + 1, false, 0, R>(q, s, h, in, none, st[(K + 1) & 1], acc);
+        hop_compute<K, SG, SL, R>(st[K & 1], acc);
+        eo_hops<SL, K + 1, SG, R, SS>(a, in, s, p, h, st, acc);
+    }
+}
+
+template <typename SL, typename SS, int MODE, bool DAG>
+__global__ void __launch_bounds__(256) k_eo_canon(CanonArgs a, const char *eo, size_t eo_stride)
+{
+    using R = typename Real<SL>::T;
+    constexpr int NP = 128;
+    __shared__ PairLds<SS, NP> L;
+    const Geom &g = a.g;
+    const int lin = a.xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const uint32_t rhs = lin % a.nrhs, h0 = lin / a.nrhs * NP;
+    const uint32_t Vh = g.Vh, np = min((uint32_t)NP, Vh - h0);
+    const uint32_t p = threadIdx.x / NP, i = threadIdx.x % NP, h = h0 + i;
+    if (threadIdx.x < np) L.base[threadIdx.x] = pair_base(g, (int)(h0 + threadIdx.x));
+    eo += rhs * eo_stride;
+    if (i < np) {
+        const size_t hb = spinor_bytes(sizeof(SS), Vh);
+        const char *other = eo + (1 - p) * hb;
+        cplx<R> acc[12], o[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[k] = {R(0), R(0)};
+        const Site s = decompose(g, (int)h, (int)p);
+        HopArgs q;
+        q.g = a.g;
+        q.links = a.links;
+        q.p = (int)p;
+        HopStage<SL, R> st[2];
+        hop_load<SL, SS, 0, false, 0, R>(q, s, h, other, LdsIn{}, st[0], acc);
+        eo_hops<SL, 0, DAG ? -1 : 1, R, SS>(a, other, s, p, h, st, acc);
+        if constexpr (MODE == HOP) {
+#pragma unroll
+            for (int k = 0; k < 12; k++) o[k] = acc[k];
+        } else {
+            cplx<R> xv[12];
+            uint32_t hx = h, dummy = 0;
+            pipeline_fence(acc, hx, dummy);
+            load_spinor<SS, R>(eo + p * hb, hx, Vh, xv);
+            const R cf = (R)a.coef;
+#pragma unroll
+            for (int half = 0; half < 2; half++) {
+                uint32_t hc = h, none = 0;
+                pipeline_fence(acc, hc, none);
+                R c[36];
+                load_clover_half<typename ClovS<SL>::T, R>(a.clov, (int)p, hc, Vh, half, c);
+                clover_mul_half(c, xv + 6 * half, o + 6 * half);
+            }
+#pragma unroll
+            for (int k = 0; k < 12; k++) o[k] = {fmar(cf, acc[k].re, o[k].re), fmar(cf, acc[k].im, o[k].im)};
+        }
+        put_spinor<SS, R>(L.w, PairLds<SS, NP>::STRIDE, (int)threadIdx.x, o);
+    }
+    __syncthreads();
+    write_pairs<SS, NP, false>(L, np, a.out + (size_t)rhs * 24 * Vh);
+}
+
+template <typename SL, typename SS>
+static hipError_t eo_canon_dispatch(const CanonLaunch &L, const CanonArgs &a, hipStream_t st)
+{
+    dim3 grid(((a.g.Vh + 127) / 128) * a.nrhs), block(256);
+    const char *eo = (const char *)L.eo;
+    if (L.mode == HOP && !L.dagger) ext_launch(k_eo_canon<SL, SS, HOP, false>, grid, block, 0, st, L.ev, a, eo, L.eo_stride);
+    else if (L.mode == CLOVX && !L.dagger) ext_launch(k_eo_canon<SL, SS, CLOVX, false>, grid, block, 0, st, L.ev, a, eo, L.eo_stride);
+    else if (L.mode == CLOVX) ext_launch(k_eo_canon<SL, SS, CLOVX, true>, grid, block, 0, st, L.ev, a, eo, L.eo_stride);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 template <typename SL, typename SS>
@@ -444,6 +542,15 @@ hipError_t launch_canon(const CanonLaunch &L, hipStream_t st)
     a.nrhs = L.nrhs;
     a.xcd = L.xcd;
     if (L.nrhs < 1) return hipErrorInvalidValue;
+    if (L.eo) {
+        switch (L.link_prec) {
+        case P32: return eo_canon_dispatch<float, float>(L, a, st);
+        case P16: return eo_canon_dispatch<__half, __half>(L, a, st);
+        case P32C: return eo_canon_dispatch<R12f, float>(L, a, st);
+        case P16C: return eo_canon_dispatch<R12h, __half>(L, a, st);
+        default: return hipErrorInvalidValue;
+        }
+    }
     switch (L.link_prec) {
     case P64: return canon_dispatch<double, double>(L, a, st);
     case P32: return canon_dispatch<float, float>(L, a, st);

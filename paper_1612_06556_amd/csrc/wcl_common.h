@@ -669,21 +669,21 @@ template <typename S> struct ClovHalfRaw { float4 v[9]; };
 template <> struct ClovHalfRaw<double> { double2 v[18]; };
 template <> struct ClovHalfRaw<__half> { uint4 v[5]; };
 
-template <typename S>
+template <typename S, bool NT = false>
 WCL_D void load_clover_half_raw(const void *base, int p, uint32_t h, uint32_t Vh, int half, ClovHalfRaw<S> &r)
 {
     static_assert(!std::is_empty<S>::value, "two-row link tags are link storage only");
     if constexpr (sizeof(S) == 8) {
 #pragma unroll
-        for (uint32_t k = 0; k < 18; k++) r.v[k] = ldf<double2>(base, (((uint32_t)p * 36 + 18 * half + k) * Vh + h) * 16u);
+        for (uint32_t k = 0; k < 18; k++) r.v[k] = ldx<NT, double2>(base, (((uint32_t)p * 36 + 18 * half + k) * Vh + h) * 16u);
     } else if constexpr (sizeof(S) == 4) {
 #pragma unroll
-        for (uint32_t k = 0; k < 9; k++) r.v[k] = ldf<float4>(base, (((uint32_t)p * 18 + 9 * half + k) * Vh + h) * 16u);
+        for (uint32_t k = 0; k < 9; k++) r.v[k] = ldx<NT, float4>(base, (((uint32_t)p * 18 + 9 * half + k) * Vh + h) * 16u);
     } else {
         // 36 halves starting at half 36*half: uint4 words w0 .. w0+4 (8 halves each)
         const uint32_t w0 = half ? 4u : 0u;
 #pragma unroll
-        for (uint32_t k = 0; k < 5; k++) r.v[k] = ldf<uint4>(base, (((uint32_t)p * 9 + w0 + k) * Vh + h) * 16u);
+        for (uint32_t k = 0; k < 5; k++) r.v[k] = ldx<NT, uint4>(base, (((uint32_t)p * 9 + w0 + k) * Vh + h) * 16u);
     }
 }
 
@@ -729,11 +729,11 @@ WCL_D void load_clover_half_raw(__amdgpu_buffer_rsrc_t rs, int p, uint32_t h, ui
     }
 }
 
-template <typename S, typename R>
+template <typename S, typename R, bool NT = false>
 WCL_D void load_clover_half(const void *base, int p, uint32_t h, uint32_t Vh, int half, R c[36])
 {
     ClovHalfRaw<S> r;
-    load_clover_half_raw<S>(base, p, h, Vh, half, r);
+    load_clover_half_raw<S, NT>(base, p, h, Vh, half, r);
     expand_clover_half<S, R>(r, half, c);
 }
 

@@ -110,6 +110,8 @@ struct CanonLaunch {
     const void *links, *clov;
     double coef;
     int nrhs, xcd;
+    const void *eo;    // not null (modes HOP and CLOVX, FP32 / FP16): the input as packed e/o
+    size_t eo_stride;  // fields, both parities, this many bytes apart
     LaunchEvents ev;
 };
 hipError_t launch_canon(const CanonLaunch &L, hipStream_t st);
