@@ -85,7 +85,7 @@ struct wcl_ctx {
     GrasPlan gras{};                   // block fields of the global-memory Schwarz path
     bool gras_ready = false;
     std::vector<Buf> ws;        // workspace, indexed by slot
-    double *partials = nullptr; // [cap][6][pstride]
+    double *partials = nullptr; // [2][cap][6][pstride]: the second set for the x, r update's sums
     int pstride = 0;            // partial sums per term and right-hand side (>= every launch's workgroups)
     Scalars *sc = nullptr;      // [3][cap]: outer, inner, final/scratch scalars per right-hand side
     Scalars *sc_host = nullptr; // pinned mirror
@@ -475,7 +475,7 @@ int ensure_batch(wcl_ctx *c, int n)
     if (c->sc_host) (void)hipHostFree(c->sc_host);
     c->sc = nullptr; c->partials = nullptr; c->sc_host = nullptr; c->cap = 0;
     CHK(alloc((void **)&c->sc, sizeof(Scalars) * 3 * n));
-    CHK(alloc((void **)&c->partials, sizeof(double) * 6 * (size_t)c->pstride * n));
+    CHK(alloc((void **)&c->partials, sizeof(double) * 2 * 6 * (size_t)c->pstride * n));
     if (hipHostMalloc((void **)&c->sc_host, sizeof(Scalars) * 3 * n, hipHostMallocDefault) != hipSuccess)
         return fail(WCL_ENOMEM, "hipHostMalloc failed");
     memset(c->sc_host, 0, sizeof(Scalars) * 3 * n);
@@ -484,6 +484,7 @@ int ensure_batch(wcl_ctx *c, int n)
     return WCL_OK;
 }
 
+double *partials2(wcl_ctx *c) { return c->partials + 6 * (size_t)c->pstride * c->cap; }
 Scalars *SO(wcl_ctx *c) { return c->sc; }
 Scalars *SI(wcl_ctx *c) { return c->sc + c->cap; }
 Scalars *SF(wcl_ctx *c) { return c->sc + 2 * c->cap; }
@@ -1104,13 +1105,30 @@ struct InnerCfg {
     bool persistent;               // the whole inner solve as one cooperative launch
 };
 
+// Whether the finaliser steps of an iteration ride in the vector updates
+// (FoldArgs) instead of launches of their own: every workgroup of an update then
+// adds the partials of the launch before it again, which pays up to 1024 of
+// them: FP64 e/o at 16^3x32 (256 partials) 156 -> 145 us an iteration, two-row FP32
+// at 24^3x32 (864) 1% of the Schwarz solve; with 4096 (32^3x64) each of 2048
+// workgroups would read 64 KB for a step of 8 us.
+bool folds(wcl_ctx *c, int prec)
+{
+    const HopLaunch L = hop_base(c, prec, prec);
+    return hop_parts(L) <= 1024;
+}
+
 // One BiCGStab iteration (right preconditioned by RAS when enabled) on the
 // FP32 Schur system for n right-hand sides, scalars sc[0, n) on the device.
 int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, int n)
 {
     const size_t m = 12 * (size_t)c->Vh;   // complex numbers per right-hand side
     const int lp = cfg.lprec, vp = cfg.vprec;
-    HIPCHK(launch_bicg_p(vp, m, w.r32, w.p32, w.v32, sc, c->st, n, m));
+    // the reductions ride in the Schur operator's second half and the x, r
+    // update, except with several right-hand sides per thread
+    const bool fused = c->hop_rhs == 1 || n == 1;
+    const bool fold = fused && folds(c, lp);
+    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n)};
+    HIPCHK(launch_bicg_p(vp, m, w.r32, w.p32, w.v32, sc, c->st, n, m, fold ? &rho : nullptr));
     void *ph = w.p32, *sh = w.s32;
     RasLaunch R{};
     if (cfg.ras) {
@@ -1132,20 +1150,18 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
         else CHK(run_ras(c, R));
         ph = w.ph32;
     }
-    // the reductions ride in the Schur operator's second half and the x, r
-    // update, except with several right-hand sides per thread
-    const bool fused = c->hop_rhs == 1 || n == 1;
     int np = 0;
     if (fused) {
         CHK(schur_dot(c, lp, vp, ph, w.v32, w.o32, sc, n, 1, w.rt32, &np));
-        HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+        if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
     } else {
         CHK(schur(c, lp, vp, ph, w.v32, w.o32, sc, n));
         const void *a[1] = {w.rt32}, *b[1] = {w.v32};
         HIPCHK(launch_dots(vp, m, 1, a, b, c->partials, sc, c->st, n, m, c->pstride));
         HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride));
     }
-    HIPCHK(launch_bicg_s(vp, m, w.r32, w.v32, w.s32, sc, c->st, n, m));
+    const FoldArgs alpha{c->partials, c->pstride, np};
+    HIPCHK(launch_bicg_s(vp, m, w.r32, w.v32, w.s32, sc, c->st, n, m, fold ? &alpha : nullptr));
     if (cfg.ras) {
         R.in = w.s32;
         R.out = w.sh32;
@@ -1155,10 +1171,11 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
     }
     if (fused) {
         CHK(schur_dot(c, lp, vp, sh, w.t32, w.o32, sc, n, 2, w.s32, &np));
-        HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
-        HIPCHK(launch_bicg_xr_dots(vp, m, w.x32, ph, sh, w.r32, w.s32, w.t32, w.rt32, sc, c->st, n, m, c->partials,
-                                   c->pstride, &np));
-        HIPCHK(launch_finalize(BICG_RHO, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+        if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+        const FoldArgs omega{c->partials, c->pstride, np};
+        HIPCHK(launch_bicg_xr_dots(vp, m, w.x32, ph, sh, w.r32, w.s32, w.t32, w.rt32, sc, c->st, n, m, partials2(c),
+                                   c->pstride, &np, fold ? &omega : nullptr));
+        if (!fold) HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, np));
     } else {
         CHK(schur(c, lp, vp, sh, w.t32, w.o32, sc, n));
         {
@@ -1276,6 +1293,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     std::vector<int> it_prev(n, 0);
     std::vector<size_t> rec_mark;  // profile records at the start of each queued iteration
     Scalars *h = HI(c);
+    const bool fold = (c->hop_rhs == 1 || n == 1) && folds(c, cfg.lprec);
     while (launched < cfg.maxit) {
         chunk = std::max(1, std::min(chunk, cfg.maxit - launched));
         if (cfg.graph && !*cfg.exec) {
@@ -1301,6 +1319,8 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
             if (cfg.graph) HIPCHK(hipGraphLaunch(*cfg.exec, c->st));
             else CHK(inner_iteration(c, cfg, w, sc, n));
         }
+        if (fold)   // the last iteration's step, before the host reads the scalars
+            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n)));
         launched += chunk;
         CHK(read_sc(c, h, sc, n));
         bool all = true;
@@ -1465,6 +1485,11 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
     for (int k = 0; k < n; k++) info[k].outer_iters = 0;
     int iter = 0;
     const int every = d.flex ? 1 : std::max(1, o.check_every);
+    // on the even/odd system the reductions ride in the Schur operator's second
+    // half and the x/r update, as in the inner solver
+    const bool fused = d.eo && (c->hop_rhs == 1 || n == 1);
+    const bool fold = fused && folds(c, P64);
+    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n)};
     while (iter < o.max_outer) {
         bool any_active = false;
         for (int k = 0; k < n; k++) any_active = any_active || !final_[k];
@@ -1473,27 +1498,25 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
         std::vector<size_t> rec_mark;
         for (int q = 0; q < chunk; q++) {
             rec_mark.push_back(c->recs.size());
-            HIPCHK(launch_bicg_p(P64, m, w.r, w.p, w.v, sc, c->st, n, m));
+            HIPCHK(launch_bicg_p(P64, m, w.r, w.p, w.v, sc, c->st, n, m, fold ? &rho : nullptr));
             void *ph = w.p, *sh = w.s;
             if (d.flex) {
                 CHK(inner_solve(c, *cfg, w, w.p, w.ph, n, it_inner));
                 for (int k = 0; k < n; k++) info[k].inner_iters_total += final_[k] ? 0 : it_inner[k];
                 ph = w.ph;
             }
-            // on the even/odd system the reductions ride in the Schur operator's
-            // second half and the x/r update, as in the inner solver
-            const bool fused = d.eo && (c->hop_rhs == 1 || n == 1);
             int np = 0;
             if (fused) {
                 CHK(schur_dot(c, P64, P64, ph, w.v, w.o, sc, n, 1, w.rt, &np));
-                HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+                if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
             } else {
                 CHK(apply_A(c, d, w, ph, w.v, sc));
                 const void *a[1] = {w.rt}, *b[1] = {w.v};
                 HIPCHK(launch_dots(P64, m, 1, a, b, c->partials, sc, c->st, n, m, c->pstride));
                 HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride));
             }
-            HIPCHK(launch_bicg_s(P64, m, w.r, w.v, w.s, sc, c->st, n, m));
+            const FoldArgs alpha{c->partials, c->pstride, np};
+            HIPCHK(launch_bicg_s(P64, m, w.r, w.v, w.s, sc, c->st, n, m, fold ? &alpha : nullptr));
             if (d.flex) {
                 CHK(inner_solve(c, *cfg, w, w.s, w.sh, n, it_inner));
                 for (int k = 0; k < n; k++) info[k].inner_iters_total += final_[k] ? 0 : it_inner[k];
@@ -1501,10 +1524,11 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
             }
             if (fused) {
                 CHK(schur_dot(c, P64, P64, sh, w.t, w.o, sc, n, 2, w.s, &np));
-                HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
-                HIPCHK(launch_bicg_xr_dots(P64, m, d.x, ph, sh, w.r, w.s, w.t, w.rt, sc, c->st, n, m, c->partials,
-                                           c->pstride, &np));
-                HIPCHK(launch_finalize(BICG_RHO, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+                if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+                const FoldArgs omega{c->partials, c->pstride, np};
+                HIPCHK(launch_bicg_xr_dots(P64, m, d.x, ph, sh, w.r, w.s, w.t, w.rt, sc, c->st, n, m, partials2(c),
+                                           c->pstride, &np, fold ? &omega : nullptr));
+                if (!fold) HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, np));
             } else {
                 CHK(apply_A(c, d, w, sh, w.t, sc));
                 {
@@ -1521,6 +1545,8 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
             }
         }
         iter += chunk;
+        if (fold)   // the last iteration's step, before the host reads the scalars
+            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n)));
         CHK(read_sc(c, HO(c), sc, n));
         bool candidates = false;
         int exec = 0;  // iterations of this chunk that did work for some right-hand side

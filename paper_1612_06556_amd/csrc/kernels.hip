@@ -8,6 +8,8 @@
 //   T = 1 - c_sw kappa sum_{mu<nu} sigma_{mu nu} F_{mu nu}  (clover leaves),
 // in the chiral basis; H maps one parity onto the other ("hopping matrix
 // multiplication", the paper's measured kernel, Sec. 3).
+#include <algorithm>
+
 #include "hop_dev.h"
 
 namespace wcl {
@@ -464,6 +466,55 @@ WCL_D void cdiv(const double a[2], const double b[2], double o[2])
     o[1] = (a[1] * b[0] - a[0] * b[1]) / d;
 }
 
+// omega = <t, s> / <t, t> from the sums (Re, Im <t, s>, <t, t>).
+WCL_D void bicg_omega(const double v[3], double omega[2])
+{
+    const double tt = v[2];
+    if (tt == 0.0) { omega[0] = 0.0; omega[1] = 0.0; }
+    else { omega[0] = v[0] / tt; omega[1] = v[1] / tt; }
+}
+
+// State of the recurrence after <rt, r> and |r|^2: 0 go on, 1 converged, 2 breakdown or NaN.
+WCL_D int bicg_stop(const double v[3], const Scalars &sc)
+{
+    if (!(v[2] <= sc.stop2 * sc.b2) && !(v[2] >= 0.0)) return 2;   // NaN
+    if (v[2] <= sc.stop2 * sc.b2) return 1;
+    return ((sc.omega[0] == 0.0 && sc.omega[1] == 0.0) || (v[0] == 0.0 && v[1] == 0.0)) ? 2 : 0;
+}
+
+// The sums k_finalize forms (512 threads, thread by thread, then wave by
+// wave), by a workgroup of 256 in every thread, bitwise the same: each thread
+// stands for two of those.
+template <int NT>
+WCL_D void fold_sums(const FoldArgs &f, int rhs, double *lds /* [NT][8] */, double v[NT])
+{
+    const double *p = f.partials + (size_t)rhs * 6 * f.pstride;
+    double a[NT], b[NT];
+#pragma unroll
+    for (int k = 0; k < NT; k++) a[k] = b[k] = 0.0;
+    for (int j = threadIdx.x; j < f.nparts; j += 512) {
+        const bool two = j + 256 < f.nparts;
+#pragma unroll
+        for (int k = 0; k < NT; k++) {
+            a[k] += p[k * f.pstride + j];
+            b[k] += two ? p[k * f.pstride + j + 256] : 0.0;
+        }
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NT; k++) {
+        a[k] = wave_sum(a[k]);
+        b[k] = wave_sum(b[k]);
+        if (lane == 0) {
+            lds[k * 8 + wid] = a[k];
+            lds[k * 8 + 4 + wid] = b[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NT; k++) v[k] = row_sum((lane & 15) < 8 ? lds[k * 8 + (lane & 7)] : 0.0);
+}
+
 // One workgroup per right-hand side.  gate (optional): a right-hand side
 // whose gate scalars are done is marked done at BICG_INIT_RHO.
 __global__ void __launch_bounds__(512) k_finalize(int step, int nterms, const double *partials_all, Scalars *sc_all,
@@ -472,7 +523,8 @@ __global__ void __launch_bounds__(512) k_finalize(int step, int nterms, const do
     const int rhs = blockIdx.x;
     Scalars *sc = sc_all + rhs;
     const double *partials = partials_all + (size_t)rhs * 6 * pstride;
-    if (sc->done && (step == BICG_ALPHA || step == BICG_OMEGA || step == BICG_RHO)) return;
+    const Scalars in = *sc;   // read together with the partials, not after them
+    if (in.done && (step == BICG_ALPHA || step == BICG_OMEGA || step == BICG_RHO)) return;
     __shared__ double lds[6 * 16];
     double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     // each thread adds partials j = tid, tid + 512, ... in that order; eight of
@@ -505,30 +557,27 @@ __global__ void __launch_bounds__(512) k_finalize(int step, int nterms, const do
         sc->alpha[0] = 1.0; sc->alpha[1] = 0.0;
         sc->omega[0] = 1.0; sc->omega[1] = 0.0;
         sc->iter = 0;
+        sc->fresh = 1;
         sc->done = (v[2] == 0.0) ? 1 : 0;
         if (gate && gate[rhs].done) sc->done = 1;
         break;
     case BICG_ALPHA: {
         const double d[2] = {v[0], v[1]};
         if (d[0] == 0.0 && d[1] == 0.0) { sc->done = 2; break; }
-        cdiv(sc->rho, d, sc->alpha);
+        cdiv(in.rho, d, sc->alpha);
         break;
     }
-    case BICG_OMEGA: {
+    case BICG_OMEGA:
         // pairs (t, s), (t, t)
-        const double tt = v[2];
-        if (tt == 0.0) { sc->omega[0] = 0.0; sc->omega[1] = 0.0; }
-        else { sc->omega[0] = v[0] / tt; sc->omega[1] = v[1] / tt; }
+        bicg_omega(v, sc->omega);
         break;
-    }
     case BICG_RHO:
-        sc->rho_old[0] = sc->rho[0]; sc->rho_old[1] = sc->rho[1];
+        sc->rho_old[0] = in.rho[0]; sc->rho_old[1] = in.rho[1];
         sc->rho[0] = v[0]; sc->rho[1] = v[1];
         sc->r2 = v[2];
-        sc->iter += 1;
-        if (!(v[2] <= sc->stop2 * sc->b2) && !(v[2] >= 0.0)) sc->done = 2;     // NaN
-        else if (v[2] <= sc->stop2 * sc->b2) sc->done = 1;
-        else if ((sc->omega[0] == 0.0 && sc->omega[1] == 0.0) || (v[0] == 0.0 && v[1] == 0.0)) sc->done = 2;
+        sc->iter = in.iter + 1;
+        sc->fresh = 1;
+        if (const int d = bicg_stop(v, in)) sc->done = d;
         break;
     case NORM_ONLY:
         sc->t[0] = v[0];
@@ -548,22 +597,49 @@ hipError_t launch_finalize(int step, int nterms, const double *partials, Scalars
 
 // ---------------------------------------------------------------------------
 // BiCGStab vector updates (complex scalars from the device), blockIdx.y = rhs.
-template <typename T>
+// FOLD: the finaliser's step before the update is done here by every workgroup
+// from the partials (f), and workgroup 0 of each right-hand side stores the
+// scalars.  What it stores is read by later launches only, or (done) says to
+// every reader what its own sums say: p's new rho waits in t[4..5] until the s
+// update, which reads it, puts it in rho.  fresh: the scalars are complete
+// (start, or an explicit BICG_RHO step), nothing to fold.
+template <typename T, bool FOLD>
 __global__ void __launch_bounds__(256) k_bicg_p(size_t n, size_t stride, const typename CT<T>::V *r,
-                                               typename CT<T>::V *p, const typename CT<T>::V *v, const Scalars *sc_all)
+                                               typename CT<T>::V *p, const typename CT<T>::V *v, Scalars *sc_all,
+                                               FoldArgs f)
 {
-    const Scalars *sc = sc_all + blockIdx.y;
-    if (sc->done) return;
+    Scalars *sc = sc_all + blockIdx.y;
+    const Scalars in = *sc;
+    if (in.done) return;
     const size_t off = blockIdx.y * stride;
     r += off; p += off; v += off;
+    double rho[2] = {in.rho[0], in.rho[1]}, rho_old[2] = {in.rho_old[0], in.rho_old[1]};
+    if constexpr (FOLD) {
+        __shared__ double lds[3 * 8];
+        const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+        if (!in.fresh) {   // the BICG_RHO step
+            double s[3];
+            fold_sums<3>(f, blockIdx.y, lds, s);
+            const int stop = bicg_stop(s, in);
+            rho_old[0] = in.rho[0]; rho_old[1] = in.rho[1];
+            rho[0] = s[0]; rho[1] = s[1];
+            if (first) {
+                sc->r2 = s[2];
+                sc->iter = in.iter + 1;
+                if (stop) sc->done = stop;
+            }
+            if (stop) return;
+        }
+        if (first) { sc->t[4] = rho[0]; sc->t[5] = rho[1]; }
+    }
     // beta = (rho / rho_old) (alpha / omega)
     double q1[2], q2[2], beta[2];
-    cdiv(sc->rho, sc->rho_old, q1);
-    cdiv(sc->alpha, sc->omega, q2);
+    cdiv(rho, rho_old, q1);
+    cdiv(in.alpha, in.omega, q2);
     beta[0] = q1[0] * q2[0] - q1[1] * q2[1];
     beta[1] = q1[0] * q2[1] + q1[1] * q2[0];
     using C = typename CT<T>::C;
-    const C br = (C)beta[0], bi = (C)beta[1], wr = (C)sc->omega[0], wi = (C)sc->omega[1];
+    const C br = (C)beta[0], bi = (C)beta[1], wr = (C)in.omega[0], wi = (C)in.omega[1];
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const auto pv = ldv(p[i]), vv = ldv(v[i]), rv = ldv(r[i]);
         // d = p - omega v
@@ -573,16 +649,35 @@ __global__ void __launch_bounds__(256) k_bicg_p(size_t n, size_t stride, const t
     }
 }
 
-template <typename T>
+template <typename T, bool FOLD>
 __global__ void __launch_bounds__(256) k_bicg_s(size_t n, size_t stride, const typename CT<T>::V *r,
-                                               const typename CT<T>::V *v, typename CT<T>::V *s, const Scalars *sc_all)
+                                               const typename CT<T>::V *v, typename CT<T>::V *s, Scalars *sc_all,
+                                               FoldArgs f)
 {
-    const Scalars *sc = sc_all + blockIdx.y;
-    if (sc->done) return;
+    Scalars *sc = sc_all + blockIdx.y;
+    const Scalars in = *sc;
+    if (in.done) return;
     const size_t off = blockIdx.y * stride;
     r += off; v += off; s += off;
+    double alpha[2] = {in.alpha[0], in.alpha[1]};
+    if constexpr (FOLD) {   // the BICG_ALPHA step
+        __shared__ double lds[2 * 8];
+        const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+        double d[2];
+        fold_sums<2>(f, blockIdx.y, lds, d);
+        if (first) {
+            sc->rho[0] = in.t[4]; sc->rho[1] = in.t[5];
+            sc->fresh = 0;
+        }
+        if (d[0] == 0.0 && d[1] == 0.0) {
+            if (first) sc->done = 2;
+            return;
+        }
+        cdiv(in.t + 4, d, alpha);
+        if (first) { sc->alpha[0] = alpha[0]; sc->alpha[1] = alpha[1]; }
+    }
     using C = typename CT<T>::C;
-    const C ar = (C)sc->alpha[0], ai = (C)sc->alpha[1];
+    const C ar = (C)alpha[0], ai = (C)alpha[1];
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const auto rv = ldv(r[i]), vv = ldv(v[i]);
         stv(s[i], rv.x - (ar * vv.x - ai * vv.y), rv.y - (ar * vv.y + ai * vv.x));
@@ -612,20 +707,29 @@ __global__ void __launch_bounds__(256) k_bicg_xr(size_t n, size_t stride, typena
 // x += alpha ph + omega sh; r = s - omega t, with the partials of <rt, r>
 // and <r, r> (of the stored r) per workgroup: terms 0, 1 = Re, Im <rt, r>,
 // 2 = <r, r>, 3 = 0 at partials[rhs][k][block] (stride pstride).
-template <typename T>
+template <typename T, bool FOLD>
 __global__ void __launch_bounds__(256) k_bicg_xr_dots(size_t n, size_t stride, typename CT<T>::V *x,
                                                      const typename CT<T>::V *ph, const typename CT<T>::V *sh,
                                                      typename CT<T>::V *r, const typename CT<T>::V *s,
                                                      const typename CT<T>::V *t, const typename CT<T>::V *rt,
-                                                     const Scalars *sc_all, double *partials, int pstride)
+                                                     Scalars *sc_all, double *partials, int pstride, FoldArgs f)
 {
-    const Scalars *sc = sc_all + blockIdx.y;
-    if (sc->done) return;
+    Scalars *sc = sc_all + blockIdx.y;
+    const Scalars in = *sc;
+    if (in.done) return;
     __shared__ double lds[4 * 16];
     const size_t off = blockIdx.y * stride;
     x += off; ph += off; sh += off; r += off; s += off; t += off; rt += off;
+    double omega[2] = {in.omega[0], in.omega[1]};
+    if constexpr (FOLD) {   // the BICG_OMEGA step
+        __shared__ double fl[3 * 8];
+        double d[3];
+        fold_sums<3>(f, blockIdx.y, fl, d);
+        bicg_omega(d, omega);
+        if (blockIdx.x == 0 && threadIdx.x == 0) { sc->omega[0] = omega[0]; sc->omega[1] = omega[1]; }
+    }
     using C = typename CT<T>::C;
-    const C ar = (C)sc->alpha[0], ai = (C)sc->alpha[1], wr = (C)sc->omega[0], wi = (C)sc->omega[1];
+    const C ar = (C)in.alpha[0], ai = (C)in.alpha[1], wr = (C)omega[0], wi = (C)omega[1];
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const auto xv = ldv(x[i]), pv = ldv(ph[i]), sv = ldv(sh[i]), s2 = ldv(s[i]), tv = ldv(t[i]);
@@ -674,17 +778,31 @@ static dim3 blas_grid(size_t n, int nrhs = 1)
 #define WCL_V(x) ((typename CT<T>::V *)(x))
 #define WCL_CV(x) ((const typename CT<T>::V *)(x))
 
-hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, const Scalars *sc,
-                         hipStream_t st, int nrhs, size_t stride)
+// Grid of a vector update that folds a finaliser step: one round of workgroups
+// over the chip (each adds the partials again, once).
+static dim3 fold_grid(size_t n, int nrhs)
 {
-    WCL_BY_PREC((k_bicg_p<T><<<blas_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_V(p), WCL_CV(v), sc)));
+    dim3 g = blas_grid(n, nrhs);
+    const unsigned cap = (unsigned)std::max(64, 2048 / nrhs);
+    if (g.x > cap) g.x = cap;
+    return g;
+}
+
+int bicg_parts(size_t n, int nrhs) { return (int)std::min(fold_grid(n, nrhs).x, (unsigned)RED_BLOCKS); }
+
+hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, Scalars *sc, hipStream_t st, int nrhs,
+                         size_t stride, const FoldArgs *f)
+{
+    if (f) WCL_BY_PREC((k_bicg_p<T, true><<<fold_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_V(p), WCL_CV(v), sc, *f)));
+    else WCL_BY_PREC((k_bicg_p<T, false><<<blas_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_V(p), WCL_CV(v), sc, FoldArgs{})));
     return hipGetLastError();
 }
 
-hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, const Scalars *sc,
-                         hipStream_t st, int nrhs, size_t stride)
+hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, Scalars *sc, hipStream_t st, int nrhs,
+                         size_t stride, const FoldArgs *f)
 {
-    WCL_BY_PREC((k_bicg_s<T><<<blas_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_CV(v), WCL_V(s), sc)));
+    if (f) WCL_BY_PREC((k_bicg_s<T, true><<<fold_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_CV(v), WCL_V(s), sc, *f)));
+    else WCL_BY_PREC((k_bicg_s<T, false><<<blas_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_CV(r), WCL_CV(v), WCL_V(s), sc, FoldArgs{})));
     return hipGetLastError();
 }
 
@@ -697,18 +815,21 @@ hipError_t launch_bicg_xr(int prec, size_t n, void *x, const void *ph, const voi
 }
 
 hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
-                               const void *s, const void *t, const void *rt, const Scalars *sc, hipStream_t st,
-                               int nrhs, size_t stride, double *partials, int pstride, int *nparts)
+                               const void *s, const void *t, const void *rt, Scalars *sc, hipStream_t st,
+                               int nrhs, size_t stride, double *partials, int pstride, int *nparts, const FoldArgs *f)
 {
-    // at most RED_BLOCKS workgroups per right-hand side, so that the finaliser
-    // adds few partials
-    dim3 grid = blas_grid(n, nrhs);
+    // at most RED_BLOCKS workgroups per right-hand side, so that the next
+    // step adds few partials
+    dim3 grid = f ? fold_grid(n, nrhs) : blas_grid(n, nrhs);
     if (grid.x > (unsigned)RED_BLOCKS) grid.x = RED_BLOCKS;
     if ((int)grid.x > pstride) return hipErrorInvalidValue;
     *nparts = (int)grid.x;
-    WCL_BY_PREC((k_bicg_xr_dots<T><<<grid, 256, 0, st>>>(n, stride, WCL_V(x), WCL_CV(ph), WCL_CV(sh), WCL_V(r),
-                                                          WCL_CV(s), WCL_CV(t), WCL_CV(rt), sc, partials,
-                                                          pstride)));
+#define WCL_XR(FOLD, F)                                                                                             \
+    WCL_BY_PREC((k_bicg_xr_dots<T, FOLD><<<grid, 256, 0, st>>>(n, stride, WCL_V(x), WCL_CV(ph), WCL_CV(sh), WCL_V(r), \
+                                                               WCL_CV(s), WCL_CV(t), WCL_CV(rt), sc, partials, pstride, F)))
+    if (f) WCL_XR(true, *f);
+    else WCL_XR(false, FoldArgs{});
+#undef WCL_XR
     return hipGetLastError();
 }
 

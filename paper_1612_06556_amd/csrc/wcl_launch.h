@@ -159,7 +159,8 @@ struct Scalars {
     double t[8];                 // spare scalars for reductions
     int done;                    // 1 converged, 2 breakdown
     int iter;
-    int pad[2];
+    int fresh;                   // rho, r2 and iter are complete (no BICG_RHO step pending)
+    int pad;
 };
 
 // dot partials: for each (a_k, b_k) pair listed, sum conj(a_k) b_k, per
@@ -183,12 +184,24 @@ hipError_t launch_finalize(int step, int nterms, const double *partials, Scalars
                            int nrhs = 1, const Scalars *gate = nullptr, int pstride = RED_BLOCKS,
                            int nparts = RED_BLOCKS);
 
+// A finaliser step done by the vector update that needs its result, from the
+// partials [nrhs][6][pstride] (nparts per term) of the launch before it:
+// BICG_RHO in p, BICG_ALPHA in s, BICG_OMEGA in the x, r update; all three of an
+// iteration or none.  BICG_RHO of the last iteration queued is launched by
+// itself before the host reads the scalars.  The x, r update's own partials go
+// to another buffer than the one it folds.
+struct FoldArgs {
+    const double *partials;
+    int pstride, nparts;
+};
+// partials per term of launch_bicg_xr_dots when it folds
+int bicg_parts(size_t n, int nrhs);
 // p = r + beta (p - omega v), beta = (rho/rho_old)(alpha/omega)
-hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, const Scalars *sc,
-                         hipStream_t st, int nrhs = 1, size_t stride = 0);
+hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, Scalars *sc,
+                         hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
 // s = r - alpha v
-hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, const Scalars *sc,
-                         hipStream_t st, int nrhs = 1, size_t stride = 0);
+hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, Scalars *sc,
+                         hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
 // x += alpha ph + omega sh ; r = s - omega t
 hipError_t launch_bicg_xr(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
                           const void *s, const void *t, const Scalars *sc, hipStream_t st, int nrhs = 1,
@@ -197,8 +210,9 @@ hipError_t launch_bicg_xr(int prec, size_t n, void *x, const void *ph, const voi
 // the same with the partials of <rt, r>, <r, r> of the new r per workgroup
 // (terms 0..3 as for BICG_RHO); *nparts receives the workgroup count.
 hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
-                               const void *s, const void *t, const void *rt, const Scalars *sc, hipStream_t st,
-                               int nrhs, size_t stride, double *partials, int pstride, int *nparts);
+                               const void *s, const void *t, const void *rt, Scalars *sc, hipStream_t st,
+                               int nrhs, size_t stride, double *partials, int pstride, int *nparts,
+                               const FoldArgs *f = nullptr);
 
 // Generic complex axpby: y = a x + b y, a and b host constants.
 hipError_t launch_axpby(int prec, size_t n, double2 a, const void *x, double2 b, void *y, hipStream_t st);

@@ -1,0 +1,66 @@
+"""BiCGStab with the scalar steps folded into the vector updates (up to 1024
+partial sums a term) and as launches of their own (more): right-hand sides
+that stop at different iterations, at once (zero) and by breakdown."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import rel, require_gpu, setup, to_gpu, to_host
+from paper_1612_06556_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+_refs = {}
+
+
+def _reference(orc, b, key):
+    if key not in _refs:
+        _refs[key] = orc.bicgstab_eo(b, 1e-13, 20000)[0]
+    return _refs[key]
+
+
+# half-sites / block: 2048 / 256 = 8 partials; 1024 (the last folded); 1040 (the first that is not)
+@pytest.mark.parametrize("dims,block", [((8, 8, 8, 8), 256), ((16, 16, 16, 32), 64), ((20, 16, 16, 26), 64)])
+@pytest.mark.parametrize("kw", [dict(outer=3, max_outer=2000), dict(use_ras=0, inner_tol=0.1),
+                                dict(use_ras=0, inner_tol=0.1, inner_prec=16, inner_vec_prec=16, use_graph=1)])
+def test_solves_either_side_of_the_fold(dims, block, kw):
+    """x within 1e-8 of the oracle's 1e-13 solution, true residual <= 1e-10; the
+    zero right-hand side returns zero, and each is what it is alone (1e-9: the
+    vector updates of a batch add their sums over other workgroups)."""
+    from paper_1612_06556_amd import wcl
+    lat, orc, _ = setup(dims, -1, 0.115, 1.0, 61, None)
+    wcl.wcl_set_tuning(lat.h, block, 2, 1, 0)
+    b = synth.gaussian_spinor(dims, 62, 3)
+    b[1] = 0.0
+    b[2] = 0.0
+    b[2, 5, 1, 2] = 1.0
+    x, info, rc = lat.solve(to_gpu(b), tol=1e-10, **kw)
+    assert rc == 0 and all(i["status"] == 0 for i in info)
+    x = to_host(x)
+    assert not x[1].any()
+    for k in (0, 2):
+        ref = _reference(orc, b[k], (dims, k))
+        assert np.linalg.norm(b[k] - orc.D(x[k])) <= 1e-10 * np.linalg.norm(b[k])
+        assert rel(x[k], ref) <= 1e-8
+        one, _, _ = lat.solve(to_gpu(b[k]), tol=1e-10, **kw)
+        print(dims, block, kw, k, info[k]["outer_iters"], info[k]["inner_iters_total"], rel(to_host(one), x[k]), flush=True)
+        assert rel(to_host(one), x[k]) <= 1e-9
+    wcl.wcl_set_tuning(lat.h, 256, 2, 1, 0)
+
+
+def test_iteration_limits_inside_a_chunk():
+    """max_outer not a multiple of the queue length: the iterate and count are
+    those of that many iterations, however the checks fall."""
+    from paper_1612_06556_amd import wcl
+    dims = (8, 8, 8, 8)
+    lat, _, _ = setup(dims, -1, 0.12, 1.0, 1001, None)
+    b = to_gpu(synth.gaussian_spinor(dims, 63))
+    for limit in (1, 3, 7):
+        got = []
+        for every in (1, 2, 5, 8):
+            x, info, rc = lat.solve(b, raise_on_error=False, tol=1e-12, outer=wcl.OUTER_PLAIN64_EO, max_outer=limit,
+                                    check_every=every)
+            assert rc == wcl.WCL_ENOCONV and info["outer_iters"] == limit
+            got.append(to_host(x))
+        assert all(np.array_equal(g, got[0]) for g in got)
