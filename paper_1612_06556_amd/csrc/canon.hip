@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(2 * NP) k_canon(CanonArgs a)
 // between right-hand sides) to canonical spinors: neighbours at 16-byte words
 // a lane instead of 192 bytes of the canonical vector.
 template <typename SL, int K, int SG, typename R, typename SS>
-WCL_D void eo_hops(const CanonArgs &a, const char *in, const Site &s, uint32_t p, uint32_t h, HopStage<SL, R> st[2],
+WCL_D void eo_hops(const CanonArgs &a, const char *in, const Site &s, uint32_t p, uint32_t h, HopStage<SL, SS, R> st[2],
                    cplx<R> acc[12])
 {
     // hop_load and hop_compute of the even/odd kernel, unstaged
@@ -439,7 +439,7 @@ WCL_D void eo_hops(const CanonArgs &a, const char *in, const Site &s, uint32_t p
         q.p = (int)p;
         const LdsIn none{};
         if constexpr (K + 1 < 8) hop_load<SL, SS, K + 1, false, 0, R>(q, s, h, in, none, st[(K + 1) & 1], acc);
-        hop_compute<K, SG, SL, R>(st[K & 1], acc);
+        hop_compute<K, SG, SL, SS, R>(st[K & 1], acc);
         eo_hops<SL, K + 1, SG, R, SS>(a, in, s, p, h, st, acc);
     }
 }
@@ -468,7 +468,7 @@ __global__ void __launch_bounds__(256) k_eo_canon(CanonArgs a, const char *eo, s
         q.g = a.g;
         q.links = a.links;
         q.p = (int)p;
-        HopStage<SL, R> st[2];
+        HopStage<SL, SS, R> st[2];
         hop_load<SL, SS, 0, false, 0, R>(q, s, h, other, LdsIn{}, st[0], acc);
         eo_hops<SL, 0, DAG ? -1 : 1, R, SS>(a, other, s, p, h, st, acc);
         if constexpr (MODE == HOP) {

@@ -31,12 +31,80 @@ struct HopArgs {
 // link of hop k+1 are in flight while hop k is computed; a scheduling barrier
 // after each hop keeps the compiler from hoisting further loads (which would
 // raise the register count and lower the occupancy).
-template <typename SL, typename R>
-struct HopStage {
+// The neighbour spinor stays as loaded too where it is FP16: 12 registers, and
+// the projection reads the halves directly (project_raw): 16% fewer vector
+// instructions, 12 sources at 16^3x32 in the FP16 tier 45.7 -> 44.0 ms a solve.
+template <typename SS, typename R>
+struct SpinRaw {
     cplx<R> psi[12];
+};
+template <typename R>
+struct SpinRaw<__half, R> {
+    uint32_t w[12];   // complex i: re in the low half, im in the high one
+};
+template <typename SL, typename SS, typename R>
+struct HopStage {
+    SpinRaw<SS, R> psi;
     LinkRaw<SL> u;   // as loaded; decoded when the hop is computed
     R sign;
 };
+
+template <typename SS, typename R>
+WCL_D void load_spinor_raw(const void *base, uint32_t h, uint32_t Vh, SpinRaw<SS, R> &r)
+{
+    if constexpr (sizeof(SS) == 2) {
+#pragma unroll
+        for (uint32_t k = 0; k < 3; k++) {
+            const uint4 u = ldf<uint4>(base, (k * Vh + h) * 16u);
+            r.w[4 * k] = u.x; r.w[4 * k + 1] = u.y; r.w[4 * k + 2] = u.z; r.w[4 * k + 3] = u.w;
+        }
+    } else {
+        load_spinor<SS, R>(base, h, Vh, r.psi);
+    }
+}
+
+// up + lo of two FP16 numbers in FP32 (UH, LH: the high half; NEG: up - lo):
+// the conversions of both and the addition in one instruction, rounded once as
+// the FP32 addition is (the product with 1 is exact).
+template <int UH, int LH, bool NEG>
+WCL_D float half_add(uint32_t up, uint32_t lo)
+{
+    float d;
+    if constexpr (UH == 0 && LH == 0 && !NEG) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (UH == 0 && LH == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (UH == 0 && !NEG) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (UH == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (LH == 0 && !NEG) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (LH == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else if constexpr (!NEG) asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(up), "v"(lo));
+    return d;
+}
+
+// up + i^CODE lo
+template <int CODE>
+WCL_D cplx<float> half_add_unit(uint32_t up, uint32_t lo)
+{
+    if constexpr ((CODE & 3) == 0) return {half_add<0, 0, false>(up, lo), half_add<1, 1, false>(up, lo)};
+    else if constexpr ((CODE & 3) == 1) return {half_add<0, 1, true>(up, lo), half_add<1, 0, false>(up, lo)};
+    else if constexpr ((CODE & 3) == 2) return {half_add<0, 0, true>(up, lo), half_add<1, 1, true>(up, lo)};
+    else return {half_add<0, 1, false>(up, lo), half_add<1, 0, true>(up, lo)};
+}
+
+// project of a spinor as loaded
+template <int MU, int S, typename SS, typename R>
+WCL_D void project_raw(const SpinRaw<SS, R> &r, cplx<R> h[6])
+{
+    if constexpr (sizeof(SS) == 2) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            h[c] = half_add_unit<gcode(MU, 0) + (S < 0 ? 2 : 0)>(r.w[c], r.w[(2 + gcol(MU, 0)) * 3 + c]);
+            h[3 + c] = half_add_unit<gcode(MU, 1) + (S < 0 ? 2 : 0)>(r.w[3 + c], r.w[(2 + gcol(MU, 1)) * 3 + c]);
+        }
+    } else {
+        project<MU, S, R>(r.psi, h);
+    }
+}
 
 // hop K: direction MU = K/2, forward (K even) or backward (K odd)
 // The load offsets of hop K pass through an empty asm that also "rewrites"
@@ -65,38 +133,34 @@ struct LdsIn {
 };
 
 // A spinor from the LDS copy of the tile (same word layout as the field).
-template <typename S, int NS, typename R>
-WCL_D void lds_spinor(lds_u4p s, uint32_t l, cplx<R> v[12])
+template <typename SS, int NS, typename R>
+WCL_D void lds_spinor(lds_u4p s, uint32_t l, SpinRaw<SS, R> &r)
 {
-    if constexpr (sizeof(S) == 8) {
+    if constexpr (sizeof(SS) == 8) {
 #pragma unroll
         for (uint32_t i = 0; i < 12; i++) {
             const u32x4 u = s[i * NS + l];
-            v[i] = {(R)__hiloint2double(u.y, u.x), (R)__hiloint2double(u.w, u.z)};
+            r.psi[i] = {(R)__hiloint2double(u.y, u.x), (R)__hiloint2double(u.w, u.z)};
         }
-    } else if constexpr (sizeof(S) == 4) {
+    } else if constexpr (sizeof(SS) == 4) {
 #pragma unroll
         for (uint32_t k = 0; k < 6; k++) {
             const u32x4 u = s[k * NS + l];
-            v[2 * k] = {(R)__uint_as_float(u.x), (R)__uint_as_float(u.y)};
-            v[2 * k + 1] = {(R)__uint_as_float(u.z), (R)__uint_as_float(u.w)};
+            r.psi[2 * k] = {(R)__uint_as_float(u.x), (R)__uint_as_float(u.y)};
+            r.psi[2 * k + 1] = {(R)__uint_as_float(u.z), (R)__uint_as_float(u.w)};
         }
     } else {
 #pragma unroll
         for (uint32_t k = 0; k < 3; k++) {
             const u32x4 u = s[k * NS + l];
-            float2 a = h2f2(u.x), b = h2f2(u.y), c = h2f2(u.z), d = h2f2(u.w);
-            v[4 * k + 0] = {(R)a.x, (R)a.y};
-            v[4 * k + 1] = {(R)b.x, (R)b.y};
-            v[4 * k + 2] = {(R)c.x, (R)c.y};
-            v[4 * k + 3] = {(R)d.x, (R)d.y};
+            r.w[4 * k] = u.x; r.w[4 * k + 1] = u.y; r.w[4 * k + 2] = u.z; r.w[4 * k + 3] = u.w;
         }
     }
 }
 
 template <typename SL, typename SS, int K, bool NT, int NS, typename R>
 WCL_D void hop_load(const HopArgs &a, const Site &s, uint32_t h0, const char *in, const LdsIn &li,
-                    HopStage<SL, R> &st, cplx<R> acc[12])
+                    HopStage<SL, SS, R> &st, cplx<R> acc[12])
 {
     constexpr int MU = K >> 1;
     constexpr bool FWD = (K & 1) == 0;
@@ -108,9 +172,9 @@ WCL_D void hop_load(const HopArgs &a, const Site &s, uint32_t h0, const char *in
     if constexpr (NS > 0) {
         const uint32_t l = hn - li.base;
         if (l < (uint32_t)NS) lds_spinor<SS, NS, R>(li.s, l, st.psi);
-        else load_spinor<SS, R>(in, hn, Vh, st.psi);
+        else load_spinor_raw<SS, R>(in, hn, Vh, st.psi);
     } else {
-        load_spinor<SS, R>(in, hn, Vh, st.psi);
+        load_spinor_raw<SS, R>(in, hn, Vh, st.psi);
     }
     if (FWD) load_link_raw<SL, NT>(a.links, MU, a.p, h, Vh, st.u);
     else load_link_raw<SL, NT>(a.links, MU, 1 - a.p, hn, Vh, st.u);
@@ -119,14 +183,14 @@ WCL_D void hop_load(const HopArgs &a, const Site &s, uint32_t h0, const char *in
 }
 
 // forward: (1 - SG g_mu) U_mu(x) psi(x+mu);  backward: (1 + SG g_mu) U_mu(x-mu)^dag psi(x-mu)
-template <int K, int SG, typename SL, typename R>
-WCL_D void hop_compute(const HopStage<SL, R> &st, cplx<R> acc[12])
+template <int K, int SG, typename SL, typename SS, typename R>
+WCL_D void hop_compute(const HopStage<SL, SS, R> &st, cplx<R> acc[12])
 {
     constexpr int MU = K >> 1;
     constexpr bool FWD = (K & 1) == 0;
     constexpr int S = FWD ? -SG : SG;
     cplx<R> hh[6], uh[6], u[9];
-    project<MU, S, R>(st.psi, hh);
+    project_raw<MU, S, SS, R>(st.psi, hh);
 #pragma unroll
     for (int k = 0; k < 6; k++) hh[k] = st.sign * hh[k];
     expand_link<SL, R>(st.u, u);
@@ -137,7 +201,7 @@ WCL_D void hop_compute(const HopStage<SL, R> &st, cplx<R> acc[12])
 
 template <typename SL, typename SS, int SG, int D, int K, bool NT, int NS, typename R>
 WCL_D void hop_prologue(const HopArgs &a, const Site &s, uint32_t h, const char *in, const LdsIn &li,
-                        HopStage<SL, R> st[D], cplx<R> acc[12])
+                        HopStage<SL, SS, R> st[D], cplx<R> acc[12])
 {
     if constexpr (K < D - 1) {
         hop_load<SL, SS, K, NT, NS, R>(a, s, h, in, li, st[K], acc);
@@ -148,12 +212,12 @@ WCL_D void hop_prologue(const HopArgs &a, const Site &s, uint32_t h, const char 
 // hop K is computed while the operands of hop K + D - 1 are in flight
 template <typename SL, typename SS, int SG, int D, int K, bool NT, int NS, typename R>
 WCL_D void hop_pipeline(const HopArgs &a, const Site &s, uint32_t h, const char *in, const LdsIn &li,
-                        HopStage<SL, R> st[D], cplx<R> acc[12])
+                        HopStage<SL, SS, R> st[D], cplx<R> acc[12])
 {
     if constexpr (K < 8) {
         if constexpr (K + D - 1 < 8)
             hop_load<SL, SS, K + D - 1, NT, NS, R>(a, s, h, in, li, st[(K + D - 1) % D], acc);
-        hop_compute<K, SG, SL, R>(st[K % D], acc);
+        hop_compute<K, SG, SL, SS, R>(st[K % D], acc);
         hop_pipeline<SL, SS, SG, D, K + 1, NT, NS, R>(a, s, h, in, li, st, acc);
     }
 }
@@ -193,7 +257,7 @@ WCL_D void hop_block(const HopArgs &a, int bid, int rhs, uint4 *sin, const void 
     cplx<R> acc[12];
 #pragma unroll
     for (int i = 0; i < 12; i++) acc[i] = {R(0), R(0)};
-    HopStage<SL, R> st[DEPTH];
+    HopStage<SL, SS, R> st[DEPTH];
     hop_prologue<SL, SS, SG, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
     hop_pipeline<SL, SS, SG, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
 
