@@ -1124,10 +1124,10 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
     const size_t m = 12 * (size_t)c->Vh;   // complex numbers per right-hand side
     const int lp = cfg.lprec, vp = cfg.vprec;
     // the reductions ride in the Schur operator's second half and the x, r
-    // update, except with several right-hand sides per thread
+    // update, the first two not with several right-hand sides per thread
     const bool fused = c->hop_rhs == 1 || n == 1;
-    const bool fold = fused && folds(c, lp);
-    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n)};
+    const bool fold = !fused || folds(c, lp);
+    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n, fold)};
     HIPCHK(launch_bicg_p(vp, m, w.r32, w.p32, w.v32, sc, c->st, n, m, fold ? &rho : nullptr));
     void *ph = w.p32, *sh = w.s32;
     RasLaunch R{};
@@ -1150,16 +1150,15 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
         else CHK(run_ras(c, R));
         ph = w.ph32;
     }
-    int np = 0;
+    int np = RED_BLOCKS;
     if (fused) {
         CHK(schur_dot(c, lp, vp, ph, w.v32, w.o32, sc, n, 1, w.rt32, &np));
-        if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
     } else {
         CHK(schur(c, lp, vp, ph, w.v32, w.o32, sc, n));
         const void *a[1] = {w.rt32}, *b[1] = {w.v32};
         HIPCHK(launch_dots(vp, m, 1, a, b, c->partials, sc, c->st, n, m, c->pstride));
-        HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride));
     }
+    if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
     const FoldArgs alpha{c->partials, c->pstride, np};
     HIPCHK(launch_bicg_s(vp, m, w.r32, w.v32, w.s32, sc, c->st, n, m, fold ? &alpha : nullptr));
     if (cfg.ras) {
@@ -1171,25 +1170,16 @@ int inner_iteration(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, Scalars *sc, in
     }
     if (fused) {
         CHK(schur_dot(c, lp, vp, sh, w.t32, w.o32, sc, n, 2, w.s32, &np));
-        if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
-        const FoldArgs omega{c->partials, c->pstride, np};
-        HIPCHK(launch_bicg_xr_dots(vp, m, w.x32, ph, sh, w.r32, w.s32, w.t32, w.rt32, sc, c->st, n, m, partials2(c),
-                                   c->pstride, &np, fold ? &omega : nullptr));
-        if (!fold) HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, np));
     } else {
         CHK(schur(c, lp, vp, sh, w.t32, w.o32, sc, n));
-        {
-            const void *a[2] = {w.t32, w.t32}, *b[2] = {w.s32, w.t32};
-            HIPCHK(launch_dots(vp, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
-            HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride));
-        }
-        HIPCHK(launch_bicg_xr(vp, m, w.x32, ph, sh, w.r32, w.s32, w.t32, sc, c->st, n, m));
-        {
-            const void *a[2] = {w.rt32, w.r32}, *b[2] = {w.r32, w.r32};
-            HIPCHK(launch_dots(vp, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
-            HIPCHK(launch_finalize(BICG_RHO, 4, c->partials, sc, c->st, n, nullptr, c->pstride));
-        }
+        const void *a[2] = {w.t32, w.t32}, *b[2] = {w.s32, w.t32};
+        HIPCHK(launch_dots(vp, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
     }
+    if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+    const FoldArgs omega{c->partials, c->pstride, np};
+    HIPCHK(launch_bicg_xr_dots(vp, m, w.x32, ph, sh, w.r32, w.s32, w.t32, w.rt32, sc, c->st, n, m, partials2(c),
+                               c->pstride, fold ? &omega : nullptr));
+    if (!fold) HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n, false)));
     return WCL_OK;
 }
 
@@ -1293,7 +1283,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     std::vector<int> it_prev(n, 0);
     std::vector<size_t> rec_mark;  // profile records at the start of each queued iteration
     Scalars *h = HI(c);
-    const bool fold = (c->hop_rhs == 1 || n == 1) && folds(c, cfg.lprec);
+    const bool fold = (c->hop_rhs != 1 && n > 1) || folds(c, cfg.lprec);
     while (launched < cfg.maxit) {
         chunk = std::max(1, std::min(chunk, cfg.maxit - launched));
         if (cfg.graph && !*cfg.exec) {
@@ -1320,7 +1310,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
             else CHK(inner_iteration(c, cfg, w, sc, n));
         }
         if (fold)   // the last iteration's step, before the host reads the scalars
-            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n)));
+            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n, true)));
         launched += chunk;
         CHK(read_sc(c, h, sc, n));
         bool all = true;
@@ -1486,10 +1476,10 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
     int iter = 0;
     const int every = d.flex ? 1 : std::max(1, o.check_every);
     // on the even/odd system the reductions ride in the Schur operator's second
-    // half and the x/r update, as in the inner solver
+    // half; always in the x, r update
     const bool fused = d.eo && (c->hop_rhs == 1 || n == 1);
-    const bool fold = fused && folds(c, P64);
-    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n)};
+    const bool fold = !fused || folds(c, P64);
+    const FoldArgs rho{partials2(c), c->pstride, bicg_parts(m, n, fold)};
     while (iter < o.max_outer) {
         bool any_active = false;
         for (int k = 0; k < n; k++) any_active = any_active || !final_[k];
@@ -1505,16 +1495,15 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
                 for (int k = 0; k < n; k++) info[k].inner_iters_total += final_[k] ? 0 : it_inner[k];
                 ph = w.ph;
             }
-            int np = 0;
+            int np = RED_BLOCKS;
             if (fused) {
                 CHK(schur_dot(c, P64, P64, ph, w.v, w.o, sc, n, 1, w.rt, &np));
-                if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
             } else {
                 CHK(apply_A(c, d, w, ph, w.v, sc));
                 const void *a[1] = {w.rt}, *b[1] = {w.v};
                 HIPCHK(launch_dots(P64, m, 1, a, b, c->partials, sc, c->st, n, m, c->pstride));
-                HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride));
             }
+            if (!fold) HIPCHK(launch_finalize(BICG_ALPHA, 2, c->partials, sc, c->st, n, nullptr, c->pstride, np));
             const FoldArgs alpha{c->partials, c->pstride, np};
             HIPCHK(launch_bicg_s(P64, m, w.r, w.v, w.s, sc, c->st, n, m, fold ? &alpha : nullptr));
             if (d.flex) {
@@ -1524,29 +1513,21 @@ int bicgstab_driver(wcl_ctx *c, const Driver &d, const wcl_solve_opts &o, const 
             }
             if (fused) {
                 CHK(schur_dot(c, P64, P64, sh, w.t, w.o, sc, n, 2, w.s, &np));
-                if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
-                const FoldArgs omega{c->partials, c->pstride, np};
-                HIPCHK(launch_bicg_xr_dots(P64, m, d.x, ph, sh, w.r, w.s, w.t, w.rt, sc, c->st, n, m, partials2(c),
-                                           c->pstride, &np, fold ? &omega : nullptr));
-                if (!fold) HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, np));
             } else {
                 CHK(apply_A(c, d, w, sh, w.t, sc));
-                {
-                    const void *a[2] = {w.t, w.t}, *b[2] = {w.s, w.t};
-                    HIPCHK(launch_dots(P64, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
-                    HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride));
-                }
-                HIPCHK(launch_bicg_xr(P64, m, d.x, ph, sh, w.r, w.s, w.t, sc, c->st, n, m));
-                {
-                    const void *a[2] = {w.rt, w.r}, *b[2] = {w.r, w.r};
-                    HIPCHK(launch_dots(P64, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
-                    HIPCHK(launch_finalize(BICG_RHO, 4, c->partials, sc, c->st, n, nullptr, c->pstride));
-                }
+                const void *a[2] = {w.t, w.t}, *b[2] = {w.s, w.t};
+                HIPCHK(launch_dots(P64, m, 2, a, b, c->partials, sc, c->st, n, m, c->pstride));
             }
+            if (!fold) HIPCHK(launch_finalize(BICG_OMEGA, 4, c->partials, sc, c->st, n, nullptr, c->pstride, np));
+            const FoldArgs omega{c->partials, c->pstride, np};
+            HIPCHK(launch_bicg_xr_dots(P64, m, d.x, ph, sh, w.r, w.s, w.t, w.rt, sc, c->st, n, m, partials2(c),
+                                       c->pstride, fold ? &omega : nullptr));
+            if (!fold)
+                HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n, false)));
         }
         iter += chunk;
         if (fold)   // the last iteration's step, before the host reads the scalars
-            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n)));
+            HIPCHK(launch_finalize(BICG_RHO, 4, partials2(c), sc, c->st, n, nullptr, c->pstride, bicg_parts(m, n, true)));
         CHK(read_sc(c, HO(c), sc, n));
         bool candidates = false;
         int exec = 0;  // iterations of this chunk that did work for some right-hand side

@@ -63,6 +63,26 @@ WCL_D void load_spinor_raw(const void *base, uint32_t h, uint32_t Vh, SpinRaw<SS
     }
 }
 
+// Spins 2 half, 2 half + 1 of an FP64 or FP32 spinor.
+template <typename SS, typename R>
+WCL_D void load_spinor_half(const void *base, uint32_t h, uint32_t Vh, int half, cplx<R> v[6])
+{
+    if constexpr (sizeof(SS) == 8) {
+#pragma unroll
+        for (uint32_t i = 0; i < 6; i++) {
+            const double2 d = ldf<double2>(base, ((6 * half + i) * Vh + h) * 16u);
+            v[i] = {(R)d.x, (R)d.y};
+        }
+    } else {
+#pragma unroll
+        for (uint32_t k = 0; k < 3; k++) {
+            const float4 f = ldf<float4>(base, ((3 * half + k) * Vh + h) * 16u);
+            v[2 * k] = {(R)f.x, (R)f.y};
+            v[2 * k + 1] = {(R)f.z, (R)f.w};
+        }
+    }
+}
+
 // up + lo of two FP16 numbers in FP32 (UH, LH: the high half; NEG: up - lo):
 // the conversions of both and the addition in one instruction, rounded once as
 // the FP32 addition is (the product with 1 is exact).
@@ -266,24 +286,34 @@ WCL_D void hop_block(const HopArgs &a, int bid, int rhs, uint4 *sin, const void 
 #pragma unroll
         for (int i = 0; i < 12; i++) o[i] = acc[i];
     } else {
-        R c[72];
-        load_clover<typename ClovS<SL>::T, R, NT>(a.clov, a.p, h, Vh, c);
-        if constexpr (MODE == CLOV_H) {
-            clover_mul(c, acc, o);
-        } else if constexpr (MODE == XPAY) {
-            cplx<R> xv[12], t[12];
-            load_spinor<SS, R>((const char *)a.x + rhs * a.x_stride, h, Vh, xv);
-            clover_mul(c, acc, t);
-            const R cf = (R)a.coef;
+        // one chirality block at a time: 36 clover reals live, not 72 (FP64 kernels
+        // then fit 256 registers, two waves per SIMD, FP32 ones mostly 128)
+        cplx<R> xv[12];
+        const char *x = (const char *)a.x + rhs * a.x_stride;
+        const R cf = (R)a.coef;
 #pragma unroll
-            for (int i = 0; i < 12; i++) o[i] = {fmar(cf, t[i].re, xv[i].re), fmar(cf, t[i].im, xv[i].im)};
-        } else {
-            cplx<R> xv[12];
-            load_spinor<SS, R>((const char *)a.x + rhs * a.x_stride, h, Vh, xv);
-            clover_mul(c, xv, o);
-            const R cf = (R)a.coef;
+        for (int half = 0; half < 2; half++) {
+            const uint32_t hc = (uint32_t)h;
+            R c[36];
+            load_clover_half<typename ClovS<SL>::T, R, NT>(a.clov, a.p, hc, (uint32_t)Vh, half, c);
+            if constexpr (MODE != CLOV_H) {
+                if constexpr (sizeof(SS) != 2) load_spinor_half<SS, R>(x, hc, (uint32_t)Vh, half, xv + 6 * half);
+                else if (half == 0) load_spinor<SS, R>(x, hc, (uint32_t)Vh, xv);   // 1.5 words a half
+            }
+            cplx<R> *oh = o + 6 * half;
+            const cplx<R> *ah = acc + 6 * half, *xh = xv + 6 * half;
+            if constexpr (MODE == CLOV_H) {
+                clover_mul_half(c, ah, oh);
+            } else if constexpr (MODE == XPAY) {
+                cplx<R> t[6];
+                clover_mul_half(c, ah, t);
 #pragma unroll
-            for (int i = 0; i < 12; i++) o[i] = {fmar(cf, acc[i].re, o[i].re), fmar(cf, acc[i].im, o[i].im)};
+                for (int i = 0; i < 6; i++) oh[i] = {fmar(cf, t[i].re, xh[i].re), fmar(cf, t[i].im, xh[i].im)};
+            } else {
+                clover_mul_half(c, xh, oh);
+#pragma unroll
+                for (int i = 0; i < 6; i++) oh[i] = {fmar(cf, ah[i].re, oh[i].re), fmar(cf, ah[i].im, oh[i].im)};
+            }
         }
     }
     store_spinor<SS, R>(out, h, Vh, o);

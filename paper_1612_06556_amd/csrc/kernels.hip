@@ -684,26 +684,6 @@ __global__ void __launch_bounds__(256) k_bicg_s(size_t n, size_t stride, const t
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_bicg_xr(size_t n, size_t stride, typename CT<T>::V *x,
-                                                const typename CT<T>::V *ph, const typename CT<T>::V *sh,
-                                                typename CT<T>::V *r, const typename CT<T>::V *s,
-                                                const typename CT<T>::V *t, const Scalars *sc_all)
-{
-    const Scalars *sc = sc_all + blockIdx.y;
-    if (sc->done) return;
-    const size_t off = blockIdx.y * stride;
-    x += off; ph += off; sh += off; r += off; s += off; t += off;
-    using C = typename CT<T>::C;
-    const C ar = (C)sc->alpha[0], ai = (C)sc->alpha[1], wr = (C)sc->omega[0], wi = (C)sc->omega[1];
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const auto xv = ldv(x[i]), pv = ldv(ph[i]), sv = ldv(sh[i]), s2 = ldv(s[i]), tv = ldv(t[i]);
-        stv(x[i], xv.x + (ar * pv.x - ai * pv.y) + (wr * sv.x - wi * sv.y),
-            xv.y + (ar * pv.y + ai * pv.x) + (wr * sv.y + wi * sv.x));
-        stv(r[i], s2.x - (wr * tv.x - wi * tv.y), s2.y - (wr * tv.y + wi * tv.x));
-    }
-}
-
 // x += alpha ph + omega sh; r = s - omega t, with the partials of <rt, r>
 // and <r, r> (of the stored r) per workgroup: terms 0, 1 = Re, Im <rt, r>,
 // 2 = <r, r>, 3 = 0 at partials[rhs][k][block] (stride pstride).
@@ -788,7 +768,10 @@ static dim3 fold_grid(size_t n, int nrhs)
     return g;
 }
 
-int bicg_parts(size_t n, int nrhs) { return (int)std::min(fold_grid(n, nrhs).x, (unsigned)RED_BLOCKS); }
+int bicg_parts(size_t n, int nrhs, bool fold)
+{
+    return (int)std::min((fold ? fold_grid(n, nrhs) : blas_grid(n, nrhs)).x, (unsigned)RED_BLOCKS);
+}
 
 hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, Scalars *sc, hipStream_t st, int nrhs,
                          size_t stride, const FoldArgs *f)
@@ -806,24 +789,14 @@ hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void 
     return hipGetLastError();
 }
 
-hipError_t launch_bicg_xr(int prec, size_t n, void *x, const void *ph, const void *sh, void *r, const void *s,
-                          const void *t, const Scalars *sc, hipStream_t st, int nrhs, size_t stride)
-{
-    WCL_BY_PREC((k_bicg_xr<T><<<blas_grid(n, nrhs), 256, 0, st>>>(n, stride, WCL_V(x), WCL_CV(ph), WCL_CV(sh),
-                                                                   WCL_V(r), WCL_CV(s), WCL_CV(t), sc)));
-    return hipGetLastError();
-}
-
 hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
                                const void *s, const void *t, const void *rt, Scalars *sc, hipStream_t st,
-                               int nrhs, size_t stride, double *partials, int pstride, int *nparts, const FoldArgs *f)
+                               int nrhs, size_t stride, double *partials, int pstride, const FoldArgs *f)
 {
     // at most RED_BLOCKS workgroups per right-hand side, so that the next
     // step adds few partials
-    dim3 grid = f ? fold_grid(n, nrhs) : blas_grid(n, nrhs);
-    if (grid.x > (unsigned)RED_BLOCKS) grid.x = RED_BLOCKS;
+    const dim3 grid((unsigned)bicg_parts(n, nrhs, f != nullptr), nrhs);
     if ((int)grid.x > pstride) return hipErrorInvalidValue;
-    *nparts = (int)grid.x;
 #define WCL_XR(FOLD, F)                                                                                             \
     WCL_BY_PREC((k_bicg_xr_dots<T, FOLD><<<grid, 256, 0, st>>>(n, stride, WCL_V(x), WCL_CV(ph), WCL_CV(sh), WCL_V(r), \
                                                                WCL_CV(s), WCL_CV(t), WCL_CV(rt), sc, partials, pstride, F)))

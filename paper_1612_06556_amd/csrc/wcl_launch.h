@@ -194,24 +194,20 @@ struct FoldArgs {
     const double *partials;
     int pstride, nparts;
 };
-// partials per term of launch_bicg_xr_dots when it folds
-int bicg_parts(size_t n, int nrhs);
+// partials per term of launch_bicg_xr_dots
+int bicg_parts(size_t n, int nrhs, bool fold);
 // p = r + beta (p - omega v), beta = (rho/rho_old)(alpha/omega)
 hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, Scalars *sc,
                          hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
 // s = r - alpha v
 hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, Scalars *sc,
                          hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
-// x += alpha ph + omega sh ; r = s - omega t
-hipError_t launch_bicg_xr(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
-                          const void *s, const void *t, const Scalars *sc, hipStream_t st, int nrhs = 1,
-                          size_t stride = 0);
-
-// the same with the partials of <rt, r>, <r, r> of the new r per workgroup
-// (terms 0..3 as for BICG_RHO); *nparts receives the workgroup count.
+// x += alpha ph + omega sh ; r = s - omega t, with the partials of <rt, r>,
+// <r, r> of the new r per workgroup (terms 0..3 as for BICG_RHO; bicg_parts of
+// them a term).
 hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, const void *sh, void *r,
                                const void *s, const void *t, const void *rt, Scalars *sc, hipStream_t st,
-                               int nrhs, size_t stride, double *partials, int pstride, int *nparts,
+                               int nrhs, size_t stride, double *partials, int pstride,
                                const FoldArgs *f = nullptr);
 
 // Generic complex axpby: y = a x + b y, a and b host constants.
