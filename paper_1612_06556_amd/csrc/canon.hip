@@ -141,13 +141,14 @@ WCL_D void stage_pairs(PairLds<SS, NP> &L, const Geom &g, uint32_t h0, uint32_t 
     }
 }
 
-// LDS slots to the canonical pairs; ODD0: the odd sites are written as zero.
-template <typename SS, int NP, bool ODD0>
+// LDS slots to the canonical pairs by T threads; ODD0: the odd sites are
+// written as zero.
+template <typename SS, int NP, bool ODD0, int T = 2 * NP>
 WCL_D void write_pairs(const PairLds<SS, NP> &L, uint32_t np, double2 *canon)
 {
     const uint32_t tid = threadIdx.x;
 #pragma unroll 4
-    for (uint32_t i = tid; i < 24u * NP; i += 2u * NP) {
+    for (uint32_t i = tid; i < 24u * NP; i += (uint32_t)T) {
         const uint32_t pr = i / 24u, c = i - pr * 24u;
         if (pr >= np) break;
         const uint32_t b = L.base[pr];
@@ -310,7 +311,10 @@ WCL_D void canon_load(const CanonArgs &a, const double2 *in, const Site &s, uint
     const uint32_t l = hn - h0;
     const bool near = l < (uint32_t)NP;
     st.slot = near ? (1u - p) * NP + l : CUT;
-    if constexpr (NP == 32) {
+    if constexpr (NP == 0) {   // no region: every neighbour
+#pragma unroll
+        for (uint32_t i = 0; i < 12; i++) st.far[i] = ldf<double2>(in, nn * 192u + i * 16u);
+    } else if constexpr (NP == 32) {
         // few waves, each waiting for its own chain of loads: unconditional loads
         // keep the wait counts exact (out of range, so zero, where the LDS serves)
         const uint32_t off = near ? CUT : nn * 192u;
@@ -322,6 +326,18 @@ WCL_D void canon_load(const CanonArgs &a, const double2 *in, const Site &s, uint
     }
     if (FWD) load_link_raw<SL>(a.links, MU, (int)p, h, g.Vh, st.u);
     else load_link_raw<SL>(a.links, MU, 1 - (int)p, hn, g.Vh, st.u);
+}
+
+// A component of the canonical vector as the tier's fields hold it.
+template <typename SS, typename R>
+WCL_D cplx<R> tier_value(double2 v)
+{
+    if constexpr (sizeof(SS) == 2) {
+        const float2 f = h2f2(f22h((float)v.x, (float)v.y));
+        return {f.x, f.y};
+    } else {
+        return {(R)v.x, (R)v.y};
+    }
 }
 
 template <typename SL, typename SS, int K, int SG, int NP, typename R>
@@ -336,13 +352,7 @@ WCL_D void canon_compute(const CanonArgs &a, const PairLds<SS, NP> &L, const Sit
     get_spinor<SS, R>(L.w, PairLds<SS, NP>::STRIDE, near ? (int)st.slot : 0, psi);
 #pragma unroll
     for (int i = 0; i < 12; i++) {
-        cplx<R> f;
-        if constexpr (sizeof(SS) == 2) {
-            const float2 v = h2f2(f22h((float)st.far[i].x, (float)st.far[i].y));
-            f = {v.x, v.y};
-        } else {
-            f = {(R)st.far[i].x, (R)st.far[i].y};
-        }
+        const cplx<R> f = tier_value<SS, R>(st.far[i]);
         psi[i] = {near ? psi[i].re : f.re, near ? psi[i].im : f.im};
     }
     project<MU, S, R>(psi, hh);
@@ -365,6 +375,33 @@ WCL_D void canon_hops(const CanonArgs &a, const double2 *in, const PairLds<SS, N
         if constexpr (K + 1 < 8) canon_load<SL, K + 1, NP, R>(a, in, s, p, h0, h, n, st[(K + 1) & 1], acc);
         canon_compute<SL, SS, K, SG, NP, R>(a, L, s, st[K & 1], acc);
         canon_hops<SL, SS, K + 1, SG, NP, R>(a, in, L, s, p, h0, h, n, st, acc);
+    }
+}
+
+// The hops of an odd site with every neighbour from the canonical vector.
+template <typename SL, typename SS, int K, typename R>
+WCL_D void canon_hops_direct(const CanonArgs &a, const double2 *in, const Site &s, uint32_t h, uint32_t n,
+                             CanonStage<SL> st[2], cplx<R> acc[12])
+{
+    if constexpr (K < 8) {
+        constexpr int MU = K >> 1;
+        constexpr bool FWD = (K & 1) == 0;
+        constexpr int S = FWD ? -1 : 1;
+        if constexpr (K + 1 < 8) canon_load<SL, K + 1, 0, R>(a, in, s, 1u, 0u, h, n, st[(K + 1) & 1], acc);
+        cplx<R> psi[12], hh[6], uh[6], u[9];
+#pragma unroll
+        for (int i = 0; i < 12; i++) psi[i] = tier_value<SS, R>(st[K & 1].far[i]);
+        project<MU, S, R>(psi, hh);
+        if constexpr (MU == 3) {
+            const R sign = (a.g.tbc < 0 && s.x[3] == (FWD ? a.g.L[3] - 1 : 0)) ? R(-1) : R(1);
+#pragma unroll
+            for (int k = 0; k < 6; k++) hh[k] = sign * hh[k];
+        }
+        expand_link<SL, R>(st[K & 1].u, u);
+        if (FWD) su3_mul(u, hh, uh);
+        else su3_dag_mul(u, hh, uh);
+        accumulate<MU, S, R>(acc, uh);
+        canon_hops_direct<SL, SS, K + 1, R>(a, in, s, h, n, st, acc);
     }
 }
 
@@ -507,6 +544,119 @@ static hipError_t eo_canon_dispatch(const CanonLaunch &L, const CanonArgs &a, hi
     else if (L.mode == CLOVX) ext_launch(k_eo_canon<SL, SS, CLOVX, true>, grid, block, 0, st, L.ev, a, eo, L.eo_stride);
     else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The even/odd operator on small lattices in two launches, canonical to
+// canonical: odd = A_oo^-1 H_oe in_e (an e/o field of the tier), then
+// out_e = in_e + coef A_ee^-1 H_eo odd, out_o = 0.  NP pairs and NP threads a
+// workgroup, one output site each; what pack and unpack launches would do
+// rides along (Schur FP32 on 2 x 12x6x10x14: 16.7 us a call, 27.2 with them).
+// The neighbours of the first come from the canonical vector, 192 bytes each,
+// which large lattices pay for (24^3x32 FP32: 148 against 114 us; even at 16^3x32).
+template <typename SL, typename SS, int NP>
+__global__ void __launch_bounds__(NP) k_schur_odd(CanonArgs a, char *odd, size_t odd_stride)
+{
+    using R = typename Real<SL>::T;
+    const Geom &g = a.g;
+    const uint32_t rhs = blockIdx.x % a.nrhs, h = blockIdx.x / a.nrhs * NP + threadIdx.x;
+    const uint32_t Vh = g.Vh;
+    if (h >= Vh) return;
+    const double2 *in = a.in + (size_t)rhs * 24 * Vh;
+    cplx<R> acc[12], o[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) acc[k] = {R(0), R(0)};
+    const Site s = decompose(g, (int)h, 1);
+    const uint32_t n = (uint32_t)(s.x[0] + g.L[0] * (s.x[1] + g.L[1] * (s.x[2] + g.L[2] * s.x[3])));
+    CanonStage<SL> st[2];
+    canon_load<SL, 0, 0, R>(a, in, s, 1u, 0u, h, n, st[0], acc);
+    canon_hops_direct<SL, SS, 0, R>(a, in, s, h, n, st, acc);
+#pragma unroll
+    for (int half = 0; half < 2; half++) {
+        R c[36];
+        load_clover_half<typename ClovS<SL>::T, R>(a.clov, 1, h, Vh, half, c);
+        clover_mul_half(c, acc + 6 * half, o + 6 * half);
+    }
+    store_spinor<SS, R>(odd + rhs * odd_stride, h, Vh, o);
+}
+
+template <typename SL, typename SS, int NP>
+__global__ void __launch_bounds__(NP) k_schur_even(CanonArgs a, const char *odd, size_t odd_stride)
+{
+    using R = typename Real<SL>::T;
+    __shared__ PairLds<SS, NP> L;
+    const Geom &g = a.g;
+    const uint32_t rhs = blockIdx.x % a.nrhs, h0 = blockIdx.x / a.nrhs * NP, i = threadIdx.x, h = h0 + i;
+    const uint32_t Vh = g.Vh, np = min((uint32_t)NP, Vh - h0);
+    if (i < np) {
+        const uint32_t b = pair_base(g, (int)h);
+        L.base[i] = b;
+        odd += rhs * odd_stride;
+        cplx<R> acc[12], xv[12], o[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) acc[k] = {R(0), R(0)};
+        // the even site's own spinor, rounded to the tier
+        const double2 *x = a.in + (size_t)rhs * 24 * Vh + (size_t)((b & 0x7fffffffu) + (b >> 31)) * 12;
+        double2 xr[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) xr[k] = x[k];
+        const Site s = decompose(g, (int)h, 0);
+        HopArgs q;
+        q.g = a.g;
+        q.links = a.links;
+        q.p = 0;
+        HopStage<SL, SS, R> st[2];
+        hop_load<SL, SS, 0, false, 0, R>(q, s, h, odd, LdsIn{}, st[0], acc);
+        eo_hops<SL, 0, 1, R, SS>(a, odd, s, 0u, h, st, acc);
+        const R cf = (R)a.coef;
+#pragma unroll
+        for (int k = 0; k < 12; k++) xv[k] = tier_value<SS, R>(xr[k]);
+#pragma unroll
+        for (int half = 0; half < 2; half++) {
+            R c[36];
+            cplx<R> t[6];
+            load_clover_half<typename ClovS<SL>::T, R>(a.clov, 0, h, Vh, half, c);
+            clover_mul_half(c, acc + 6 * half, t);
+#pragma unroll
+            for (int k = 0; k < 6; k++)
+                o[6 * half + k] = {fmar(cf, t[k].re, xv[6 * half + k].re), fmar(cf, t[k].im, xv[6 * half + k].im)};
+        }
+        put_spinor<SS, R>(L.w, PairLds<SS, NP>::STRIDE, (int)i, o);
+    }
+    __syncthreads();
+    write_pairs<SS, NP, true, NP>(L, np, a.out + (size_t)rhs * 24 * Vh);
+}
+
+template <typename SL, typename SS>
+static hipError_t schur_canon_dispatch(const CanonLaunch &L, const CanonArgs &a, hipStream_t st)
+{
+    constexpr int NP = 64;
+    dim3 grid(((a.g.Vh + NP - 1) / NP) * a.nrhs), block(NP);
+    if (L.mode == CLOV_H) ext_launch(k_schur_odd<SL, SS, NP>, grid, block, 0, st, L.ev, a, (char *)L.eo, L.eo_stride);
+    else ext_launch(k_schur_even<SL, SS, NP>, grid, block, 0, st, L.ev, a, (const char *)L.eo, L.eo_stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_schur_canon(const CanonLaunch &L, hipStream_t st)
+{
+    CanonArgs a;
+    a.g = *L.g;
+    a.in = (const double2 *)L.in;
+    a.out = (double2 *)L.out;
+    a.links = L.links;
+    a.clov = L.clov;
+    a.coef = L.coef;
+    a.nrhs = L.nrhs;
+    a.xcd = 0;
+    if (L.nrhs < 1 || !L.eo || (L.mode != CLOV_H && L.mode != XPAY)) return hipErrorInvalidValue;
+    switch (L.link_prec) {
+    case P64: return schur_canon_dispatch<double, double>(L, a, st);
+    case P32: return schur_canon_dispatch<float, float>(L, a, st);
+    case P16: return schur_canon_dispatch<__half, __half>(L, a, st);
+    case P32C: return schur_canon_dispatch<R12f, float>(L, a, st);
+    case P16C: return schur_canon_dispatch<R12h, __half>(L, a, st);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename SL, typename SS>

@@ -960,6 +960,34 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             HIPCHK(launch_unpack(c->g, P64, true, b, hb, outk, n, c->st));
             continue;
         }
+        if (op == WCL_OP_SCHUR && (long long)Vh * n < 32768) {
+            // launch-bound: the layout conversions ride in the two hops (k_schur_odd)
+            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            CanonLaunch L{};
+            L.g = &c->g;
+            L.link_prec = eff_lprec(c, lp);
+            L.in = ink;
+            L.out = outk;
+            L.links = links_for(c, L.link_prec);
+            L.clov = clovinv_for(c, lp);
+            L.nrhs = n;
+            L.eo = t;
+            L.eo_stride = hb;
+            HopLaunch W = hop_base(c, lp, sp);
+            W.nrhs = n;
+            for (const int mode : {CLOV_H, XPAY}) {
+                L.mode = W.mode = mode;
+                L.coef = -c->kappa * c->kappa;
+                double wb = 0, wf = 0;
+                if (c->prof) hop_work(W, &wb, &wf);
+                CHK(profiled_ev(c, WCL_K_HOP, wb, wf, [&](const LaunchEvents &ev) {
+                    CanonLaunch T = L;
+                    T.ev = ev;
+                    return launch_schur_canon(T, c->st);
+                }));
+            }
+            continue;
+        }
         CHK(wsget(c, S_IN32, hb * step, &a));
         CHK(wsget(c, S_OUT32, hb * step, &b));
         HIPCHK(launch_pack(c->g, sp, true, ink, a, hb, n, c->st));

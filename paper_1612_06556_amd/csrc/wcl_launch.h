@@ -110,11 +110,15 @@ struct CanonLaunch {
     const void *links, *clov;
     double coef;
     int nrhs, xcd;
-    const void *eo;    // not null (modes HOP and CLOVX, FP32 / FP16): the input as packed e/o
+    void *eo;          // not null (modes HOP and CLOVX, FP32 / FP16): the input as packed e/o
     size_t eo_stride;  // fields, both parities, this many bytes apart
     LaunchEvents ev;
 };
 hipError_t launch_canon(const CanonLaunch &L, hipStream_t st);
+// Even/odd operator halves on canonical spinors with the odd e/o field L.eo
+// between them: mode CLOV_H eo = A_oo H_oe in_e, mode XPAY out_e = in_e +
+// coef A_ee H_eo eo, out_o = 0 (A = clov).
+hipError_t launch_schur_canon(const CanonLaunch &L, hipStream_t st);
 // Canonical U [V][4][3][3] -> internal link fields; with c32 (P32C) and c16
 // (P16C) also the two-row copies, and *defect = max of it and the bits of the
 // largest SU(3) defect (launch_su3_check) if above tol.
