@@ -1221,17 +1221,18 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     const size_t Vh = c->Vh;
     Scalars *sc = SI(c);
     const int sstride = (int)(sizeof(Scalars) / sizeof(double));
-    CHK(norms_dev(c, P64, m, in64, m, n, sc));
     const int vp = cfg.vprec;
-    HIPCHK(launch_convert(P64, vp, n * Vh, Vh, Vh, in64, w.r32, &sc->t[0], 1, 1.0, c->st, 1, sstride));
-    HIPCHK(launch_copy(vp, n * m, w.r32, w.rt32, c->st));
-    HIPCHK(launch_zero(vp, n * m, w.x32, c->st));
-    HIPCHK(launch_zero(vp, n * m, w.p32, c->st));
-    HIPCHK(launch_zero(vp, n * m, w.v32, c->st));
     {
-        const void *a[2] = {w.rt32, w.r32}, *b[2] = {w.r32, w.r32};
-        HIPCHK(launch_dots(vp, m, 2, a, b, c->partials, nullptr, c->st, n, m, c->pstride));
-        HIPCHK(launch_finalize(BICG_INIT_RHO, 4, c->partials, sc, c->st, n, SF(c), c->pstride));
+        const void *a[1] = {in64}, *b[1] = {in64};
+        HIPCHK(launch_dots(P64, m, 1, a, b, c->partials, nullptr, c->st, n, m, c->pstride));
+        int np = 0;
+        HIPCHK(launch_inner_init(vp, Vh, in64, w.r32, w.rt32, w.x32, sc, FoldArgs{c->partials, c->pstride, RED_BLOCKS},
+                                 partials2(c), &np, c->st, n));
+        HIPCHK(launch_finalize(BICG_INIT_RHO, 4, partials2(c), sc, c->st, n, SF(c), c->pstride, np));
+    }
+    if (cfg.persistent) {   // its p update reads p and v from the first iteration on
+        HIPCHK(launch_zero(vp, n * m, w.p32, c->st));
+        HIPCHK(launch_zero(vp, n * m, w.v32, c->st));
     }
     if (cfg.persistent) {
         // every iteration in one cooperative launch, then one read of the scalars
@@ -1439,8 +1440,6 @@ int restart(wcl_ctx *c, const Driver &d, SolveWs &w, int k, double tol, const st
     const int k0 = k < 0 ? 0 : k, cnt = k < 0 ? n : 1;
     const size_t off = (size_t)k0 * d.m * 16;
     HIPCHK(launch_copy(P64, cnt * d.m, (char *)w.r + off, (char *)w.rt + off, c->st));
-    HIPCHK(launch_zero(P64, cnt * d.m, (char *)w.p + off, c->st));
-    HIPCHK(launch_zero(P64, cnt * d.m, (char *)w.v + off, c->st));
     const void *a[2] = {(char *)w.rt + off, (char *)w.r + off}, *b[2] = {(char *)w.r + off, (char *)w.r + off};
     HIPCHK(launch_dots(P64, d.m, 2, a, b, c->partials, nullptr, c->st, cnt, d.m, c->pstride));
     HIPCHK(launch_finalize(BICG_INIT_RHO, 4, c->partials, SO(c) + k0, c->st, cnt, SF(c) + k0, c->pstride));

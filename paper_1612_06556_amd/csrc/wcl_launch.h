@@ -163,7 +163,7 @@ struct Scalars {
     double t[8];                 // spare scalars for reductions
     int done;                    // 1 converged, 2 breakdown
     int iter;
-    int fresh;                   // rho, r2 and iter are complete (no BICG_RHO step pending)
+    int fresh;                   // rho, r2, iter are complete, no BICG_RHO step pending (2: at the start)
     int pad;
 };
 
@@ -203,6 +203,10 @@ int bicg_parts(size_t n, int nrhs, bool fold);
 // p = r + beta (p - omega v), beta = (rho/rho_old)(alpha/omega)
 hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void *v, Scalars *sc,
                          hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
+// Start of an inner solve (prec P32 or P16): from |in64_k|^2's partials f, r = rt =
+// in64 / |in64|, x = 0, t[0] = |in64|^2, and *nparts partials a term for BICG_INIT_RHO.
+hipError_t launch_inner_init(int prec, size_t Vh, const void *in64, void *r, void *rt, void *x, Scalars *sc, const FoldArgs &f,
+                             double *partials, int *nparts, hipStream_t st, int nrhs);
 // s = r - alpha v
 hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, Scalars *sc,
                          hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);

@@ -64,3 +64,23 @@ def test_iteration_limits_inside_a_chunk():
             assert rc == wcl.WCL_ENOCONV and info["outer_iters"] == limit
             got.append(to_host(x))
         assert all(np.array_equal(g, got[0]) for g in got)
+
+
+# half-sites 192 (part of a block), 1800 (eighth block part full), 138240 (past 512 blocks)
+@pytest.mark.parametrize("dims", [(4, 4, 4, 6), (6, 10, 6, 10), (24, 24, 24, 20)])
+@pytest.mark.parametrize("kw", [dict(use_ras=0), dict(), dict(use_ras=0, inner_prec=16, inner_vec_prec=16)])
+def test_a_solve_starts_from_nothing_left_over(dims, kw):
+    """The search vectors of an earlier solve do not reach the next: bitwise what
+    a new lattice gives, and a true residual within the tolerance asked for."""
+    b = synth.gaussian_spinor(dims, 64, 2)
+    lat, orc, _ = setup(dims, -1, 0.11, 1.0, 71, None)
+    x, info, rc = lat.solve(to_gpu(b), tol=1e-10, **kw)
+    assert rc == 0 and all(i["status"] == 0 for i in info)
+    y = lat.apply(x) - to_gpu(b)
+    for k in range(2):
+        assert np.linalg.norm(to_host(y[k])) <= 1e-10 * np.linalg.norm(b[k])
+    again, _, _ = lat.solve(to_gpu(b), tol=1e-10, **kw)
+    assert np.array_equal(to_host(x), to_host(again))
+    new, _, _ = setup.__wrapped__(dims, -1, 0.11, 1.0, 71, None)
+    first, _, _ = new.solve(to_gpu(b), tol=1e-10, **kw)
+    assert np.array_equal(to_host(x), to_host(first))
