@@ -86,6 +86,7 @@ struct wcl_ctx {
     bool gras_ready = false;
     std::vector<Buf> ws;        // workspace, indexed by slot
     double *partials = nullptr; // [2][cap][6][pstride]: the second set for the x, r update's sums
+    int sc_seq = 0;             // number of the last read of the scalars
     int pstride = 0;            // partial sums per term and right-hand side (>= every launch's workgroups)
     Scalars *sc = nullptr;      // [3][cap]: outer, inner, final/scratch scalars per right-hand side
     Scalars *sc_host = nullptr; // pinned mirror
@@ -492,10 +493,24 @@ Scalars *HO(wcl_ctx *c) { return c->sc_host; }
 Scalars *HI(wcl_ctx *c) { return c->sc_host + c->cap; }
 Scalars *HF(wcl_ctx *c) { return c->sc_host + 2 * c->cap; }
 
+// Scalars of n right-hand sides into the pinned host copy, everything queued
+// before them done: a kernel writes them with this read's number behind them,
+// which the host waits for.  A copy and a synchronisation leave the GPU idle for
+// longer: an inner solve reads once or more, FP32 8^3x12 5.71 -> 5.55 ms a solve,
+// FP16 24^3x32 18.3 -> 17.9.  A wait past 5 ms is left to the synchronisation,
+// which also reports a failed stream.
 int read_sc(wcl_ctx *c, Scalars *host, const Scalars *dev, int n)
 {
-    HIPCHK(hipMemcpyAsync(host, dev, sizeof(Scalars) * n, hipMemcpyDeviceToHost, c->st));
-    HIPCHK(hipStreamSynchronize(c->st));
+    const int seq = ++c->sc_seq;
+    HIPCHK(launch_report(dev, host, n, seq, c->st));
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 0; k < n; k++)
+        for (int spin = 0; __atomic_load_n(&host[k].seq, __ATOMIC_ACQUIRE) != seq;) {
+            __builtin_ia32_pause();
+            if (++spin % 64 || std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(5)) continue;
+            HIPCHK(hipStreamSynchronize(c->st));
+            break;
+        }
     return WCL_OK;
 }
 
@@ -1094,6 +1109,7 @@ struct SolveWs {
     void *rhs, *x32, *r32, *rt32, *p32, *v32, *s32, *t32, *ph32, *sh32, *o32;
     // multiplicative Schwarz temporaries (same storage; null unless used)
     void *sapr = nullptr, *sapt = nullptr, *sapo = nullptr;
+    int inner_last = 0;   // iterations of the last inner solve
 };
 
 int get_ws(wcl_ctx *c, SolveWs &w, bool inner, bool plain, int n)
@@ -1305,9 +1321,11 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     }
     // Iterations are queued in chunks; every kernel of an iteration queued
     // after a right-hand side converged is a no-op for it.  The chunk length
-    // follows the observed convergence rate of the slowest right-hand side.
+    // follows the observed convergence rate of the slowest right-hand side; the
+    // first one, the count of the inner solve before it in this solve (same tolerance):
+    // fewer reads, FP32 8^3x12 5.55 -> 5.12 ms a solve, 12 x 16^4 FP16 42.8 -> 42.0.
     int launched = 0;
-    int chunk = std::min(cfg.check_every, 4);
+    int chunk = w.inner_last > 0 ? std::min(w.inner_last, 16) : std::min(cfg.check_every, 4);
     std::vector<double> r2_prev(n, 1.0);
     std::vector<int> it_prev(n, 0);
     std::vector<size_t> rec_mark;  // profile records at the start of each queued iteration
@@ -1365,6 +1383,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
         iters[k] = h[k].iter;
         max_it = std::max(max_it, h[k].iter);
     }
+    w.inner_last = max_it;
     // work of launches after every right-hand side had converged is void
     // (with several right-hand sides the per-rhs masking is not separated)
     for (size_t q = (size_t)max_it; q < rec_mark.size(); q++) {

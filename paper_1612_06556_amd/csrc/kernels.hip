@@ -595,6 +595,28 @@ hipError_t launch_finalize(int step, int nterms, const double *partials, Scalars
     return hipGetLastError();
 }
 
+// One wave per right-hand side: all but the last word, a fence for all of them,
+// then the last word with the read's number.
+__global__ void __launch_bounds__(64) k_report(const Scalars *dev, Scalars *host, int seq)
+{
+    static_assert(offsetof(Scalars, seq) + sizeof(int) == sizeof(Scalars) && sizeof(Scalars) % 8 == 0 && sizeof(Scalars) <= 512);
+    constexpr uint32_t W = sizeof(Scalars) / 8;
+    const uint64_t *d = (const uint64_t *)(dev + blockIdx.x);
+    uint64_t *h = (uint64_t *)(host + blockIdx.x);
+    const uint32_t i = threadIdx.x;
+    const uint64_t v = i < W ? d[i] : 0;
+    if (i + 1 < W) h[i] = v;
+    __threadfence_system();
+    if (i + 1 == W)
+        __hip_atomic_store(h + i, (v & 0xffffffffu) | (uint64_t)(uint32_t)seq << 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_report(const Scalars *dev, Scalars *host, int n, int seq, hipStream_t st)
+{
+    k_report<<<n, 64, 0, st>>>(dev, host, seq);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // BiCGStab vector updates (complex scalars from the device), blockIdx.y = rhs.
 // FOLD: the finaliser's step before the update is done here by every workgroup

@@ -164,7 +164,7 @@ struct Scalars {
     int done;                    // 1 converged, 2 breakdown
     int iter;
     int fresh;                   // rho, r2, iter are complete, no BICG_RHO step pending (2: at the start)
-    int pad;
+    int seq;                     // host copies: the number of the read that wrote them (the last word written)
 };
 
 // dot partials: for each (a_k, b_k) pair listed, sum conj(a_k) b_k, per
@@ -187,6 +187,9 @@ enum BicgStep {
 hipError_t launch_finalize(int step, int nterms, const double *partials, Scalars *sc, hipStream_t st,
                            int nrhs = 1, const Scalars *gate = nullptr, int pstride = RED_BLOCKS,
                            int nparts = RED_BLOCKS);
+
+// dev[0, n) to pinned host memory, then seq in each.
+hipError_t launch_report(const Scalars *dev, Scalars *host, int n, int seq, hipStream_t st);
 
 // A finaliser step done by the vector update that needs its result, from the
 // partials [nrhs][6][pstride] (nparts per term) of the launch before it:

@@ -84,3 +84,18 @@ def test_a_solve_starts_from_nothing_left_over(dims, kw):
     new, _, _ = setup.__wrapped__(dims, -1, 0.11, 1.0, 71, None)
     first, _, _ = new.solve(to_gpu(b), tol=1e-10, **kw)
     assert np.array_equal(to_host(x), to_host(first))
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("limit", [1, 3, 17])
+def test_inner_limits_with_the_queue_length_of_the_solve_before(limit, graph):
+    """An inner solve that cannot reach its tolerance runs to its limit, however
+    long the first queue: 2 limit iterations for each outer one."""
+    dims = (4, 4, 6, 8)
+    lat, _, _ = setup(dims, -1, 0.12, 1.0, 72, None)
+    b = synth.gaussian_spinor(dims, 65, 2)
+    _, info, _ = lat.solve(to_gpu(b), raise_on_error=False, tol=1e-9, use_ras=0, inner_tol=1e-30, max_inner=limit,
+                           max_outer=3, use_graph=graph)
+    for i in info:
+        assert i["outer_iters"] > 0
+        assert i["inner_iters_total"] == 2 * limit * i["outer_iters"]
