@@ -459,6 +459,37 @@ hipError_t launch_dots(int prec, size_t n, int np, const void *const *a, const v
     return hipGetLastError();
 }
 
+// The partials of |x - y|^2 per right-hand side (FP64), as k_dots makes them of a
+// stored difference: the residual's norm without writing and reading it.
+__global__ void __launch_bounds__(RED_THREADS) k_diff_norm(size_t n, size_t stride, const double2 *x, const double2 *y,
+                                                           double *partials, int pstride)
+{
+    __shared__ double lds[16];
+    double v[1] = {0.0};
+    x += blockIdx.y * stride;
+    y += blockIdx.y * stride;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const double2 a = x[i], b = y[i];
+        const double dr = a.x - b.x, di = a.y - b.y;
+        v[0] += dr * dr + di * di;
+    }
+    block_sum<1>(v, lds);
+    if (threadIdx.x == 0) {
+        double *pr = partials + (size_t)blockIdx.y * 6 * pstride + blockIdx.x;
+        pr[0] = v[0];
+        pr[pstride] = 0.0;
+    }
+}
+
+hipError_t launch_diff_norm(size_t n, size_t stride, const void *x, const void *y, double *partials, int pstride, int nrhs,
+                            hipStream_t st)
+{
+    if (pstride < RED_BLOCKS) return hipErrorInvalidValue;
+    k_diff_norm<<<dim3(RED_BLOCKS, nrhs), RED_THREADS, 0, st>>>(n, stride, (const double2 *)x, (const double2 *)y, partials,
+                                                              pstride);
+    return hipGetLastError();
+}
+
 WCL_D void cdiv(const double a[2], const double b[2], double o[2])
 {
     const double d = b[0] * b[0] + b[1] * b[1];
@@ -905,9 +936,12 @@ __global__ void __launch_bounds__(256) k_axpby(size_t n, double ar, double ai, c
     }
 }
 
+// blockIdx.y = slice (sx, sy elements apart)
 template <typename T>
-__global__ void __launch_bounds__(256) k_copy(size_t n, const typename CT<T>::V *x, typename CT<T>::V *y)
+__global__ void __launch_bounds__(256) k_copy(size_t n, const typename CT<T>::V *x, typename CT<T>::V *y, size_t sx, size_t sy)
 {
+    x += blockIdx.y * sx;
+    y += blockIdx.y * sy;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         y[i] = x[i];
 }
@@ -925,9 +959,10 @@ hipError_t launch_axpby(int prec, size_t n, double2 a, const void *x, double2 b,
     return hipGetLastError();
 }
 
-hipError_t launch_copy(int prec, size_t n, const void *x, void *y, hipStream_t st)
+hipError_t launch_copy(int prec, size_t n, const void *x, void *y, hipStream_t st, int slices, size_t sx, size_t sy)
 {
-    WCL_BY_PREC((k_copy<T><<<blas_grid(n), 256, 0, st>>>(n, WCL_CV(x), WCL_V(y))));
+    const dim3 grid(blas_grid(n, slices).x, slices);
+    WCL_BY_PREC((k_copy<T><<<grid, 256, 0, st>>>(n, WCL_CV(x), WCL_V(y), sx, sy)));
     return hipGetLastError();
 }
 

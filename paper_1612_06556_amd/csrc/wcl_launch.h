@@ -174,6 +174,10 @@ hipError_t launch_dots(int prec, size_t n, int npairs, const void *const *a, con
                        double *partials, const Scalars *sc, hipStream_t st, int nrhs = 1, size_t stride = 0,
                        int pstride = RED_BLOCKS);
 
+// Partials of |x_k - y_k|^2 (FP64), RED_BLOCKS per term, for NORM_ONLY with two terms.
+hipError_t launch_diff_norm(size_t n, size_t stride, const void *x, const void *y, double *partials, int pstride, int nrhs,
+                            hipStream_t st);
+
 // BiCGStab building blocks (complex scalars taken from Scalars).
 enum BicgStep {
     BICG_INIT_RHO = 0,   // rho = <rt, r>, r2 = |r|^2, b2 = r2, rho_old = alpha = omega = 1, iter = 0
@@ -223,7 +227,7 @@ hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, cons
 
 // Generic complex axpby: y = a x + b y, a and b host constants.
 hipError_t launch_axpby(int prec, size_t n, double2 a, const void *x, double2 b, void *y, hipStream_t st);
-hipError_t launch_copy(int prec, size_t n, const void *x, void *y, hipStream_t st);
+hipError_t launch_copy(int prec, size_t n, const void *x, void *y, hipStream_t st, int slices = 1, size_t sx = 0, size_t sy = 0);
 hipError_t launch_zero(int prec, size_t n, void *y, hipStream_t st);
 
 // Overlapped RAS block solve: out_e = M in_e (FP32 arithmetic).

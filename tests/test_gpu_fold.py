@@ -99,3 +99,28 @@ def test_inner_limits_with_the_queue_length_of_the_solve_before(limit, graph):
     for i in info:
         assert i["outer_iters"] > 0
         assert i["inner_iters_total"] == 2 * limit * i["outer_iters"]
+
+
+@pytest.mark.parametrize("outer,limit", [("FBICGSTAB", 50), ("DC", 100), ("PLAIN64_EO", 500), ("PLAIN64", 500),
+                                         ("FBICGSTAB", 1), ("DC", 1), ("PLAIN64_EO", 3)])
+@pytest.mark.parametrize("warm", [0, 1])
+def test_reported_residual_is_that_of_the_solution(outer, limit, warm):
+    """true_relres and status belong to the x returned, converged or stopped at the
+    limit; the operator's rounding is a few 1e-16 of |b| in either computation."""
+    from paper_1612_06556_amd import wcl
+    dims = (6, 4, 8, 10)
+    lat, _, _ = setup(dims, -1, 0.12, 1.0, 73, None)
+    b = synth.gaussian_spinor(dims, 66, 3)
+    b[1] = 0.0
+    kw = dict(raise_on_error=False, tol=1e-10, outer=getattr(wcl, "OUTER_" + outer), max_outer=limit, use_ras=0, inner_tol=0.1)
+    if warm:
+        kw["x0"] = lat.solve(to_gpu(b), tol=1e-10)[0]
+        kw["x0"][2] *= 1.001
+    x, info, _ = lat.solve(to_gpu(b), **kw)
+    r = to_host(lat.apply(x)) - b
+    for k in (0, 2):
+        rel_k = np.linalg.norm(r[k]) / np.linalg.norm(b[k])
+        print(outer, limit, warm, k, info[k]["true_relres"], rel_k, info[k]["status"], flush=True)
+        assert abs(info[k]["true_relres"] - rel_k) <= 1e-14 + 1e-9 * rel_k
+        assert (info[k]["status"] == 0) == (rel_k <= 1e-10)
+    assert not to_host(x[1]).any()
