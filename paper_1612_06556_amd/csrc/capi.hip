@@ -1238,7 +1238,6 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     const size_t m = 12 * (size_t)c->Vh;
     const size_t Vh = c->Vh;
     Scalars *sc = SI(c);
-    const int sstride = (int)(sizeof(Scalars) / sizeof(double));
     const int vp = cfg.vprec;
     {
         const void *a[1] = {in64}, *b[1] = {in64};
@@ -1318,7 +1317,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
             c->recs[rec].bytes = b;
             c->recs[rec].flops = f;
         }
-        HIPCHK(launch_convert(vp, P64, n * Vh, Vh, Vh, w.x32, out64, &sc->t[0], 2, 1.0, c->st, 1, sstride));
+        HIPCHK(launch_inner_out(vp, Vh, w.x32, out64, sc, c->st, n));
         return WCL_OK;
     }
     // Iterations are queued in chunks; every kernel of an iteration queued
@@ -1392,7 +1391,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
         const size_t end = (q + 1 < rec_mark.size()) ? rec_mark[q + 1] : c->recs.size();
         for (size_t r = rec_mark[q]; r < end; r++) c->recs[r].bytes = c->recs[r].flops = 0.0;
     }
-    HIPCHK(launch_convert(vp, P64, n * Vh, Vh, Vh, w.x32, out64, &sc->t[0], 2, 1.0, c->st, 1, sstride));
+    HIPCHK(launch_inner_out(vp, Vh, w.x32, out64, sc, c->st, n));
     return WCL_OK;
 }
 

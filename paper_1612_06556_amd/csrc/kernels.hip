@@ -313,50 +313,6 @@ hipError_t launch_clover(const Geom &g, int lp, int sp, int p, const void *clov,
 }
 
 // ---------------------------------------------------------------------------
-// Precision conversion of spinor sections (each section Vh sites).
-template <typename SI, typename SO>
-__global__ void k_convert(size_t nsites, size_t Vi, size_t Vo, const char *in, char *out, const double *sdev,
-                          int mode, double shost, int sec_per_scale, int sdev_stride)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nsites) return;
-    const size_t sec = i / Vi, h = i - sec * Vi;
-    double sc = shost;
-    if (mode) {
-        const double v = sdev[(sec / sec_per_scale) * sdev_stride];
-        if (mode == 1) sc = (v > 0.0) ? shost / sqrt(v) : 0.0;
-        else sc = shost * sqrt(v);
-    }
-    cplx<double> v[12];
-    load_spinor<SI, double>(in + sec * spinor_bytes(sizeof(SI), Vi), h, Vi, v);
-#pragma unroll
-    for (int k = 0; k < 12; k++) v[k] = sc * v[k];
-    store_spinor<SO, double>(out + sec * spinor_bytes(sizeof(SO), Vo), h, Vo, v);
-}
-
-hipError_t launch_convert(int ip, int op, size_t nsites, size_t Vi, size_t Vo, const void *in, void *out,
-                          const double *sdev, int mode, double shost, hipStream_t st, int sec_per_scale,
-                          int sdev_stride)
-{
-    dim3 grid((unsigned)((nsites + 255) / 256)), block(256);
-    const char *i = (const char *)in;
-    char *o = (char *)out;
-#define WCL_CONV(A, B) \
-    k_convert<A, B><<<grid, block, 0, st>>>(nsites, Vi, Vo, i, o, sdev, mode, shost, sec_per_scale, sdev_stride)
-    if (ip == P64 && op == P32) WCL_CONV(double, float);
-    else if (ip == P32 && op == P64) WCL_CONV(float, double);
-    else if (ip == P64 && op == P16) WCL_CONV(double, __half);
-    else if (ip == P16 && op == P64) WCL_CONV(__half, double);
-    else if (ip == P64 && op == P64) WCL_CONV(double, double);
-    else if (ip == P32 && op == P32) WCL_CONV(float, float);
-    else if (ip == P32 && op == P16) WCL_CONV(float, __half);
-    else if (ip == P16 && op == P32) WCL_CONV(__half, float);
-    else return hipErrorInvalidValue;
-#undef WCL_CONV
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 // Reductions: wave sums, then one value per wave through LDS.
 template <int NV>
 WCL_D void block_sum(double v[NV], double *lds /* [NV][16] */)
@@ -860,6 +816,29 @@ hipError_t launch_bicg_xr_dots(int prec, size_t n, void *x, const void *ph, cons
     if (f) WCL_XR(true, *f);
     else WCL_XR(false, FoldArgs{});
 #undef WCL_XR
+    return hipGetLastError();
+}
+
+// End of an inner solve: out64 = |in64| x, with |in64|^2 in t[0].
+template <typename SI>
+__global__ void __launch_bounds__(256) k_inner_out(uint32_t Vh, const char *x, char *out, const Scalars *sc)
+{
+    const uint32_t h = blockIdx.x * 256u + threadIdx.x;
+    if (h >= Vh) return;
+    const double scale = sqrt(sc[blockIdx.y].t[0]);
+    cplx<double> v[12];
+    load_spinor<SI, double>(x + blockIdx.y * spinor_bytes(sizeof(SI), Vh), h, Vh, v);
+#pragma unroll
+    for (int k = 0; k < 12; k++) v[k] = scale * v[k];
+    store_spinor<double, double>(out + blockIdx.y * spinor_bytes(8, Vh), h, Vh, v);
+}
+
+hipError_t launch_inner_out(int prec, size_t Vh, const void *x, void *out64, const Scalars *sc, hipStream_t st, int nrhs)
+{
+    const dim3 grid((unsigned)((Vh + 255) / 256), nrhs);
+    if (prec == P32) k_inner_out<float><<<grid, 256, 0, st>>>((uint32_t)Vh, (const char *)x, (char *)out64, sc);
+    else if (prec == P16) k_inner_out<__half><<<grid, 256, 0, st>>>((uint32_t)Vh, (const char *)x, (char *)out64, sc);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -140,14 +140,6 @@ hipError_t launch_clover_build(const Geom &g, const void *u64, double csw_kappa,
                                void *t32, void *ti32, void *t16, void *ti16, int *info_dev, double *fbuf,
                                hipStream_t st);
 
-// Spinor precision conversion of nsites sites in sections of Vh sites (both
-// layouts hold 12 complex per site): out = scale * in.  mode 0: scale =
-// scale_host; mode 1: scale_host / sqrt(v); mode 2: scale_host * sqrt(v), with
-// v = scale_dev[(section / sec_per_scale) * sdev_stride].
-hipError_t launch_convert(int in_prec, int out_prec, size_t nsites, size_t Vh_in, size_t Vh_out,
-                          const void *in, void *out, const double *scale_dev, int mode,
-                          double scale_host, hipStream_t st, int sec_per_scale = 1, int sdev_stride = 0);
-
 // ---------------------------------------------------------------------------
 // Reductions and BLAS-1 on flat complex arrays (length n complex numbers).
 // Partials are written per workgroup in double; finalisers combine them in
@@ -214,6 +206,8 @@ hipError_t launch_bicg_p(int prec, size_t n, const void *r, void *p, const void 
 // in64 / |in64|, x = 0, t[0] = |in64|^2, and *nparts partials a term for BICG_INIT_RHO.
 hipError_t launch_inner_init(int prec, size_t Vh, const void *in64, void *r, void *rt, void *x, Scalars *sc, const FoldArgs &f,
                              double *partials, int *nparts, hipStream_t st, int nrhs);
+// Its end: out64 = |in64| x, from t[0].
+hipError_t launch_inner_out(int prec, size_t Vh, const void *x, void *out64, const Scalars *sc, hipStream_t st, int nrhs);
 // s = r - alpha v
 hipError_t launch_bicg_s(int prec, size_t n, const void *r, const void *v, void *s, Scalars *sc,
                          hipStream_t st, int nrhs = 1, size_t stride = 0, const FoldArgs *f = nullptr);
