@@ -37,13 +37,13 @@ PAPER_KNC_HOP_GFLOPS = 200.0
 
 # Traffic of the RAS kernel from rocprofv3 counters over the bench step:
 # FETCH_SIZE and WRITE_SIZE per working dispatch (KiB), each scaled by what it
-# reads for a 1 GiB device copy (FETCH 524315.3 KiB -> x2.0, WRITE x1.0).
+# reads for a 1 GiB device copy (FETCH 524307.8 KiB -> x2.0, WRITE x1.0).
 # FETCH_SIZE counts L2 misses, Infinity-Cache hits included.  Valid only for
 # the kernel sources it was taken on (checked by hash; else traffic is null).
 PMC_TRAFFIC = {
-    "ras": {"fetch_kib": 1832045.5, "fetch_scale": 1048576 / 524315.3125, "write_kib": 82944.2,
+    "ras": {"fetch_kib": 1536472.7, "fetch_scale": 1048576 / 524307.75, "write_kib": 82947.0,
             "write_scale": 1.0, "sources": ("ras.hip", "ras_dev.h", "wcl_common.h"),
-            "sha256": "451b8c81dd189e2d08915806a3d687afc92a4e449d49647534c8d3992b186fdd",
+            "sha256": "e81850cf9b988b2ddbe7474aad2222c18149d76a590dd1f6d558a16fdeb1825e",
             "profile": "profiles/k_ras_R12f_24x24x24x32_pmc.md"},
 }
 
