@@ -477,7 +477,8 @@ int ensure_batch(wcl_ctx *c, int n)
     c->sc = nullptr; c->partials = nullptr; c->sc_host = nullptr; c->cap = 0;
     CHK(alloc((void **)&c->sc, sizeof(Scalars) * 3 * n));
     CHK(alloc((void **)&c->partials, sizeof(double) * 2 * 6 * (size_t)c->pstride * n));
-    if (hipHostMalloc((void **)&c->sc_host, sizeof(Scalars) * 3 * n, hipHostMallocDefault) != hipSuccess)
+    // coherent: the device writes it while the host reads (read_sc)
+    if (hipHostMalloc((void **)&c->sc_host, sizeof(Scalars) * 3 * n, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
         return fail(WCL_ENOMEM, "hipHostMalloc failed");
     memset(c->sc_host, 0, sizeof(Scalars) * 3 * n);
     HIPCHK(hipMemcpyAsync(c->sc, c->sc_host, sizeof(Scalars) * 3 * n, hipMemcpyHostToDevice, c->st));
