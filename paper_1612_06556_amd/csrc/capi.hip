@@ -72,8 +72,12 @@ struct wcl_ctx {
     int device = 0;
     void *U64 = nullptr, *U32 = nullptr, *U16 = nullptr;
     void *U32c = nullptr, *U16c = nullptr;  // two-row links (built when compression is on)
-    int gauge_epoch = 0, params_epoch = 0;  // successful-or-not wcl_set_gauge / wcl_set_params calls
-    struct RasCopy { int o = -1, gauge = -1, params = -1; } ras_copy[4];   // see ensure_ras_copies
+    // operator copies of the fused Schwarz kernel, per tier (ras_tier) and parity
+    // of the overlap; links and clov: made from the present fields
+    struct RasCopy {
+        void *links_dev = nullptr, *clov_dev = nullptr;
+        bool links = false, clov = false;
+    } ras_copy[4][2];
     int compress = 0;                       // FP32/FP16 tiers read the two-row links
     void *T64 = nullptr, *Ti64 = nullptr, *T32 = nullptr, *Ti32 = nullptr, *T16 = nullptr, *Ti16 = nullptr;
     Flags *flags = nullptr, *flags_host = nullptr;   // device, pinned host
@@ -130,6 +134,14 @@ int alloc_host(void **p, size_t bytes)
     }
     return WCL_OK;
 }
+
+// While it lives, this thread may allocate and make streams although a stream
+// capture is under way (the calls are not part of it).
+struct OutsideCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 
 int clear_flags(wcl_ctx *c)
 {
@@ -559,8 +571,6 @@ enum Slot {
     S_CLOVF,
     // persistent inner solve: per-workgroup partial sums, barrier counters + time-out flag
     S_PPART, S_PBAR,
-    // operator copies of the fused Schwarz kernel: links and clover inverse of each tier
-    S_RASL, S_RASC = S_RASL + 4,
     // bench copies start here
     S_BENCH = 96,
 };
@@ -595,31 +605,77 @@ int ensure_gras(wcl_ctx *c)
 }
 
 // The fused Schwarz kernel's copies of the links and clover inverse in its
-// block order, for the tier's storage code lprec: rebuilt (two launches) when
-// the gauge field, the clover term or the parity of the overlap changed since,
-// so the work is that of the first application on a new field.
+// block order: one pair per tier (storage code) and parity of the overlap, made
+// by the first application that needs it and from then on wherever the fields
+// are (refresh_ras_links, refresh_ras_clover).  A buffer never changes its
+// order or its address, so an application recorded in a graph reads the fields
+// of its replay.
+constexpr int RAS_TIER[4] = {P32, P16, P32C, P16C};
+bool two_row(int lprec) { return lprec == P32C || lprec == P16C; }
+
+int copy_ras_links(wcl_ctx *c, int k, int o, hipStream_t st)
+{
+    wcl_ctx::RasCopy &r = c->ras_copy[k][o];
+    r.links = false;
+    HIPCHK(launch_ras_links(c->g, RAS_TIER[k], o, links_for(c, RAS_TIER[k]), r.links_dev, st));
+    r.links = true;
+    return WCL_OK;
+}
+
+int copy_ras_clover(wcl_ctx *c, int k, int o, hipStream_t st)
+{
+    wcl_ctx::RasCopy &r = c->ras_copy[k][o];
+    r.clov = false;
+    HIPCHK(launch_ras_clover(c->g, RAS_TIER[k], o, clovinv_for(c, RAS_TIER[k]), r.clov_dev, st));
+    r.clov = true;
+    return WCL_OK;
+}
+
+// After new link fields (full: the FP32 and FP16 ones, rows: the two-row ones);
+// copies whose field was not written with them wait for it.
+int refresh_ras_links(wcl_ctx *c, bool full, bool rows)
+{
+    for (int k = 0; k < 4; k++)
+        for (int o = 0; o < 2; o++)
+            if (c->ras_copy[k][o].links_dev && (two_row(RAS_TIER[k]) ? rows : full)) CHK(copy_ras_links(c, k, o, c->st));
+    return WCL_OK;
+}
+
+int refresh_ras_clover(wcl_ctx *c)
+{
+    for (int k = 0; k < 4; k++)
+        for (int o = 0; o < 2; o++)
+            if (c->ras_copy[k][o].clov_dev) CHK(copy_ras_clover(c, k, o, c->st));
+    return WCL_OK;
+}
+
+// The copies for storage code lprec and the context's overlap.  The first time
+// they are made on a stream of their own and waited for, so that they are there
+// for every later call, also if the context's stream is being captured; the
+// fields are complete once wcl_set_params (or wcl_set_compression) returned.
 int ensure_ras_copies(wcl_ctx *c, int lprec, const void **links, const void **clov_inv)
 {
-    const int k = lprec == P32 ? 0 : lprec == P16 ? 1 : lprec == P32C ? 2 : 3, o = c->ras_overlap & 1;
+    const int o = c->ras_overlap & 1;
+    int k = 0;
+    while (RAS_TIER[k] != lprec) k++;
     const size_t Vh = c->Vh;
-    const size_t lb = lprec == P32 || lprec == P16 ? link_bytes(prec_bytes(lprec), Vh) : link_bytes_c(lprec, Vh);
-    void *l, *t;
-    CHK(wsget(c, S_RASL + k, lb, &l));
-    CHK(wsget(c, S_RASC + k, clover_bytes(prec_bytes(lprec), Vh), &t));
-    wcl_ctx::RasCopy &r = c->ras_copy[k];
-    if (r.o != o || r.gauge != c->gauge_epoch) {
-        r.gauge = -1;
-        HIPCHK(launch_ras_links(c->g, lprec, o, links_for(c, lprec), l, c->st));
-        r.gauge = c->gauge_epoch;
+    wcl_ctx::RasCopy &r = c->ras_copy[k][o];
+    if (!r.links || !r.clov) {
+        OutsideCapture outside;
+        if (!r.links_dev) CHK(alloc(&r.links_dev, two_row(lprec) ? link_bytes_c(lprec, Vh) : link_bytes(prec_bytes(lprec), Vh)));
+        if (!r.clov_dev) CHK(alloc(&r.clov_dev, clover_bytes(prec_bytes(lprec), Vh)));
+        hipStream_t st = nullptr;
+        HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+        int rc = copy_ras_links(c, k, o, st);
+        if (rc == WCL_OK) rc = copy_ras_clover(c, k, o, st);
+        const hipError_t e = hipStreamSynchronize(st);
+        (void)hipStreamDestroy(st);
+        if (rc == WCL_OK && e != hipSuccess) rc = fail(WCL_EHIP, std::string("Schwarz operator copies: ") + hipGetErrorString(e));
+        if (rc != WCL_OK) r.links = r.clov = false;
+        CHK(rc);
     }
-    if (r.o != o || r.params != c->params_epoch) {
-        r.params = -1;
-        HIPCHK(launch_ras_clover(c->g, lprec, o, clovinv_for(c, lprec), t, c->st));
-        r.params = c->params_epoch;
-    }
-    r.o = o;
-    *links = l;
-    *clov_inv = t;
+    *links = r.links_dev;
+    *clov_inv = r.clov_dev;
     return WCL_OK;
 }
 
@@ -660,6 +716,8 @@ int build_compressed(wcl_ctx *c)
         if (d > m || d != d) m = d;
     if (!(m <= SU3_TOL)) return su3_failure(m);
     HIPCHK(launch_compress_links(c->g, c->U64, c->U32c, c->U16c, c->st));
+    CHK(refresh_ras_links(c, false, true));
+    HIPCHK(hipStreamSynchronize(c->st));
     return WCL_OK;
 }
 
@@ -748,6 +806,11 @@ int wcl_destroy(wcl_ctx *c)
                     c->partials, c->sc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    for (auto &tier : c->ras_copy)
+        for (auto &r : tier) {
+            if (r.links_dev) (void)hipFree(r.links_dev);
+            if (r.clov_dev) (void)hipFree(r.clov_dev);
+        }
     for (Buf &b : c->ws)
         if (b.p) (void)hipFree(b.p);
     if (c->sc_host) (void)hipHostFree(c->sc_host);
@@ -772,10 +835,10 @@ int wcl_set_gauge(wcl_ctx *c, const double *U)
     if (!c->U16) CHK(alloc(&c->U16, link_bytes(2, Vh)));
     c->have_gauge = false;
     c->have_params = false;
-    c->gauge_epoch++;
     if (c->compress) CHK(alloc_compressed(c));
     HIPCHK(launch_ingest_gauge(c->g, U, c->U64, c->U32, c->U16, c->compress ? c->U32c : nullptr, c->U16c, SU3_TOL,
                                &c->flags->defect, c->st));
+    CHK(refresh_ras_links(c, true, c->compress != 0));
     if (c->compress) {
         HIPCHK(hipMemcpyAsync(c->flags_host, c->flags, sizeof(Flags), hipMemcpyDeviceToHost, c->st));
         HIPCHK(hipStreamSynchronize(c->st));
@@ -818,11 +881,11 @@ int wcl_set_params(wcl_ctx *c, double kappa, double csw)
         if (!*cl[i]) CHK(alloc(cl[i], clover_bytes(cl_bytes[i], Vh)));
     c->kappa = kappa;
     c->csw = csw;
-    c->params_epoch++;
     void *fbuf;
     CHK(wsget(c, S_CLOVF, (size_t)6 * 9 * 2 * c->Vh * sizeof(double), &fbuf));
     HIPCHK(launch_clover_build(c->g, c->U64, csw * kappa, c->T64, c->Ti64, c->T32, c->Ti32, c->T16, c->Ti16,
                                &c->flags->bad_blocks, (double *)fbuf, c->st));
+    CHK(refresh_ras_clover(c));
     HIPCHK(hipMemcpyAsync(c->flags_host, c->flags, sizeof(Flags), hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
     if (const int bad = c->flags_host->bad_blocks) {
