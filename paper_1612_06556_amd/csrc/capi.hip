@@ -8,10 +8,12 @@
 // scalar live on the GPU; the host reads the convergence flags only.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <string>
@@ -89,6 +91,7 @@ struct wcl_ctx {
     GrasPlan gras{};                   // block fields of the global-memory Schwarz path
     bool gras_ready = false;
     std::vector<Buf> ws;        // workspace, indexed by slot
+    std::vector<void *> outgrown;   // workspace that graphs may still hold (see reserve)
     double *partials = nullptr; // [2][cap][6][pstride]: the second set for the x, r update's sums
     int sc_seq = 0;             // number of the last read of the scalars
     int pstride = 0;            // partial sums per term and right-hand side (>= every launch's workgroups)
@@ -167,6 +170,37 @@ int wsget(wcl_ctx *c, int slot, size_t bytes, void **out)
         b.bytes = bytes;
     }
     *out = b.p;
+    return WCL_OK;
+}
+
+// Workspace of applications, n right-hand sides of per_rhs bytes in each slot
+// listed.  A caller may have recorded an application in a graph, which holds
+// the addresses: a buffer that is outgrown stays until the context is
+// destroyed.  Growing at least doubles a buffer (up to 1 GiB), so all that
+// were outgrown take no more than the present one.
+struct Want {
+    int slot;
+    size_t per_rhs;
+    void **p;
+};
+int reserve(wcl_ctx *c, std::initializer_list<Want> wants, int n)
+{
+    for (const Want &w : wants) {
+        const size_t bytes = w.per_rhs * n;
+        if ((int)c->ws.size() <= w.slot) c->ws.resize(w.slot + 1);
+        Buf &b = c->ws[w.slot];
+        if (b.bytes < bytes) {
+            Buf g;
+            g.bytes = std::max(bytes, std::min(2 * b.bytes, (size_t)1 << 30));
+            if (alloc(&g.p, g.bytes) != WCL_OK) {
+                g.bytes = bytes;
+                CHK(alloc(&g.p, g.bytes));
+            }
+            if (b.p) c->outgrown.push_back(b.p);
+            b = g;
+        }
+        *w.p = b.p;
+    }
     return WCL_OK;
 }
 
@@ -813,6 +847,7 @@ int wcl_destroy(wcl_ctx *c)
         }
     for (Buf &b : c->ws)
         if (b.p) (void)hipFree(b.p);
+    for (void *p : c->outgrown) (void)hipFree(p);
     if (c->sc_host) (void)hipHostFree(c->sc_host);
     if (c->flags_host) (void)hipHostFree(c->flags_host);
     for (auto &r : c->recs) {
@@ -1023,17 +1058,14 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
         double *outk = out + (size_t)k * c->V * 24;
         if (canon) {
             void *eo = nullptr;
-            if (pack) CHK(wsget(c, S_IN32, 2 * hb * step, &eo));
+            if (pack) CHK(reserve(c, {{S_IN32, 2 * hb, &eo}}, step));
             CHK(run_canon(c, op, ink, outk, n, prec, eo));
             continue;
         }
         void *a, *b, *t;
         if (op == WCL_OP_SCHUR_RHS) {
             void *te;
-            CHK(wsget(c, S_IN64, 2 * hb * step, &a));
-            CHK(wsget(c, S_OUT64, hb * step, &b));
-            CHK(wsget(c, S_TMP64E, hb * step, &te));
-            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            CHK(reserve(c, {{S_IN64, 2 * hb, &a}, {S_OUT64, hb, &b}, {S_TMP64E, hb, &te}, {S_TMP64O, hb, &t}}, step));
             HIPCHK(launch_pack(c->g, P64, false, ink, a, 2 * hb, n, c->st));
             CHK(schur_rhs64(c, a, b, t, te, n));
             HIPCHK(launch_unpack(c->g, P64, true, b, hb, outk, n, c->st));
@@ -1041,7 +1073,7 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
         }
         if (op == WCL_OP_SCHUR && (long long)Vh * n < 32768) {
             // launch-bound: the layout conversions ride in the two hops (k_schur_odd)
-            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            CHK(reserve(c, {{S_TMP64O, hb, &t}}, step));
             CanonLaunch L{};
             L.g = &c->g;
             L.link_prec = eff_lprec(c, lp);
@@ -1067,11 +1099,10 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             }
             continue;
         }
-        CHK(wsget(c, S_IN32, hb * step, &a));
-        CHK(wsget(c, S_OUT32, hb * step, &b));
+        CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}}, step));
         HIPCHK(launch_pack(c->g, sp, true, ink, a, hb, n, c->st));
         if (op == WCL_OP_SCHUR) {
-            CHK(wsget(c, S_TMP64O, hb * step, &t));
+            CHK(reserve(c, {{S_TMP64O, hb, &t}}, step));
             CHK(schur(c, lp, sp, a, b, t, nullptr, n));
         } else {
             RasLaunch R{};
@@ -1090,9 +1121,7 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             R.stride = hb;
             if (c->ras_mult) {
                 void *rt, *tt, *to;
-                CHK(wsget(c, S_SAPR, hb * step, &rt));
-                CHK(wsget(c, S_SAPT, hb * step, &tt));
-                CHK(wsget(c, S_SAPO, hb * step, &to));
+                CHK(reserve(c, {{S_SAPR, hb, &rt}, {S_SAPT, hb, &tt}, {S_SAPO, hb, &to}}, step));
                 CHK(run_sap(c, R, lp, sp, a, b, rt, tt, to));
             } else {
                 CHK(run_ras(c, R));
@@ -1193,11 +1222,8 @@ int get_ws(wcl_ctx *c, SolveWs &w, bool inner, bool plain, int n)
     if (inner) {
         void **v32[] = {&w.rhs, &w.x32, &w.r32, &w.rt32, &w.p32, &w.v32, &w.s32, &w.t32, &w.ph32, &w.sh32, &w.o32};
         for (int k = 0; k < 11; k++) CHK(wsget(c, S_RHS32 + k, e32, v32[k]));
-        if (c->ras_mult) {
-            CHK(wsget(c, S_SAPR, e32, &w.sapr));
-            CHK(wsget(c, S_SAPT, e32, &w.sapt));
-            CHK(wsget(c, S_SAPO, e32, &w.sapo));
-        }
+        if (c->ras_mult)
+            CHK(reserve(c, {{S_SAPR, e32 / n, &w.sapr}, {S_SAPT, e32 / n, &w.sapt}, {S_SAPO, e32 / n, &w.sapo}}, n));
     }
     return WCL_OK;
 }
