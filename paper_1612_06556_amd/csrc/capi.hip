@@ -177,7 +177,8 @@ int wsget(wcl_ctx *c, int slot, size_t bytes, void **out)
 // listed.  A caller may have recorded an application in a graph, which holds
 // the addresses: a buffer that is outgrown stays until the context is
 // destroyed.  Growing at least doubles a buffer (up to 1 GiB), so all that
-// were outgrown take no more than the present one.
+// were outgrown take no more than the present one.  Growing while the stream is
+// being captured is allowed: nothing but the allocation happens.
 struct Want {
     int slot;
     size_t per_rhs;
@@ -185,6 +186,7 @@ struct Want {
 };
 int reserve(wcl_ctx *c, std::initializer_list<Want> wants, int n)
 {
+    OutsideCapture outside;
     for (const Want &w : wants) {
         const size_t bytes = w.per_rhs * n;
         if ((int)c->ws.size() <= w.slot) c->ws.resize(w.slot + 1);

@@ -1,5 +1,6 @@
 """Applications recorded in a caller's graph (any operator, any number of
-right-hand sides): the workspace they were recorded with stays theirs."""
+right-hand sides): the workspace they were recorded with stays theirs, and what
+is missing is allocated while recording."""
 import pytest
 
 from gpu_util import require_gpu, to_gpu
@@ -55,4 +56,28 @@ def test_recorded_workspace_outlives_larger_calls(name, prec, dims):
         assert bool((got[0] == want).all())
         _replays(graph, out, want)
         del junk
+    lat.close()
+
+
+# what was applied before decides which buffers exist: none, or another tier's
+BEFORE = [None, ("D", 64)]
+
+
+@pytest.mark.parametrize("name,prec,dims", CASES)
+@pytest.mark.parametrize("before", BEFORE)
+def test_recorded_first_or_with_more_right_hand_sides(name, prec, dims, before):
+    """The first application of its kind only recorded, then one with more
+    right-hand sides than any before."""
+    from paper_1612_06556_amd import wcl
+    psi = to_gpu(synth.gaussian_spinor(dims, 89, 3))
+    ref, op = _lattice(name, dims)
+    want = ref.apply_op(op, psi, prec=prec)
+    ref.close()
+    lat, op = _lattice(name, dims)
+    if before:
+        lat.apply_op(getattr(wcl, "OP_" + before[0]), psi[0], prec=before[1])
+    g1, out1 = _record(lat, op, psi[0], prec)
+    g3, out3 = _record(lat, op, psi, prec)
+    _replays(g3, out3, want)
+    _replays(g1, out1, want[0])
     lat.close()
