@@ -184,26 +184,49 @@ struct Want {
     size_t per_rhs;
     void **p;
 };
-int reserve(wcl_ctx *c, std::initializer_list<Want> wants, int n)
+int reserve_all(wcl_ctx *c, std::initializer_list<Want> wants, int n)
 {
-    OutsideCapture outside;
+    std::vector<Buf> fresh;   // in the order of wants; p null: the slot's buffer is large enough
+    int rc = WCL_OK;
     for (const Want &w : wants) {
         const size_t bytes = w.per_rhs * n;
         if ((int)c->ws.size() <= w.slot) c->ws.resize(w.slot + 1);
+        const size_t have = c->ws[w.slot].bytes;
+        Buf g;
+        if (have < bytes) {
+            g.bytes = std::max(bytes, std::min(2 * have, (size_t)1 << 30));
+            rc = alloc(&g.p, g.bytes);
+            if (rc != WCL_OK && g.bytes > bytes) rc = alloc(&g.p, g.bytes = bytes);
+        }
+        fresh.push_back(g);
+        if (rc != WCL_OK) break;
+    }
+    if (rc != WCL_OK) {
+        for (Buf &g : fresh)
+            if (g.p) (void)hipFree(g.p);
+        return rc;
+    }
+    size_t i = 0;
+    for (const Want &w : wants) {
         Buf &b = c->ws[w.slot];
-        if (b.bytes < bytes) {
-            Buf g;
-            g.bytes = std::max(bytes, std::min(2 * b.bytes, (size_t)1 << 30));
-            if (alloc(&g.p, g.bytes) != WCL_OK) {
-                g.bytes = bytes;
-                CHK(alloc(&g.p, g.bytes));
-            }
+        const Buf &g = fresh[i++];
+        if (g.p) {
             if (b.p) c->outgrown.push_back(b.p);
             b = g;
         }
         *w.p = b.p;
     }
     return WCL_OK;
+}
+
+// The same for as many right-hand sides as memory allows, at most *n; *n
+// receives their number, which the caller then takes at a time.
+int reserve(wcl_ctx *c, std::initializer_list<Want> wants, int *n)
+{
+    OutsideCapture outside;
+    int rc = reserve_all(c, wants, *n);
+    while (rc == WCL_ENOMEM && *n > 1) rc = reserve_all(c, wants, *n = (*n + 1) / 2);
+    return rc;
 }
 
 // Link storage the kernels read for a precision tier (two-row links when on).
@@ -1052,30 +1075,34 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
     // them; at most 16, and a workspace of at most 1 GiB a field
     const size_t hb = half_bytes(sp, Vh);
     const bool pack = canon && packs_first(c, op, nrhs, prec);
-    const int step = canon && !pack ? std::min(nrhs, 4096)
-                           : (int)std::max<size_t>(1, std::min<size_t>({(size_t)nrhs, 16, ((size_t)1 << 30) / (2 * hb)}));
+    int step = canon && !pack ? std::min(nrhs, 4096)
+                              : (int)std::max<size_t>(1, std::min<size_t>({(size_t)nrhs, 16, ((size_t)1 << 30) / (2 * hb)}));
+    // launch-bound: the layout conversions ride in the two hops (k_schur_odd)
+    const bool fused = op == WCL_OP_SCHUR && (long long)Vh * step < 32768;
+    void *eo = nullptr, *a, *b, *t, *te, *rt, *tt, *to;
+    if (pack) CHK(reserve(c, {{S_IN32, 2 * hb, &eo}}, &step));
+    else if (op == WCL_OP_SCHUR_RHS)
+        CHK(reserve(c, {{S_IN64, 2 * hb, &a}, {S_OUT64, hb, &b}, {S_TMP64E, hb, &te}, {S_TMP64O, hb, &t}}, &step));
+    else if (fused) CHK(reserve(c, {{S_TMP64O, hb, &t}}, &step));
+    else if (op == WCL_OP_SCHUR) CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}, {S_TMP64O, hb, &t}}, &step));
+    else if (op == WCL_OP_RAS && c->ras_mult)
+        CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}, {S_SAPR, hb, &rt}, {S_SAPT, hb, &tt}, {S_SAPO, hb, &to}}, &step));
+    else if (op == WCL_OP_RAS) CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}}, &step));
     for (int k = 0; k < nrhs; k += step) {
         const int n = std::min(step, nrhs - k);
         const double *ink = in + (size_t)k * c->V * 24;
         double *outk = out + (size_t)k * c->V * 24;
         if (canon) {
-            void *eo = nullptr;
-            if (pack) CHK(reserve(c, {{S_IN32, 2 * hb, &eo}}, step));
             CHK(run_canon(c, op, ink, outk, n, prec, eo));
             continue;
         }
-        void *a, *b, *t;
         if (op == WCL_OP_SCHUR_RHS) {
-            void *te;
-            CHK(reserve(c, {{S_IN64, 2 * hb, &a}, {S_OUT64, hb, &b}, {S_TMP64E, hb, &te}, {S_TMP64O, hb, &t}}, step));
             HIPCHK(launch_pack(c->g, P64, false, ink, a, 2 * hb, n, c->st));
             CHK(schur_rhs64(c, a, b, t, te, n));
             HIPCHK(launch_unpack(c->g, P64, true, b, hb, outk, n, c->st));
             continue;
         }
-        if (op == WCL_OP_SCHUR && (long long)Vh * n < 32768) {
-            // launch-bound: the layout conversions ride in the two hops (k_schur_odd)
-            CHK(reserve(c, {{S_TMP64O, hb, &t}}, step));
+        if (fused) {
             CanonLaunch L{};
             L.g = &c->g;
             L.link_prec = eff_lprec(c, lp);
@@ -1101,10 +1128,8 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             }
             continue;
         }
-        CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}}, step));
         HIPCHK(launch_pack(c->g, sp, true, ink, a, hb, n, c->st));
         if (op == WCL_OP_SCHUR) {
-            CHK(reserve(c, {{S_TMP64O, hb, &t}}, step));
             CHK(schur(c, lp, sp, a, b, t, nullptr, n));
         } else {
             RasLaunch R{};
@@ -1121,13 +1146,8 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
             R.sc = nullptr;
             R.nrhs = n;
             R.stride = hb;
-            if (c->ras_mult) {
-                void *rt, *tt, *to;
-                CHK(reserve(c, {{S_SAPR, hb, &rt}, {S_SAPT, hb, &tt}, {S_SAPO, hb, &to}}, step));
-                CHK(run_sap(c, R, lp, sp, a, b, rt, tt, to));
-            } else {
-                CHK(run_ras(c, R));
-            }
+            if (c->ras_mult) CHK(run_sap(c, R, lp, sp, a, b, rt, tt, to));
+            else CHK(run_ras(c, R));
         }
         HIPCHK(launch_unpack(c->g, sp, true, b, hb, outk, n, c->st));
     }
@@ -1225,7 +1245,7 @@ int get_ws(wcl_ctx *c, SolveWs &w, bool inner, bool plain, int n)
         void **v32[] = {&w.rhs, &w.x32, &w.r32, &w.rt32, &w.p32, &w.v32, &w.s32, &w.t32, &w.ph32, &w.sh32, &w.o32};
         for (int k = 0; k < 11; k++) CHK(wsget(c, S_RHS32 + k, e32, v32[k]));
         if (c->ras_mult)
-            CHK(reserve(c, {{S_SAPR, e32 / n, &w.sapr}, {S_SAPT, e32 / n, &w.sapt}, {S_SAPO, e32 / n, &w.sapo}}, n));
+            CHK(reserve_all(c, {{S_SAPR, e32 / n, &w.sapr}, {S_SAPT, e32 / n, &w.sapt}, {S_SAPO, e32 / n, &w.sapo}}, n));
     }
     return WCL_OK;
 }
