@@ -111,8 +111,9 @@ int wcl_set_compression(wcl_ctx *ctx, int enable);
  * measured "MULT" kernel (Sec. 2, Sec. 3).  Computed with links, clover and
  * vectors stored in prec (64; 32: FP32 storage and arithmetic; 16: FP16
  * storage, FP32 arithmetic).  in_dev / out_dev: complex128
- * [nrhs][V][4][3] device buffers owned by the caller; they must not
- * overlap.  WCL_ESTATE before wcl_set_params; WCL_EINVAL for nrhs < 1, an
+ * [nrhs][V][4][3] device buffers owned by the caller, best apart: where they
+ * overlap (out_dev = in_dev in place, say), right-hand sides are processed one
+ * after another, each read before its result is written.  WCL_ESTATE before wcl_set_params; WCL_EINVAL for nrhs < 1, an
  * unknown prec or a null pointer; WCL_ENOMEM when the context's workspace
  * cannot grow (prec 16 on large lattices: allocated on first use and kept;
  * the other calls need none). */

@@ -694,6 +694,7 @@ hipError_t launch_canon(const CanonLaunch &L, hipStream_t st)
     if (L.nrhs < 1) return hipErrorInvalidValue;
     if (L.eo) {
         switch (L.link_prec) {
+        case P64: return eo_canon_dispatch<double, double>(L, a, st);
         case P32: return eo_canon_dispatch<float, float>(L, a, st);
         case P16: return eo_canon_dispatch<__half, __half>(L, a, st);
         case P32C: return eo_canon_dispatch<R12f, float>(L, a, st);

@@ -1058,6 +1058,30 @@ static bool packs_first(const wcl_ctx *c, int op, int nrhs, int prec)
     return prec == 16 && op != WCL_OP_CLOVER && op != WCL_OP_CLOVER_INV && (long long)c->Vh * nrhs >= 32768;
 }
 
+// Whether two buffers of n doubles share any.
+static bool overlapping(const double *a, const double *b, size_t n)
+{
+    const size_t x = (size_t)a, y = (size_t)b, bytes = n * sizeof(double);
+    return x < y ? y - x < bytes : x - y < bytes;
+}
+
+// run_canon for one right-hand side whose output may overlap its input: the
+// input is packed first, into the scratch of wcl_set_params (864 bytes a
+// half-site, a field takes at most 384).
+static int run_canon_overlapping(wcl_ctx *c, int op, const double *in, double *out, int prec)
+{
+    void *eo;
+    CHK(wsget(c, S_CLOVF, 0, &eo));
+    if (op != WCL_OP_CLOVER && op != WCL_OP_CLOVER_INV) return run_canon(c, op, in, out, 1, prec, eo);
+    HIPCHK(launch_pack(c->g, prec, false, in, eo, 0, 1, c->st));
+    for (int p = 0; p < 2; p++) {
+        void *f = par(eo, prec, c->Vh, p);
+        CHK(run_clover(c, prec, prec, p, op == WCL_OP_CLOVER ? clov_for(c, prec) : clovinv_for(c, prec), f, f));
+    }
+    HIPCHK(launch_unpack(c->g, prec, false, eo, 0, out, 1, c->st));
+    return WCL_OK;
+}
+
 int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, int prec)
 {
     if (!c || !in || !out) return fail(WCL_EINVAL, "null argument");
@@ -1072,13 +1096,19 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
     const int lp = prec;
     const int sp = (op == WCL_OP_RAS) ? P32 : prec;  // RAS vectors are FP32 in both tiers
     // right-hand sides per set of launches: the links of a launch serve all of
-    // them; at most 16, and a workspace of at most 1 GiB a field
-    const size_t hb = half_bytes(sp, Vh);
+    // them; at most 16, and a workspace of at most 1 GiB a field; where the
+    // buffers overlap, one after another, each packed before its output is written
+    const size_t hb = half_bytes(sp, Vh), field = (size_t)c->V * 24;
+    const bool apart = !overlapping(in, out, nrhs * field);
+    if (canon && !apart) {
+        for (int k = 0; k < nrhs; k++) CHK(run_canon_overlapping(c, op, in + k * field, out + k * field, prec));
+        return WCL_OK;
+    }
     const bool pack = canon && packs_first(c, op, nrhs, prec);
     int step = canon && !pack ? std::min(nrhs, 4096)
-                              : (int)std::max<size_t>(1, std::min<size_t>({(size_t)nrhs, 16, ((size_t)1 << 30) / (2 * hb)}));
+                              : (int)std::max<size_t>(1, std::min<size_t>({(size_t)nrhs, apart ? 16u : 1u, ((size_t)1 << 30) / (2 * hb)}));
     // launch-bound: the layout conversions ride in the two hops (k_schur_odd)
-    const bool fused = op == WCL_OP_SCHUR && (long long)Vh * step < 32768;
+    const bool fused = op == WCL_OP_SCHUR && apart && (long long)Vh * step < 32768;
     void *eo = nullptr, *a, *b, *t, *te, *rt, *tt, *to;
     if (pack) CHK(reserve(c, {{S_IN32, 2 * hb, &eo}}, &step));
     else if (op == WCL_OP_SCHUR_RHS)
@@ -1090,8 +1120,8 @@ int wcl_apply_op(wcl_ctx *c, int op, const double *in, double *out, int nrhs, in
     else if (op == WCL_OP_RAS) CHK(reserve(c, {{S_IN32, hb, &a}, {S_OUT32, hb, &b}}, &step));
     for (int k = 0; k < nrhs; k += step) {
         const int n = std::min(step, nrhs - k);
-        const double *ink = in + (size_t)k * c->V * 24;
-        double *outk = out + (size_t)k * c->V * 24;
+        const double *ink = in + k * field;
+        double *outk = out + k * field;
         if (canon) {
             CHK(run_canon(c, op, ink, outk, n, prec, eo));
             continue;
@@ -1179,9 +1209,13 @@ int wcl_apply_noalloc(wcl_ctx *c, const double *in, double *out, int nrhs, int d
     const bool prof = c->prof;
     c->prof = false;
     int rc = WCL_OK;
-    for (int k = 0; k < nrhs && rc == WCL_OK; k += 4096)   // the one-launch kernel in every tier
-        rc = run_canon(c, dagger ? WCL_OP_DDAG : WCL_OP_D, in + (size_t)k * c->V * 24, out + (size_t)k * c->V * 24,
-                       std::min(nrhs - k, 4096), prec);
+    const int op = dagger ? WCL_OP_DDAG : WCL_OP_D;
+    const size_t field = (size_t)c->V * 24;
+    const bool apart = !overlapping(in, out, nrhs * field);
+    const int step = apart ? 4096 : 1;   // the one-launch kernel in every tier
+    for (int k = 0; k < nrhs && rc == WCL_OK; k += step)
+        rc = apart ? run_canon(c, op, in + k * field, out + k * field, std::min(nrhs - k, step), prec)
+                   : run_canon_overlapping(c, op, in + k * field, out + k * field, prec);
     c->prof = prof;
     return rc;
 }

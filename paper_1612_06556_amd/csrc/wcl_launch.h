@@ -110,7 +110,7 @@ struct CanonLaunch {
     const void *links, *clov;
     double coef;
     int nrhs, xcd;
-    void *eo;          // not null (modes HOP and CLOVX, FP32 / FP16): the input as packed e/o
+    void *eo;          // not null (modes HOP and CLOVX): the input as packed e/o
     size_t eo_stride;  // fields, both parities, this many bytes apart
     LaunchEvents ev;
 };
