@@ -608,10 +608,22 @@ hipError_t launch_report(const Scalars *dev, Scalars *host, int n, int seq, hipS
 // BiCGStab vector updates (complex scalars from the device), blockIdx.y = rhs.
 // FOLD: the finaliser's step before the update is done here by every workgroup
 // from the partials (f), and workgroup 0 of each right-hand side stores the
-// scalars.  What it stores is read by later launches only, or (done) says to
-// every reader what its own sums say: p's new rho waits in t[4..5] until the s
-// update, which reads it, puts it in rho.  fresh: the scalars are complete
-// (2: start, 1: an explicit BICG_RHO step), nothing to fold.
+// scalars while others may still start.  What it stores is either read by later
+// launches only (p's new rho waits in t[4..5] until the s update, which reads it,
+// puts it in rho), or it is `done`, which each workgroup reads once for all of
+// its waves (stopped): one that finds it set leaves whole, one that does not
+// forms the sums itself and comes to the same end.  fresh: the scalars are
+// complete (2: start, 1: an explicit BICG_RHO step), nothing to fold.
+template <bool FOLD>
+WCL_D bool stopped(const Scalars *sc)
+{
+    if constexpr (!FOLD) return sc->done;   // no launch that reads it so writes it
+    __shared__ int done;
+    if (threadIdx.x == 0) done = __hip_atomic_load(&sc->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return done;
+}
+
 template <typename T, bool FOLD>
 __global__ void __launch_bounds__(256) k_bicg_p(size_t n, size_t stride, const typename CT<T>::V *r,
                                                typename CT<T>::V *p, const typename CT<T>::V *v, Scalars *sc_all,
@@ -619,7 +631,7 @@ __global__ void __launch_bounds__(256) k_bicg_p(size_t n, size_t stride, const t
 {
     Scalars *sc = sc_all + blockIdx.y;
     const Scalars in = *sc;
-    if (in.done) return;
+    if (stopped<FOLD>(sc)) return;
     const size_t off = blockIdx.y * stride;
     r += off; p += off; v += off;
     double rho[2] = {in.rho[0], in.rho[1]}, rho_old[2] = {in.rho_old[0], in.rho_old[1]};
@@ -669,7 +681,7 @@ __global__ void __launch_bounds__(256) k_bicg_s(size_t n, size_t stride, const t
 {
     Scalars *sc = sc_all + blockIdx.y;
     const Scalars in = *sc;
-    if (in.done) return;
+    if (stopped<FOLD>(sc)) return;
     const size_t off = blockIdx.y * stride;
     r += off; v += off; s += off;
     double alpha[2] = {in.alpha[0], in.alpha[1]};
