@@ -194,7 +194,9 @@ typedef struct {
     int ras_iters;       /* minimal-residual steps per block solve                   */
     int inner_prec;      /* 32: FP32 links/clover; 16: FP16 links/clover (FP32 math) */
     int use_graph;       /* replay the inner iteration as a captured hipGraph        */
-    int check_every;     /* inner iterations between host convergence checks         */
+    int check_every;     /* iterations between host convergence checks: at most this many
+                          * before the first check of each inner solve (then as many as
+                          * its rate asks for, up to 16); PLAIN64*: between any two  */
     int adjoint;         /* 1: solve D^dag x = b instead, as x = g5 D^-1 (g5 b)      */
     int ras_solver;      /* WCL_RAS_MR, WCL_RAS_JACOBI or WCL_RAS_BICGSTAB (RAS block solver) */
     int inner_vec_prec;  /* 32, or 16: the inner solver's vectors stored in FP16 (FP32

@@ -1469,10 +1469,10 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
     // Iterations are queued in chunks; every kernel of an iteration queued
     // after a right-hand side converged is a no-op for it.  The chunk length
     // follows the observed convergence rate of the slowest right-hand side; the
-    // first one, the count of the inner solve before it in this solve (same tolerance):
-    // fewer reads, FP32 8^3x12 5.55 -> 5.12 ms a solve, 12 x 16^4 FP16 42.8 -> 42.0.
+    // first one, within check_every, the count of the inner solve before it in this
+    // solve (same tolerance): fewer reads than 4.
     int launched = 0;
-    int chunk = w.inner_last > 0 ? std::min(w.inner_last, 16) : std::min(cfg.check_every, 4);
+    int chunk = std::min(cfg.check_every, w.inner_last > 0 ? std::min(w.inner_last, 16) : 4);
     std::vector<double> r2_prev(n, 1.0);
     std::vector<int> it_prev(n, 0);
     std::vector<size_t> rec_mark;  // profile records at the start of each queued iteration
