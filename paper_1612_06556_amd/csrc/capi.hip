@@ -1426,7 +1426,7 @@ int inner_solve(wcl_ctx *c, const InnerCfg &cfg, SolveWs &w, const void *in64, v
         P.num_cus = c->num_cus;
         const size_t rec = c->recs.size();
         CHK(profiled(c, WCL_K_INNER, 0.0, 0.0, [&] { return launch_persist(P, c->st); }));
-        CHK(read_sc(c, HI(c), sc, n));   // synchronises the stream
+        CHK(read_sc(c, HI(c), sc, n));   // after the launch, whose flag is written then
         int err = 0;
         HIPCHK(hipMemcpy(&err, P.err, sizeof(int), hipMemcpyDeviceToHost));
         if (err) return fail(WCL_EHIP, "persistent inner solve: a grid barrier wait exceeded its bound");
@@ -2086,7 +2086,9 @@ extern "C" int wcl_grad(wcl_ctx *c, const double *x, const double *y, double *gU
     // 6 pstride >= 6 Vh / 64 of them
     HIPCHK(launch_grad(c->g, c->U64, X, Y, (double *)K, c->kappa, c->csw, gU, c->partials, c->st));
     HIPCHK(launch_finalize(NORM_ONLY, 1, c->partials, SF(c), c->st, 1, nullptr, 6 * c->pstride, grad_parts(c->g)));
-    CHK(read_sc(c, HF(c), SF(c), 1));   // synchronises the stream
+    // gU is to be complete for any reader, so the stream is waited for, not the report
+    HIPCHK(launch_report(SF(c), HF(c), 1, ++c->sc_seq, c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
     *gk = HF(c)[0].t[0];
     return WCL_OK;
 }
