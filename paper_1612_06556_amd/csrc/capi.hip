@@ -21,6 +21,7 @@
 
 #include "../../include/wcl.h"
 #include "wcl_launch.h"
+#include "wcl_test.h"
 
 using namespace wcl;
 
@@ -2320,5 +2321,44 @@ extern "C" int wcl_autotune_hop(wcl_ctx *c, int prec, int copies, int *best)
             }
     CHK(wcl_set_tuning(c, bb, bo, bx, c->hop_nt));
     if (best) { best[0] = bb; best[1] = bo; best[2] = bx; }
+    return WCL_OK;
+}
+
+// ===========================================================================
+extern "C" int wclt_hop(wcl_ctx *c, int op, const double *in, double *out, int nrhs, int link_prec, int vec_prec, int dots)
+{
+    if (!c || !in || !out) return fail(WCL_EINVAL, "null argument");
+    if (!c->have_params) return fail(WCL_ESTATE, "wclt_hop before wcl_set_gauge and wcl_set_params");
+    CHK(check_prec(link_prec));
+    CHK(check_prec(vec_prec));
+    const bool pair = vec_prec == link_prec || (link_prec == 16 && vec_prec == 32);
+    if (nrhs < 1 || dots < 0 || dots > 2 || !pair || (op == WCL_OP_HOP && vec_prec != 32) || (op == WCL_OP_D && vec_prec != 64) ||
+        (op != WCL_OP_HOP && op != WCL_OP_SCHUR && op != WCL_OP_D) || (dots && (op != WCL_OP_SCHUR || (c->hop_rhs > 1 && nrhs > 1))))
+        return fail(WCL_EINVAL, "wclt_hop: not a launch of the library");
+    const bool even = op == WCL_OP_SCHUR;
+    const size_t stride = even ? half_bytes(vec_prec, c->Vh) : full_bytes(vec_prec, c->Vh);
+    CHK(ensure_batch(c, nrhs));
+    struct Field {
+        void *p = nullptr;
+        ~Field() { if (p) (void)hipFree(p); }
+    } a, b, t;
+    for (Field *f : {&a, &b, &t}) CHK(alloc(&f->p, nrhs * stride));
+    HIPCHK(launch_pack(c->g, vec_prec, even, in, a.p, stride, nrhs, c->st));
+    int np = 0;
+    if (even && dots) CHK(schur_dot(c, link_prec, vec_prec, a.p, b.p, t.p, nullptr, nrhs, dots, a.p, &np));
+    else if (even) CHK(schur(c, link_prec, vec_prec, a.p, b.p, t.p, nullptr, nrhs));
+    else if (op == WCL_OP_D) CHK(full_D(c, P64, P64, a.p, b.p, 0, nullptr, nrhs));
+    for (int p = 0; op == WCL_OP_HOP && p < 2; p++) {
+        HopLaunch L = hop_base(c, link_prec, vec_prec);
+        L.mode = HOP;
+        L.p = p;
+        L.in = par(a.p, vec_prec, c->Vh, 1 - p);
+        L.out = par(b.p, vec_prec, c->Vh, p);
+        L.nrhs = nrhs;
+        L.in_stride = L.out_stride = stride;
+        CHK(run_hop(c, L));
+    }
+    HIPCHK(launch_unpack(c->g, vec_prec, even, b.p, stride, out, nrhs, c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
     return WCL_OK;
 }
