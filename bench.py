@@ -43,7 +43,7 @@ PAPER_KNC_HOP_GFLOPS = 200.0
 PMC_TRAFFIC = {
     "ras": {"fetch_kib": 1536472.7, "fetch_scale": 1048576 / 524307.75, "write_kib": 82947.0,
             "write_scale": 1.0, "sources": ("ras.hip", "ras_dev.h", "wcl_common.h"),
-            "sha256": "e81850cf9b988b2ddbe7474aad2222c18149d76a590dd1f6d558a16fdeb1825e",
+            "sha256": "0bc41fb99304372f37aa39a23e05962eaf8a904a148b7a3977b0e3e285931416",
             "profile": "profiles/k_ras_R12f_24x24x24x32_pmc.md"},
 }
 

@@ -412,31 +412,23 @@ int run_clover(wcl_ctx *c, int lp, int sp, int p, const void *clov, const void *
 size_t half_bytes(int prec, size_t Vh) { return spinor_bytes(prec_bytes(prec), Vh); }
 size_t full_bytes(int prec, size_t Vh) { return 2 * spinor_bytes(prec_bytes(prec), Vh); }
 
-// One parity of the full operator: out_p = A_pp x_p + coef H in_{1-p}
-int full_D_parity(wcl_ctx *c, int lprec, int sprec, int p, const void *field_in, void *field_out, int dagger,
-                  const Scalars *sc, int nrhs)
+// out = D in (FP64), one launch per parity: out_p = A_pp x_p - kappa H in_{1-p}
+int full_D(wcl_ctx *c, const void *in, void *out, const Scalars *sc = nullptr, int nrhs = 1)
 {
-    HopLaunch L = hop_base(c, lprec, sprec);
+    HopLaunch L = hop_base(c, P64, P64);
     L.mode = CLOVX;
-    L.dagger = dagger;
-    L.p = p;
-    L.in = par(field_in, sprec, c->Vh, 1 - p);
-    L.x = par(field_in, sprec, c->Vh, p);
-    L.out = par(field_out, sprec, c->Vh, p);
-    L.clov = clov_for(c, lprec);
+    L.clov = c->T64;
     L.coef = -c->kappa;
     L.sc = sc;
     L.nrhs = nrhs;
-    L.in_stride = L.out_stride = L.x_stride = full_bytes(sprec, c->Vh);
-    CHK(run_hop(c, L));
-    return WCL_OK;
-}
-
-int full_D(wcl_ctx *c, int lprec, int sprec, const void *in, void *out, int dagger, const Scalars *sc = nullptr,
-           int nrhs = 1)
-{
-    CHK(full_D_parity(c, lprec, sprec, 0, in, out, dagger, sc, nrhs));
-    CHK(full_D_parity(c, lprec, sprec, 1, in, out, dagger, sc, nrhs));
+    L.in_stride = L.out_stride = L.x_stride = full_bytes(P64, c->Vh);
+    for (int p = 0; p < 2; p++) {
+        L.p = p;
+        L.in = par(in, P64, c->Vh, 1 - p);
+        L.x = par(in, P64, c->Vh, p);
+        L.out = par(out, P64, c->Vh, p);
+        CHK(run_hop(c, L));
+    }
     return WCL_OK;
 }
 
@@ -1547,7 +1539,7 @@ int true_residuals(wcl_ctx *c, SolveWs &w, const std::vector<double> &bnorm2, st
 {
     const size_t mf = 24 * (size_t)c->Vh;
     const int n = w.n;
-    CHK(full_D(c, P64, P64, w.x, w.res, 0, nullptr, n));
+    CHK(full_D(c, w.x, w.res, nullptr, n));
     HIPCHK(launch_diff_norm(mf, mf, w.b, w.res, c->partials, c->pstride, n, c->st));
     HIPCHK(launch_finalize(NORM_ONLY, 2, c->partials, SF(c), c->st, n, nullptr, c->pstride));
     CHK(read_sc(c, HF(c), SF(c), n));
@@ -1583,7 +1575,7 @@ struct Driver {
 int apply_A(wcl_ctx *c, const Driver &d, SolveWs &w, const void *in, void *out, const Scalars *sc)
 {
     if (d.eo) return schur(c, P64, P64, in, out, w.o, sc, w.n);
-    return full_D(c, P64, P64, in, out, 0, sc, w.n);
+    return full_D(c, in, out, sc, w.n);
 }
 
 // The full solution (in w.x) of the even one: even halves copied, odd halves written by the hop.
@@ -2347,7 +2339,7 @@ extern "C" int wclt_hop(wcl_ctx *c, int op, const double *in, double *out, int n
     int np = 0;
     if (even && dots) CHK(schur_dot(c, link_prec, vec_prec, a.p, b.p, t.p, nullptr, nrhs, dots, a.p, &np));
     else if (even) CHK(schur(c, link_prec, vec_prec, a.p, b.p, t.p, nullptr, nrhs));
-    else if (op == WCL_OP_D) CHK(full_D(c, P64, P64, a.p, b.p, 0, nullptr, nrhs));
+    else if (op == WCL_OP_D) CHK(full_D(c, a.p, b.p, nullptr, nrhs));
     for (int p = 0; op == WCL_OP_HOP && p < 2; p++) {
         HopLaunch L = hop_base(c, link_prec, vec_prec);
         L.mode = HOP;

@@ -219,26 +219,26 @@ WCL_D void hop_compute(const HopStage<SL, SS, R> &st, cplx<R> acc[12])
     accumulate<MU, S, R>(acc, uh);
 }
 
-template <typename SL, typename SS, int SG, int D, int K, bool NT, int NS, typename R>
+template <typename SL, typename SS, int D, int K, bool NT, int NS, typename R>
 WCL_D void hop_prologue(const HopArgs &a, const Site &s, uint32_t h, const char *in, const LdsIn &li,
                         HopStage<SL, SS, R> st[D], cplx<R> acc[12])
 {
     if constexpr (K < D - 1) {
         hop_load<SL, SS, K, NT, NS, R>(a, s, h, in, li, st[K], acc);
-        hop_prologue<SL, SS, SG, D, K + 1, NT, NS, R>(a, s, h, in, li, st, acc);
+        hop_prologue<SL, SS, D, K + 1, NT, NS, R>(a, s, h, in, li, st, acc);
     }
 }
 
 // hop K is computed while the operands of hop K + D - 1 are in flight
-template <typename SL, typename SS, int SG, int D, int K, bool NT, int NS, typename R>
+template <typename SL, typename SS, int D, int K, bool NT, int NS, typename R>
 WCL_D void hop_pipeline(const HopArgs &a, const Site &s, uint32_t h, const char *in, const LdsIn &li,
                         HopStage<SL, SS, R> st[D], cplx<R> acc[12])
 {
     if constexpr (K < 8) {
         if constexpr (K + D - 1 < 8)
             hop_load<SL, SS, K + D - 1, NT, NS, R>(a, s, h, in, li, st[(K + D - 1) % D], acc);
-        hop_compute<K, SG, SL, SS, R>(st[K % D], acc);
-        hop_pipeline<SL, SS, SG, D, K + 1, NT, NS, R>(a, s, h, in, li, st, acc);
+        hop_compute<K, 1, SL, SS, R>(st[K % D], acc);
+        hop_pipeline<SL, SS, D, K + 1, NT, NS, R>(a, s, h, in, li, st, acc);
     }
 }
 
@@ -249,7 +249,7 @@ WCL_D void hop_pipeline(const HopArgs &a, const Site &s, uint32_t h, const char 
 // dot[0..1] += <w, o> (w a field of the output parity, same storage), and
 // with NDOT == 2 dot[2] += |o|^2, accumulated in FP64 (zero for sites past
 // the lattice).
-template <typename SL, typename SS, int MODE, bool DAG, int DEPTH, bool NT, int NS, int NDOT = 0>
+template <typename SL, typename SS, int MODE, int DEPTH, bool NT, int NS, int NDOT = 0>
 WCL_D void hop_block(const HopArgs &a, int bid, int rhs, uint4 *sin, const void *dotw = nullptr,
                      double *dot = nullptr)
 {
@@ -273,13 +273,12 @@ WCL_D void hop_block(const HopArgs &a, int bid, int rhs, uint4 *sin, const void 
     const size_t Vh = a.g.Vh;
     char *out = (char *)a.out + rhs * a.out_stride;
     const Site s = decompose(a.g, h, a.p);
-    constexpr int SG = DAG ? -1 : 1;
     cplx<R> acc[12];
 #pragma unroll
     for (int i = 0; i < 12; i++) acc[i] = {R(0), R(0)};
     HopStage<SL, SS, R> st[DEPTH];
-    hop_prologue<SL, SS, SG, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
-    hop_pipeline<SL, SS, SG, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
+    hop_prologue<SL, SS, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
+    hop_pipeline<SL, SS, DEPTH, 0, NT, NS, R>(a, s, h, in, li, st, acc);
 
     cplx<R> o[12];
     if constexpr (MODE == HOP) {

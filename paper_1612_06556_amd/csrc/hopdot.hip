@@ -19,7 +19,7 @@ __global__ void __launch_bounds__(256) k_hop_dot(HopArgs a, const void *dotw, do
     __shared__ uint4 sin[NS > 0 ? NWORDS * NS : 1];
     __shared__ double red[3 * 16];
     double d[3] = {0.0, 0.0, 0.0};
-    hop_block<SL, SS, XPAY, false, 2, false, NS, NDOT>(a, bid, rhs, sin, dotw, d);
+    hop_block<SL, SS, XPAY, 2, false, NS, NDOT>(a, bid, rhs, sin, dotw, d);
     // workgroup sums in a fixed order
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
@@ -68,7 +68,7 @@ static hipError_t hop_dot_n(const HopLaunch &L, const HopArgs &a, dim3 grid, dim
 
 hipError_t launch_hop_dot(const HopLaunch &L, const HopArgs &a, dim3 grid, dim3 block, hipStream_t st)
 {
-    if (L.mode != XPAY || L.dagger || (L.ndot != 1 && L.ndot != 2) || !L.dotw || !L.partials) return hipErrorInvalidValue;
+    if (L.mode != XPAY || (L.ndot != 1 && L.ndot != 2) || !L.dotw || !L.partials) return hipErrorInvalidValue;
     if ((int)(grid.x / a.nrhs) > L.pstride) return hipErrorInvalidValue;
     if (L.link_prec == P64 && L.spin_prec == P64) return hop_dot_n<double, double>(L, a, grid, block, st);
     if (L.link_prec == P32 && L.spin_prec == P32) return hop_dot_n<float, float>(L, a, grid, block, st);

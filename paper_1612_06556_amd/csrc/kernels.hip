@@ -1,6 +1,5 @@
 // kernels.hip -- the even/odd hopping kernel with its fused epilogues, the
-// clover apply, precision conversion and the BLAS-1 / reduction kernels of the
-// solvers.
+// clover apply and the BLAS-1 / reduction kernels of the solvers.
 //
 // The operator (Wilson-Clover, paper Sec. 1 and Sec. 2):
 //   D = T - kappa H,  (H psi)(x) = sum_mu (1 - g_mu) U_mu(x) psi(x+mu)
@@ -17,7 +16,7 @@ namespace wcl {
 // NT: links and clover loaded non-temporally (a single right-hand side reads
 // them once per launch).  Off by default: repeated applications in a solver
 // find the links in the Infinity Cache only when they were loaded normally.
-template <typename SL, typename SS, int MODE, bool DAG, int DEPTH, bool NT, int NS>
+template <typename SL, typename SS, int MODE, int DEPTH, bool NT, int NS>
 __global__ void __launch_bounds__(256) k_hop(HopArgs a)
 {
     // workgroup id = site block * nrhs + rhs: the nrhs workgroups of one site
@@ -36,7 +35,7 @@ __global__ void __launch_bounds__(256) k_hop(HopArgs a)
         const int bid = grp * a.tpw + k;
         if (bid >= nb) break;                 // uniform in the workgroup
         if (NS > 0 && k) __syncthreads();     // the previous block's staged input is read
-        hop_block<SL, SS, MODE, DAG, DEPTH, NT, NS>(a, bid, rhs, sin);
+        hop_block<SL, SS, MODE, DEPTH, NT, NS>(a, bid, rhs, sin);
     }
 }
 
@@ -44,7 +43,7 @@ __global__ void __launch_bounds__(256) k_hop(HopArgs a)
 // Several right-hand sides per thread (batched inner solves): each link and
 // clover block is loaded once into registers and applied to the NR
 // right-hand sides of a group, whose neighbour spinors are loaded together.
-// FP32 spinors; modes HOP, CLOV_H, XPAY; no dagger.  A right-hand side whose
+// FP32 spinors; modes HOP, CLOV_H, XPAY.  A right-hand side whose
 // scalars say done is neither computed nor stored.
 template <typename SL, int K, int NR>
 WCL_D void hop_mr_hop(const HopArgs &a, const Site &s, uint32_t h0, const bool act[NR], const char *const in[NR],
@@ -184,36 +183,41 @@ static hipError_t hop_mr_nr(const HopLaunch &L, const HopArgs &a, dim3 block, hi
 }
 
 // Pipeline-depth variants (hops whose operands are in flight: 2, 3) times
-// temporal / non-temporal operator loads.  D^dag launches use depth 2.
+// temporal / non-temporal operator loads.
 template <typename SL, typename SS, int MODE>
-static void hop_dispatch_dag(const HopLaunch &L, const HopArgs &a, dim3 grid, dim3 block, hipStream_t st)
+static hipError_t hop_dispatch_shape(const HopLaunch &L, const HopArgs &a, dim3 grid, dim3 block, hipStream_t st)
 {
     const bool nt = L.nontemporal && a.nrhs == 1;
-    // staged input spinors (depth 2, non-dagger): one LDS slot per thread;
-    // with non-temporal operator loads for single-use (cold) calls
-    const bool staged = L.lds_stage && !L.dagger && L.depth == 2;
-    if (staged && nt && block.x == 64) ext_launch(k_hop<SL, SS, MODE, false, 2, true, 64>, grid, block, 0, st, L.ev, a);
-    else if (staged && nt && block.x == 128) ext_launch(k_hop<SL, SS, MODE, false, 2, true, 128>, grid, block, 0, st, L.ev, a);
-    else if (staged && nt && block.x == 256) ext_launch(k_hop<SL, SS, MODE, false, 2, true, 256>, grid, block, 0, st, L.ev, a);
-    else if (staged && !nt && block.x == 64) ext_launch(k_hop<SL, SS, MODE, false, 2, false, 64>, grid, block, 0, st, L.ev, a);
-    else if (staged && !nt && block.x == 128) ext_launch(k_hop<SL, SS, MODE, false, 2, false, 128>, grid, block, 0, st, L.ev, a);
-    else if (staged && !nt && block.x == 256) ext_launch(k_hop<SL, SS, MODE, false, 2, false, 256>, grid, block, 0, st, L.ev, a);
-    else if (L.dagger) ext_launch(k_hop<SL, SS, MODE, true, 2, false, 0>, grid, block, 0, st, L.ev, a);
-    else if (L.depth == 3 && nt) ext_launch(k_hop<SL, SS, MODE, false, 3, true, 0>, grid, block, 0, st, L.ev, a);
-    else if (L.depth == 3) ext_launch(k_hop<SL, SS, MODE, false, 3, false, 0>, grid, block, 0, st, L.ev, a);
-    else if (nt) ext_launch(k_hop<SL, SS, MODE, false, 2, true, 0>, grid, block, 0, st, L.ev, a);
-    else ext_launch(k_hop<SL, SS, MODE, false, 2, false, 0>, grid, block, 0, st, L.ev, a);
+    // staged input spinors (depth 2): one LDS slot per thread; with non-temporal
+    // operator loads for single-use (cold) calls
+    const bool staged = L.lds_stage && L.depth == 2;
+    if (staged && nt && block.x == 64) ext_launch(k_hop<SL, SS, MODE, 2, true, 64>, grid, block, 0, st, L.ev, a);
+    else if (staged && nt && block.x == 128) ext_launch(k_hop<SL, SS, MODE, 2, true, 128>, grid, block, 0, st, L.ev, a);
+    else if (staged && nt && block.x == 256) ext_launch(k_hop<SL, SS, MODE, 2, true, 256>, grid, block, 0, st, L.ev, a);
+    else if (staged && !nt && block.x == 64) ext_launch(k_hop<SL, SS, MODE, 2, false, 64>, grid, block, 0, st, L.ev, a);
+    else if (staged && !nt && block.x == 128) ext_launch(k_hop<SL, SS, MODE, 2, false, 128>, grid, block, 0, st, L.ev, a);
+    else if (staged && !nt && block.x == 256) ext_launch(k_hop<SL, SS, MODE, 2, false, 256>, grid, block, 0, st, L.ev, a);
+    else if (L.depth == 3 && nt) ext_launch(k_hop<SL, SS, MODE, 3, true, 0>, grid, block, 0, st, L.ev, a);
+    else if (L.depth == 3) ext_launch(k_hop<SL, SS, MODE, 3, false, 0>, grid, block, 0, st, L.ev, a);
+    else if (nt) ext_launch(k_hop<SL, SS, MODE, 2, true, 0>, grid, block, 0, st, L.ev, a);
+    else ext_launch(k_hop<SL, SS, MODE, 2, false, 0>, grid, block, 0, st, L.ev, a);
+    return hipGetLastError();
 }
 
+// The Schur operator's halves in every storage; H alone on FP32 vectors
+// (wcl_bench_hop) and the full operator in FP64 (residuals, the solver on the
+// full system): applications on the caller's vectors have kernels of their own
+// (canon.hip).
 template <typename SL, typename SS>
-static void hop_dispatch_mode(const HopLaunch &L, const HopArgs &a, dim3 grid, dim3 block, hipStream_t st)
+static hipError_t hop_dispatch_mode(const HopLaunch &L, const HopArgs &a, dim3 grid, dim3 block, hipStream_t st)
 {
-    switch (L.mode) {
-    case HOP: hop_dispatch_dag<SL, SS, HOP>(L, a, grid, block, st); break;
-    case CLOV_H: hop_dispatch_dag<SL, SS, CLOV_H>(L, a, grid, block, st); break;
-    case XPAY: hop_dispatch_dag<SL, SS, XPAY>(L, a, grid, block, st); break;
-    default: hop_dispatch_dag<SL, SS, CLOVX>(L, a, grid, block, st); break;
-    }
+    if (L.mode == CLOV_H) return hop_dispatch_shape<SL, SS, CLOV_H>(L, a, grid, block, st);
+    if (L.mode == XPAY) return hop_dispatch_shape<SL, SS, XPAY>(L, a, grid, block, st);
+    if constexpr (std::is_same<SS, float>::value)
+        if (L.mode == HOP) return hop_dispatch_shape<SL, SS, HOP>(L, a, grid, block, st);
+    if constexpr (std::is_same<SS, double>::value)
+        if (L.mode == CLOVX) return hop_dispatch_shape<SL, SS, CLOVX>(L, a, grid, block, st);
+    return hipErrorInvalidValue;
 }
 
 int hop_parts(const HopLaunch &L)
@@ -256,8 +260,7 @@ hipError_t launch_hop(const HopLaunch &L, hipStream_t st)
         a.tpw = L.tpw;
         grid = dim3(((nb + L.tpw - 1) / L.tpw) * a.nrhs);
     }
-    if ((L.rhs_per_thread == 2 || L.rhs_per_thread == 4) && a.nrhs >= 2 && L.spin_prec == P32 && !L.dagger &&
-        L.mode != CLOVX) {
+    if ((L.rhs_per_thread == 2 || L.rhs_per_thread == 4) && a.nrhs >= 2 && L.spin_prec == P32 && L.mode != CLOVX) {
         switch (L.link_prec) {
         case P32: return hop_mr_nr<float>(L, a, block, st);
         case P16: return hop_mr_nr<__half>(L, a, block, st);
@@ -266,15 +269,14 @@ hipError_t launch_hop(const HopLaunch &L, hipStream_t st)
         default: break;
         }
     }
-    if (L.link_prec == P64 && L.spin_prec == P64) hop_dispatch_mode<double, double>(L, a, grid, block, st);
-    else if (L.link_prec == P32 && L.spin_prec == P32) hop_dispatch_mode<float, float>(L, a, grid, block, st);
-    else if (L.link_prec == P16 && L.spin_prec == P32) hop_dispatch_mode<__half, float>(L, a, grid, block, st);
-    else if (L.link_prec == P16 && L.spin_prec == P16) hop_dispatch_mode<__half, __half>(L, a, grid, block, st);
-    else if (L.link_prec == P32C && L.spin_prec == P32) hop_dispatch_mode<R12f, float>(L, a, grid, block, st);
-    else if (L.link_prec == P16C && L.spin_prec == P32) hop_dispatch_mode<R12h, float>(L, a, grid, block, st);
-    else if (L.link_prec == P16C && L.spin_prec == P16) hop_dispatch_mode<R12h, __half>(L, a, grid, block, st);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (L.link_prec == P64 && L.spin_prec == P64) return hop_dispatch_mode<double, double>(L, a, grid, block, st);
+    if (L.link_prec == P32 && L.spin_prec == P32) return hop_dispatch_mode<float, float>(L, a, grid, block, st);
+    if (L.link_prec == P16 && L.spin_prec == P32) return hop_dispatch_mode<__half, float>(L, a, grid, block, st);
+    if (L.link_prec == P16 && L.spin_prec == P16) return hop_dispatch_mode<__half, __half>(L, a, grid, block, st);
+    if (L.link_prec == P32C && L.spin_prec == P32) return hop_dispatch_mode<R12f, float>(L, a, grid, block, st);
+    if (L.link_prec == P16C && L.spin_prec == P32) return hop_dispatch_mode<R12h, float>(L, a, grid, block, st);
+    if (L.link_prec == P16C && L.spin_prec == P16) return hop_dispatch_mode<R12h, __half>(L, a, grid, block, st);
+    return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------

@@ -197,7 +197,7 @@ WCL_D void hop_phase(const HopArgs &h, int rhs, uint4 *sin, const void *dotw, do
     const ItemRange R = xcd_items(nchunk);
     for (int c = R.first; c < R.last; c += R.step) {
         __syncthreads();   // the previous chunk's staged input is no longer read
-        hop_block<SL, SV, MODE, false, 2, false, NS, NDOT>(h, c, rhs, sin, dotw, dot);
+        hop_block<SL, SV, MODE, 2, false, NS, NDOT>(h, c, rhs, sin, dotw, dot);
     }
 }
 

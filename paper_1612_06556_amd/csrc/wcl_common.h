@@ -637,32 +637,6 @@ WCL_D void load_clover(const void *base, int p, uint32_t h, uint32_t Vh, R c[72]
     }
 }
 
-template <typename S>
-WCL_D void store_clover(void *base, int p, uint32_t h, uint32_t Vh, const double c[72])
-{
-    static_assert(!std::is_empty<S>::value, "two-row link tags are link storage only");
-    if constexpr (sizeof(S) == 8) {
-#pragma unroll
-        for (uint32_t k = 0; k < 36; k++)
-            stf(base, (((uint32_t)p * 36 + k) * Vh + h) * 16u, make_double2(c[2 * k], c[2 * k + 1]));
-    } else if constexpr (sizeof(S) == 4) {
-#pragma unroll
-        for (uint32_t k = 0; k < 18; k++)
-            stf(base, (((uint32_t)p * 18 + k) * Vh + h) * 16u,
-                make_float4((float)c[4 * k], (float)c[4 * k + 1], (float)c[4 * k + 2], (float)c[4 * k + 3]));
-    } else {
-#pragma unroll
-        for (uint32_t k = 0; k < 9; k++) {
-            uint4 w;
-            w.x = f22h((float)c[8 * k], (float)c[8 * k + 1]);
-            w.y = f22h((float)c[8 * k + 2], (float)c[8 * k + 3]);
-            w.z = f22h((float)c[8 * k + 4], (float)c[8 * k + 5]);
-            w.w = f22h((float)c[8 * k + 6], (float)c[8 * k + 7]);
-            stf(base, (((uint32_t)p * 9 + k) * Vh + h) * 16u, w);
-        }
-    }
-}
-
 // One chirality block (36 reals) of a clover site: half 0 = spins 0,1,
 // half 1 = spins 2,3.  ClovHalfRaw holds it as loaded (decoded later).
 template <typename S> struct ClovHalfRaw { float4 v[9]; };

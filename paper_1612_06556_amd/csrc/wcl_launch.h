@@ -31,8 +31,7 @@ inline int prec_bytes(int prec) { return prec == P64 ? 8 : (prec == P32 || prec 
 // bytes of one compressed link field (both parities, 4 directions)
 inline size_t link_bytes_c(int prec, size_t Vh) { return prec == P32C ? 24 * 16 * Vh : (8 * 16 + 8 * 8) * Vh; }
 
-// Epilogues of the hopping kernel; acc = H_{p,1-p} in (projectors swapped
-// when dagger):
+// Epilogues of the hopping kernel; acc = H_{p,1-p} in:
 //   HOP      out = acc
 //   CLOV_H   out = A acc                 (A = packed clover field, parity p)
 //   XPAY     out = x + coef * A acc      (Schur second half)
@@ -44,7 +43,6 @@ struct HopLaunch {
     int link_prec;      // storage of links and clover
     int spin_prec;      // storage of in / out / x
     int mode;
-    int dagger;
     int p;              // output parity
     const void *in;     // parity 1-p
     void *out;          // parity p
@@ -58,7 +56,7 @@ struct HopLaunch {
     int block;          // threads per workgroup (64..256)
     int depth;          // hops whose operands are in flight per thread (2, 3)
     int nontemporal;    // links / clover loaded non-temporally (single right-hand side only)
-    int lds_stage;      // 1: stage each 128-site tile's input spinors in LDS (block 128, 4^4 tiles)
+    int lds_stage;      // 1: stage the workgroup's own input spinors in LDS (depth 2)
     int tpw;            // consecutive site blocks per workgroup (0 or 1: one; at most 64)
     int rhs_per_thread; // 2 or 4: batched launches keep that many right-hand sides per thread
                         // (FP32 spinors, modes HOP / CLOV_H / XPAY); else one per workgroup
