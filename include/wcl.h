@@ -66,9 +66,10 @@ enum { WCL_PREC64 = 64, WCL_PREC32 = 32, WCL_PREC16 = 16 };
  * tile: extents of the internal blocked layout and of the Schwarz cores
  * (each even and dividing dims[mu]); NULL picks 4^4 when it divides the
  * lattice, else 2^4.  Not in the paper (layout): 4^4 suits the fused
- * Schwarz kernel and repeated (cache-resident) hops; tiles spanning whole
- * x-rows (e.g. 24x4x8x4 on 24^3x32) make single-use hops faster, and a
- * Schwarz solve on them needs explicit cores (wcl_set_ras_cores).  t_bc = +1 periodic, -1 antiperiodic in time.
+ * Schwarz kernel, wcl_apply and repeated (cache-resident) hops; tiles spanning
+ * whole x-rows (e.g. 24x4x8x4 on 24^3x32) make cold launches of the hopping
+ * kernel (wcl_bench_hop) faster, and a Schwarz solve on them needs explicit
+ * cores (wcl_set_ras_cores).  t_bc = +1 periodic, -1 antiperiodic in time.
  * hip_stream: a hipStream_t (NULL = the null stream).  *out receives the
  * context, owned by the caller until wcl_destroy.  Errors: WCL_EINVAL
  * (also for more than 7,456,540 sites: fields are addressed with 32-bit byte
@@ -115,15 +116,18 @@ int wcl_set_compression(wcl_ctx *ctx, int enable);
  * overlap (out_dev = in_dev in place, say), right-hand sides are processed one
  * after another, each read before its result is written.  WCL_ESTATE before wcl_set_params; WCL_EINVAL for nrhs < 1, an
  * unknown prec or a null pointer; WCL_ENOMEM when the context's workspace
- * cannot grow (prec 16 on large lattices: allocated on first use and kept;
- * the other calls need none). */
+ * cannot grow (prec 16 on large lattices, for as many right-hand sides at a
+ * time as memory allows; the other calls need none).  A call may be recorded
+ * in a graph, also as the first: workspace is allocated then, and what the
+ * recording holds stays in place until wcl_destroy. */
 int wcl_apply(wcl_ctx *ctx, const double *in_dev, double *out_dev, int nrhs, int dagger, int prec);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): wcl_apply
  * without any allocation.  Same arguments, layouts, ownership, results and
- * errors as wcl_apply, and it records no profiling events.  Its limit is lattices of at most 174762
- * sites (e.g. 8^4, 16^3x32): larger ones fail with WCL_EINVAL.  Calls on
+ * errors as wcl_apply, and it records no profiling events.  Its limit is
+ * lattices of at most 174762 sites (e.g. 8^4, 16^3x32): larger ones fail with
+ * WCL_EINVAL.  Calls on
  * different contexts, streams or host threads are independent.  The
  * context's resident fields come from wcl_set_gauge and wcl_set_params,
  * which do allocate. */
@@ -304,8 +308,10 @@ int wcl_profile_read(wcl_ctx *ctx, int kclass, wcl_kstat *out);
 int wcl_profile_mask(wcl_ctx *ctx, int mask);
 
 /* Not in the paper (tuning; the paper tunes its KNC kernel by loop blocking
- * and prefetching, Sec. 2).  Launch configuration of the hopping kernel:
- * threads per workgroup (64, 128,
+ * and prefetching, Sec. 2).  Launch configuration of the hopping kernel, which
+ * the solvers, the larger Dhat of wcl_apply_op and wcl_bench_hop run
+ * (wcl_apply and the other operators on canonical vectors have kernels of one
+ * shape and take the workgroup order only): threads per workgroup (64, 128,
  * 256), pipeline depth (2, 3: hops of a site whose neighbour spinor and
  * link are in flight while an earlier hop is computed), XCD-aware workgroup
  * order (0/1) and non-temporal link/clover loads (0/1; single right-hand
@@ -318,8 +324,8 @@ int wcl_autotune_hop(wcl_ctx *ctx, int prec, int copies, int *best);
  * copies the input spinors of its own half-sites into LDS and reads the
  * neighbours that fall in that range from there (in the blocked layout most
  * of a tile's hops stay inside the tile), the rest from global memory.
- * Applies to depth-2, non-dagger launches (temporal or non-temporal operator
- * loads); results are bitwise those of the unstaged kernel.  enable = 0 switches it off. */
+ * Applies to depth-2 launches (temporal or non-temporal operator loads);
+ * results are bitwise those of the unstaged kernel.  enable = 0 switches it off. */
 int wcl_set_hop_staging(wcl_ctx *ctx, int enable);
 /* Not in the paper (tuning).  The project autotuner: picks, by measurement,
  *   (flags & WCL_TUNE_HOP)    the hopping kernel's launch shape -- threads per

@@ -26,7 +26,7 @@
 using namespace wcl;
 
 // wcl_apply_noalloc takes lattices whose FP64 input and output fields fit
-// 64 MiB (the limit of its contract; it needs no scratch).
+// 64 MiB: a limit of its contract, not of the kernels, which need no scratch.
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(64) << 20;
 constexpr size_t NOALLOC_BYTES_PER_HALF_SITE = 768;   // FP64 in + out e/o fields, both parities
 
@@ -560,10 +560,11 @@ Scalars *HF(wcl_ctx *c) { return c->sc_host + 2 * c->cap; }
 
 // Scalars of n right-hand sides into the pinned host copy, everything queued
 // before them done: a kernel writes them with this read's number behind them,
-// which the host waits for.  A copy and a synchronisation leave the GPU idle for
-// longer: an inner solve reads once or more, FP32 8^3x12 5.71 -> 5.55 ms a solve,
-// FP16 24^3x32 18.3 -> 17.9.  A wait past 5 ms is left to the synchronisation,
-// which also reports a failed stream.
+// which the host waits for (not for the stream: that kernel may still be ending).
+// A copy and a synchronisation leave the GPU idle for longer, and an inner solve
+// reads once or more: 5.71 ms a solve with them, 5.55 without on FP32 8^3x12, 18.3
+// and 17.9 on FP16 24^3x32.  A wait past 5 ms is left to the synchronisation, which
+// also reports a failed stream.
 int read_sc(wcl_ctx *c, Scalars *host, const Scalars *dev, int n)
 {
     const int seq = ++c->sc_seq;
@@ -1043,9 +1044,10 @@ static int run_canon(wcl_ctx *c, int op, const double *in, double *out, int nrhs
 // FP16 tier, from 65536 sites of all right-hand sides on (below, launches
 // count): a first pass packs the spinors to FP16 e/o fields, so that the hops
 // read neighbours as 48 bytes in whole lines instead of 192 of the canonical
-// vector (D, two-row, 24^3x32: 55 us against 72 in one launch; 12 x 16^3x32: 207
-// against 233; 8^3x16: 13.0 against 12.0).  In FP32 the pass costs what it
-// saves (24^3x32: 109 against 87 us).
+// vector.  D, two-row, inputs changing from call to call, with the pass and
+// without: 12 x 16^3x32 227 and 294 us, 24^3x32 73 and 95, 65536 sites 16.3 and
+// 16.9, 8^3x16 12.7 and 11.8.  In FP32 the pass costs more than it saves
+// (24^3x32 113 and 105, full links 120 and 108).
 static bool packs_first(const wcl_ctx *c, int op, int nrhs, int prec)
 {
     return prec == 16 && op != WCL_OP_CLOVER && op != WCL_OP_CLOVER_INV && (long long)c->Vh * nrhs >= 32768;
@@ -1194,9 +1196,9 @@ int wcl_apply_noalloc(wcl_ctx *c, const double *in, double *out, int nrhs, int d
     if (need > NOALLOC_SCRATCH_BYTES) {
         char msg[200];
         snprintf(msg, sizeof msg,
-                 "wcl_apply_noalloc: this lattice needs %zu bytes of scratch; the fixed scratch holds %zu "
-                 "(lattices of at most %zu sites)",
-                 need, NOALLOC_SCRATCH_BYTES, 2 * (NOALLOC_SCRATCH_BYTES / NOALLOC_BYTES_PER_HALF_SITE));
+                 "wcl_apply_noalloc takes lattices of at most %zu sites (FP64 fields in a scratch of %zu bytes; this one "
+                 "would take %zu)",
+                 2 * (NOALLOC_SCRATCH_BYTES / NOALLOC_BYTES_PER_HALF_SITE), NOALLOC_SCRATCH_BYTES, need);
         return fail(WCL_EINVAL, msg);
     }
     const bool prof = c->prof;
@@ -1587,10 +1589,8 @@ int full_solution(wcl_ctx *c, SolveWs &w)
 }
 
 // true residuals; for FLEX the full solution is reconstructed first.  w.rel keeps
-// them while the iterates stand (w.checked), for the end of the solve, which
-// made the solution and its residual a second time.  With the difference's norm in
-// one pass and the even halves in one copy, 12 x 16^4 FP16 42.0 -> 40.6 ms, FP16
-// 24^3x32 17.27 -> 16.76, RAS 53.65 -> 53.1.
+// them while the iterates stand (w.checked), so that the end of the solve need not
+// make the solution and its residual again.
 int check_true(wcl_ctx *c, const Driver &d, SolveWs &w, const std::vector<double> &bnorm2, std::vector<double> &rel)
 {
     if (d.eo) CHK(full_solution(c, w));

@@ -860,8 +860,8 @@ hipError_t launch_inner_out(int prec, size_t Vh, const void *x, void *out64, con
 // side: the norm's step (f: the partials of |in|^2), r = rt = in / |in| in the
 // inner storage, x = 0, and the partials of <rt, r>, <r, r> for BICG_INIT_RHO.
 // p and v need no start (fresh).  Three launches with the norm's partials and the
-// step; nine before (convert, copy, four fills, two dots).  Same box, 12 x 16^4 FP16
-// 43.87 -> 42.95 ms a solve, FP16 24^3x32 18.83 -> 18.25, 8^4 FP32 9.68 -> 9.23.
+// step, where convert, copy, four fills and two dots are nine: 42.95 ms a solve
+// against 43.87 for 12 x 16^3x32 FP16, 18.25 against 18.83 on FP16 24^3x32.
 template <typename SO>
 __global__ void __launch_bounds__(256) k_inner_init(uint32_t Vh, const char *in, char *r, char *rt, char *x, Scalars *sc_all,
                                                    FoldArgs f, double *partials)
