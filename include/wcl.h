@@ -162,10 +162,11 @@ int wcl_apply_op(wcl_ctx *ctx, int op, const double *in_dev, double *out_dev, in
  * Tile cores with MR or Jacobi and an extended block of at most 648 sites
  * per parity run as one fused kernel (block vectors in LDS).  It reads
  * copies of the tier's links and clover inverse in its own order, as many
- * bytes as those fields, one pair for even and one for odd overlaps: the first
- * application of a tier and parity makes them (and waits for them), later
- * wcl_set_gauge, wcl_set_compression and wcl_set_params keep them up to date,
- * so an application recorded in a graph works on the fields of its replay.
+ * bytes as those fields, one pair for even and one for odd overlaps.  An
+ * application that lacks them makes them and waits for them;
+ * wcl_set_gauge, wcl_set_compression and wcl_set_params rewrite those used
+ * with the fields before and those that an application recorded in a graph
+ * reads, which so works on the fields of its replay.
  * Every other
  * setting runs the block solves with the block vectors in device memory
  * (the context allocates them here: 8 or 4 FP32 fields of the extended

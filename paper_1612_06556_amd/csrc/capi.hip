@@ -75,11 +75,12 @@ struct wcl_ctx {
     int device = 0;
     void *U64 = nullptr, *U32 = nullptr, *U16 = nullptr;
     void *U32c = nullptr, *U16c = nullptr;  // two-row links (built when compression is on)
-    // operator copies of the fused Schwarz kernel, per tier (ras_tier) and parity
-    // of the overlap; links and clov: made from the present fields
+    // operator copies of the fused Schwarz kernel, per tier (RAS_TIER) and parity
+    // of the overlap; links, clov: made from the present fields; used: since the
+    // last wcl_set_params; recorded: in a graph
     struct RasCopy {
         void *links_dev = nullptr, *clov_dev = nullptr;
-        bool links = false, clov = false;
+        bool links = false, clov = false, used = false, recorded = false;
     } ras_copy[4][2];
     int compress = 0;                       // FP32/FP16 tiers read the two-row links
     void *T64 = nullptr, *Ti64 = nullptr, *T32 = nullptr, *Ti32 = nullptr, *T16 = nullptr, *Ti16 = nullptr;
@@ -658,11 +659,12 @@ int ensure_gras(wcl_ctx *c)
 }
 
 // The fused Schwarz kernel's copies of the links and clover inverse in its
-// block order: one pair per tier (storage code) and parity of the overlap, made
-// by the first application that needs it and from then on wherever the fields
-// are (refresh_ras_links, refresh_ras_clover).  A buffer never changes its
-// order or its address, so an application recorded in a graph reads the fields
-// of its replay.
+// block order: one pair per tier (storage code) and parity of the overlap.  A
+// buffer never changes its order or its address, and the copies that a graph
+// holds, or that were used since the fields before, are rewritten wherever the
+// fields are (refresh_ras_links, refresh_ras_clover): an application recorded in
+// a graph reads the fields of its replay.  The others wait for an application
+// that needs them.
 constexpr int RAS_TIER[4] = {P32, P16, P32C, P16C};
 bool two_row(int lprec) { return lprec == P32C || lprec == P16C; }
 
@@ -685,27 +687,36 @@ int copy_ras_clover(wcl_ctx *c, int k, int o, hipStream_t st)
 }
 
 // After new link fields (full: the FP32 and FP16 ones, rows: the two-row ones);
-// copies whose field was not written with them wait for it.
+// copies of the others keep what they are of.
 int refresh_ras_links(wcl_ctx *c, bool full, bool rows)
 {
     for (int k = 0; k < 4; k++)
-        for (int o = 0; o < 2; o++)
-            if (c->ras_copy[k][o].links_dev && (two_row(RAS_TIER[k]) ? rows : full)) CHK(copy_ras_links(c, k, o, c->st));
+        for (int o = 0; o < 2; o++) {
+            wcl_ctx::RasCopy &r = c->ras_copy[k][o];
+            if (!(two_row(RAS_TIER[k]) ? rows : full)) continue;
+            if (r.used || r.recorded) CHK(copy_ras_links(c, k, o, c->st));
+            else r.links = false;
+        }
     return WCL_OK;
 }
 
 int refresh_ras_clover(wcl_ctx *c)
 {
     for (int k = 0; k < 4; k++)
-        for (int o = 0; o < 2; o++)
-            if (c->ras_copy[k][o].clov_dev) CHK(copy_ras_clover(c, k, o, c->st));
+        for (int o = 0; o < 2; o++) {
+            wcl_ctx::RasCopy &r = c->ras_copy[k][o];
+            if (r.used || r.recorded) CHK(copy_ras_clover(c, k, o, c->st));
+            else r.clov = false;
+            r.used = false;
+        }
     return WCL_OK;
 }
 
-// The copies for storage code lprec and the context's overlap.  The first time
-// they are made on a stream of their own and waited for, so that they are there
-// for every later call, also if the context's stream is being captured; the
-// fields are complete once wcl_set_params (or wcl_set_compression) returned.
+// The copies for storage code lprec and the context's overlap.  Those that are
+// made here are waited for, so that they are there for every later call on any
+// stream; while the context's stream is being captured they are made on another
+// one (the fields are complete once wcl_set_params or wcl_set_compression
+// returned).
 int ensure_ras_copies(wcl_ctx *c, int lprec, const void **links, const void **clov_inv)
 {
     const int o = c->ras_overlap & 1;
@@ -713,20 +724,29 @@ int ensure_ras_copies(wcl_ctx *c, int lprec, const void **links, const void **cl
     while (RAS_TIER[k] != lprec) k++;
     const size_t Vh = c->Vh;
     wcl_ctx::RasCopy &r = c->ras_copy[k][o];
-    if (!r.links || !r.clov) {
+    const bool there = r.links && r.clov;
+    bool capturing = false;
+    if (!there || !r.recorded) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->st, &status) != hipSuccess) (void)hipGetLastError();
+        capturing = status != hipStreamCaptureStatusNone;
+    }
+    if (!there) {
         OutsideCapture outside;
         if (!r.links_dev) CHK(alloc(&r.links_dev, two_row(lprec) ? link_bytes_c(lprec, Vh) : link_bytes(prec_bytes(lprec), Vh)));
         if (!r.clov_dev) CHK(alloc(&r.clov_dev, clover_bytes(prec_bytes(lprec), Vh)));
-        hipStream_t st = nullptr;
-        HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+        hipStream_t st = c->st;
+        if (capturing) HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
         int rc = copy_ras_links(c, k, o, st);
         if (rc == WCL_OK) rc = copy_ras_clover(c, k, o, st);
         const hipError_t e = hipStreamSynchronize(st);
-        (void)hipStreamDestroy(st);
+        if (capturing) (void)hipStreamDestroy(st);
         if (rc == WCL_OK && e != hipSuccess) rc = fail(WCL_EHIP, std::string("Schwarz operator copies: ") + hipGetErrorString(e));
         if (rc != WCL_OK) r.links = r.clov = false;
         CHK(rc);
     }
+    r.used = true;
+    r.recorded = r.recorded || capturing;
     *links = r.links_dev;
     *clov_inv = r.clov_dev;
     return WCL_OK;

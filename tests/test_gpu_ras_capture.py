@@ -123,3 +123,30 @@ def test_link_storage_switched_between_replays(prec):
     assert bool((_eager(lat, psi, prec) == want).all())
     _replays(graph, out, want)
     lat.close()
+
+
+@pytest.mark.parametrize("prec,comp", CASES)
+def test_copies_not_used_for_a_while(prec, comp):
+    """Field changes without an application between them, then an eager one, then
+    one only recorded; a graph recorded before all of it still follows."""
+    psi = to_gpu(synth.gaussian_spinor(DIMS, 96))
+    want = [_want(psi, prec, comp, k) for k in (0, 1)]
+    other = 48 - prec                      # the other tier's graph, the same overlap
+    want_other = [_want(psi, other, comp, k) for k in (0, 1)]
+    lat = _lattice(comp, 0)
+    g, out = _recorded(lat, psi, other)
+    assert bool((_eager(lat, psi, prec) == want[0]).all())
+    for k in (1, 0, 1):
+        _set(lat, k)
+    assert bool((_eager(lat, psi, prec) == want[1]).all())
+    for k in (1, 0):
+        _set(lat, k)
+    lat.set_params(KAPPA, 1.0)
+    late, out_late = _recorded(lat, psi, prec)
+    _replays(late, out_late, want[0])
+    _replays(g, out, want_other[0])
+    for k in (1, 0, 1):
+        _set(lat, k)
+    _replays(late, out_late, want[1])
+    _replays(g, out, want_other[1])
+    lat.close()
